@@ -7,8 +7,10 @@
 //             and the depth sums of the loss and of its gradient with respect
 //             to the A-scan's displacement; one depth sample per lane (float32
 //             storage, and 16-bit volumes of odd depth in the caller's layout)
-//   k_struct2 the same with two 16-bit samples per lane (every level a pair
-//             stores: an odd depth is stored with one padding sample)
+//   k_struct2 the same with two 16-bit samples per lane (small levels: an odd
+//             depth is stored with one padding sample)
+//   k_struct_mx the same for 16-bit volumes of many A-scans, the lateral
+//             resampling on the matrix cores
 //   k_struct_multi, k_struct_multi1  the structural partials of every volume
 //             pair of n = 3 or 4 volumes, each volume resampled once
 //   k_combine per output A-scan: en face residual (Eq. 7), resampled
@@ -704,6 +706,670 @@ __global__ __launch_bounds__(256) void k_struct2(const StructJobs jobs)
 }
 
 // ---------------------------------------------------------------------------
+// k_struct_mx: the structural data term on the matrix cores.
+//
+// One wave evaluates a 2 x 2 tile of output A-scans.  Per scan the distinct
+// source columns of the tile's four 4 x 4 lateral stencils (25 for a smooth
+// field instead of 64) are the inner dimension of a small contraction,
+//   D[4 g + o][k] = sum_slot W[4 g + o][slot] V[slot][k],
+// whose rows are the lateral blends o = value, x derivative, y derivative of
+// A-scan g and whose columns are source depths.  W holds the Catmull-Rom
+// products; a slot outside an A-scan's stencil has weight 0, so any set of
+// displacements is served: 32 slots take one matrix product per depth tile,
+// up to 48 a second one, and a tile with more (disjoint stencils) is evaluated
+// two A-scans at a time.
+// The products are v_mfma_f32_16x16x32 on the stored 16-bit samples.  The
+// float32 weights enter as three 16-bit parts, each the rest rounded to
+// nearest, whose sum is the weight exactly (BF16: three times 8 bits; FP16: 11 +
+// 11 + 2 bits of the weight times 2^12, undone in the depth taps), so the
+// products are those of a float32 blend and no sample is converted.  The
+// leading parts are summed first: an addend smaller than the products it is
+// added to loses bits to truncation, a larger one is rounded to nearest
+// (measured on S_str of 500 x 500 x 800 in BF16, against 64 bits: 1.3e-8 off;
+// leading parts last and split by truncation, -0.8e-8; the vector kernels
+// 1.8e-8, which is the reciprocals' of the loss).
+// Lane 16 g + n then holds the blends of A-scan g at L consecutive source
+// depths of a window, and everything along depth (interpolation of Eq. 2,
+// residual, loss of Eq. 4, its adjoint) runs on the vector units in that
+// layout, the neighbouring depths coming from the next lane of the row (DPP).
+constexpr int kMxSlots = 48;
+constexpr int kMxLimit = 1 << 28;  // positions beyond this lie outside every volume
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// Depth windows: a lane holds L consecutive source depths (one load per
+// column), a row of 16 lanes a window of 16 L.  An A-scan's window starts
+// sh = 0 .. 3 samples before its first depth tap, at an even depth (loads off a
+// 4-byte boundary take up to four times as long); A-scans with a common start
+// share their columns' loads.  Position p of the X-fast scan's window holds the
+// first tap of output kOut step + p - sh; the Y-fast scan's blends are moved to
+// the same positions.
+template <int L>
+struct MxGeo {
+    static constexpr int kWin = 16 * L;
+    static constexpr int kShift = 3;
+    static constexpr int kOut = kWin - 3 - kShift;  // outputs per step (four taps, the move), even
+};
+
+// A lane's samples of one column.
+template <int N>
+struct MxDwords;
+template <>
+struct MxDwords<2> {
+    typedef i32x2 type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
+    {
+        return __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+    }
+};
+template <>
+struct MxDwords<4> {
+    typedef i32x4 type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+    }
+};
+
+// Matrix products.  A operands live in the LDS: of slot 4 q + kg (q = 0 .. 7)
+// row m is element q of lane 16 kg + m; slots 32 .. 47 likewise with q = 0 .. 3.
+template <typename T>
+struct MxOps;
+
+// the two samples of dword p of slots 2 t, 2 t + 1 of a lane, as the B operands of their depths
+template <int NQ, typename S, typename B>
+__device__ __forceinline__ void mx_pack(const S (&v)[NQ], int p, B& b0, B& b1)
+{
+#pragma unroll
+    for (int t = 0; t < NQ / 2; ++t) {
+        const unsigned lo = (unsigned)v[2 * t][p], hi = (unsigned)v[2 * t + 1][p];
+        b0[t] = (int)__builtin_amdgcn_perm(hi, lo, 0x05040100u);
+        b1[t] = (int)__builtin_amdgcn_perm(hi, lo, 0x07060302u);
+    }
+}
+
+template <>
+struct MxOps<bf16_t> {
+    static constexpr float kUnscale = 1.f;
+    static __device__ __forceinline__ void split_weight(float w, unsigned short (&p)[3])
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const __bf16 hp = (__bf16)w;
+            p[k] = __builtin_bit_cast(unsigned short, hp);
+            w -= (float)hp;
+        }
+    }
+    static __device__ __forceinline__ f32x4 mfma(i32x4 a, i32x4 b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    }
+    static __device__ __forceinline__ f32x4 mfma(i32x2 a, i32x2 b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c,
+                                                         0, 0, 0);
+    }
+};
+
+template <>
+struct MxOps<f16_t> {
+    // binary16 has no room below 2^-24 for the trailing bits of a weight: the
+    // weights are scaled by 2^12 (the largest is below 2) and the depth taps
+    // by 2^-12, both exact
+    static constexpr float kUnscale = 1.f / 4096.f;
+    static __device__ __forceinline__ void split_weight(float w, unsigned short (&p)[3])
+    {
+        float r = w * 4096.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const _Float16 hp = (_Float16)r;
+            p[k] = __builtin_bit_cast(unsigned short, hp);
+            r -= (float)hp;
+        }
+    }
+    static __device__ __forceinline__ f32x4 mfma(i32x4 a, i32x4 b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
+                                                      0, 0);
+    }
+    static __device__ __forceinline__ f32x4 mfma(i32x2 a, i32x2 b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0,
+                                                     0, 0);
+    }
+};
+
+// Per-wave LDS of k_struct_mx.
+template <typename T, int L>
+struct MxLds {
+    struct Scan {
+        i32x4 a[3][64];   // weights of slots 0 .. 31, per part
+        i32x2 a1[3][64];  // weights of slots 32 .. 47
+    } w[2];
+    float edge[L][64];
+    int2 key[2][64];
+};
+
+// The lanes of a wave exchange data through their own part of the LDS, whose
+// accesses complete in order: only the compiler has to keep that order.
+__device__ __forceinline__ void mx_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Lane shifts within a row of 16 lanes (DPP); the row's end reads 0.
+__device__ __forceinline__ float row_next(float v)  // lane l gets lane l + 1's value
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x101, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float row_prev(float v)  // lane l gets lane l - 1's value
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x111, 0xF, 0xF, true));
+}
+// sum over a row of 16 lanes, left in its last lane
+__device__ __forceinline__ float row_sum_last(float x)
+{
+    float v = row_shr_add<1>(x);
+    v = row_shr_add<2>(v);
+    v = row_shr_add<4>(v);
+    return row_shr_add<8>(v);
+}
+
+// Per-scan state of one wave's tile.
+struct MxScan {
+    uint32_t off[8];     // byte offset of this lane's samples in the columns of slots 4 q + kg at depth zlo
+    float wz[4], dwz[4]; // depth taps of this lane's A-scan and their derivatives
+    int zb;              // source depth of window position 0 of this lane's A-scan at step 0
+    int sh;              // position of the first depth tap
+    int any;             // sh of the tile's A-scans, or-ed (wave-uniform)
+    int zlo, zhi;        // smallest and largest zb of the tile (wave-uniform)
+    int ns;              // slots (wave-uniform)
+};
+
+// The slots, weights and depth taps of one scan.  Lane 16 g + n stands for tap
+// n of A-scan ag (at pg) of group g.  disp: the scan's field [na][3]; lead:
+// position of the A-scan's output 0 (the window is laid out as if its first tap
+// lay that much earlier); groups: bit mask of the groups whose stencils are
+// laid out.
+template <typename T, int L>
+__device__ __forceinline__ void mx_setup(MxScan& S, MxLds<T, L>& M, int V, const float* disp, int ag, int2 pg, int lead,
+                                         int w, int h, int dp, int lane, int groups)
+{
+    typedef MxGeo<L> Geo;
+    typedef MxOps<T> Ops;
+    const int g = lane >> 4, n = lane & 15, kg = g;
+    int nx, ny, nz;
+    float tx, ty, tz;
+    split(pg.x, disp[(size_t)ag * 3], nx, tx);
+    split(pg.y, disp[(size_t)ag * 3 + 1], ny, ty);
+    split(0, disp[(size_t)ag * 3 + 2], nz, tz);
+    nx = min(max(nx, -kMxLimit), kMxLimit);
+    ny = min(max(ny, -kMxLimit), kMxLimit);
+    nz = min(max(nz, -kMxLimit), kMxLimit) - 1 - lead;  // source sample of the first tap of output 0, less lead
+    // the tile's stencil origins, wave-uniform
+    int ox[4], oy[4], oz[4], zb[4];
+    int zmin = kMxLimit;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        ox[q] = __builtin_amdgcn_readlane(nx, 16 * q) - 1;
+        oy[q] = __builtin_amdgcn_readlane(ny, 16 * q) - 1;
+        oz[q] = __builtin_amdgcn_readlane(nz, 16 * q);
+        if (groups >> q & 1) zmin = min(zmin, oz[q]);
+    }
+    zmin &= -2;
+    S.any = 0;
+    S.zlo = kMxLimit;
+    S.zhi = -2 * kMxLimit;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int sh = (oz[q] - zmin) & Geo::kShift;
+        zb[q] = oz[q] - sh;
+        S.any |= sh;
+        S.zlo = min(S.zlo, zb[q]);
+        S.zhi = max(S.zhi, zb[q]);
+    }
+    S.any = uni(S.any);
+    S.zlo = uni(S.zlo);
+    S.zhi = uni(S.zhi);
+    S.sh = (nz - zmin) & Geo::kShift;
+    S.zb = nz - S.sh;
+    cr_taps(tz, S.wz, S.dwz);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        S.wz[c] *= Ops::kUnscale;
+        S.dwz[c] *= Ops::kUnscale;
+    }
+    // Distinct columns: a lane's column is that of the first group's lane that
+    // reaches the same column with the same window.
+    const int cx = nx - 1 + (n & 3), cy = ny - 1 + (n >> 2);
+    int owner = lane;
+#pragma unroll
+    for (int q = 2; q >= 0; --q) {
+        const int a = cx - ox[q], b = cy - oy[q];
+        const bool same = (q < g) & ((groups >> q & 1) != 0) & ((unsigned)a < 4u) & ((unsigned)b < 4u) & (S.zb == zb[q]);
+        owner = same ? 16 * q + 4 * b + a : owner;
+    }
+    const bool active = (groups >> g & 1) != 0;
+    const bool mine = active & (owner == lane);
+    const unsigned long long mask = __ballot(mine);
+    S.ns = uni((int)__popcll(mask));
+    if (S.ns > kMxSlots) return;  // the caller takes fewer groups
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+    const int slot = __builtin_amdgcn_ds_bpermute(4 * owner, rank);
+    // weights: 0 but for the rows of an A-scan in the slots of its columns.
+    // Unused slots: an offset beyond the volume, whose loads return 0.
+    typename MxLds<T, L>::Scan& W = M.w[V];
+    const i32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) W.a[k][lane] = zero;
+    if (S.ns > 32) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) W.a1[k][lane] = i32x2{0, 0};
+    }
+    M.key[V][lane] = make_int2((int)0x80000000u, (int)0x80000000u);
+    mx_lds_fence();
+    if (mine) {
+        const int col = min(max(cy, 0), h - 1) * w + min(max(cx, 0), w - 1);
+        M.key[V][slot] = make_int2((int)((uint32_t)col * (uint32_t)dp * 2u), S.zb);
+    }
+    {
+        float wx[4], dwx[4], wy[4], dwy[4];
+        cr_taps(tx, wx, dwx);
+        cr_taps(ty, wy, dwy);
+        const int a = n & 3, b = n >> 2;
+        float vx = wx[0], gx = dwx[0], vy = wy[0], gy = dwy[0];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) {
+            vx = a == c ? wx[c] : vx;
+            gx = a == c ? dwx[c] : gx;
+            vy = b == c ? wy[c] : vy;
+            gy = b == c ? dwy[c] : gy;
+        }
+        const float wt[3] = {vx * vy, gx * vy, vx * gy};
+        const int q = (slot & 31) >> 2, row = 16 * (slot & 3) + 4 * g;
+        unsigned short* a0 = reinterpret_cast<unsigned short*>(&W.a[0][0]) + row * 8 + q;
+        unsigned short* a1 = reinterpret_cast<unsigned short*>(&W.a1[0][0]) + row * 4 + q;
+        unsigned short p[3][3];
+#pragma unroll
+        for (int o = 0; o < 3; ++o) Ops::split_weight(wt[o], p[o]);
+        if (active & (slot < 32)) {
+#pragma unroll
+            for (int o = 0; o < 3; ++o)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) a0[(k * 64 + o) * 8] = p[o][k];
+        }
+        if (active & (slot >= 32)) {
+#pragma unroll
+            for (int o = 0; o < 3; ++o)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) a1[(k * 64 + o) * 4] = p[o][k];
+        }
+    }
+    mx_lds_fence();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int2 k = M.key[V][4 * q + kg];
+        S.off[q] = (uint32_t)k.x + (uint32_t)((max(k.y, S.zlo) - S.zlo + L * n) * 2);
+    }
+}
+
+// wave-uniform: no window of the tile reaches over an end of the A-scans
+template <typename Geo>
+__device__ __forceinline__ bool mx_inside(const MxScan& S, int step, int dp)
+{
+    return S.zlo + Geo::kOut * step >= 0 && S.zhi + Geo::kOut * step + Geo::kWin <= dp;
+}
+
+// The samples of one depth step of one scan: kL depths of slots 4 q + kg.
+template <typename T, int L>
+__device__ __forceinline__ void mx_load(typename MxDwords<L / 2>::type (&s)[8], const MxScan& S,
+                                        const MxLds<T, L>& M, int V, __amdgpu_buffer_rsrc_t r, int step, int dp, int lane)
+{
+    typedef MxGeo<L> Geo;
+    const int n = lane & 15, kg = lane >> 4, z0 = Geo::kOut * step;
+    const bool inside = mx_inside<Geo>(S, step, dp);
+    const uint32_t soff = (uint32_t)uni(inside ? (S.zlo + z0) * 2 : 0);
+    uint32_t off[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) off[q] = S.off[q];
+    if (!inside) {
+        if (S.zlo == S.zhi) {  // one window start: the clamped depth replaces the lane's own
+            const int m = min(max(S.zlo + z0 + L * n, 0), dp - L);
+            const uint32_t delta = (uint32_t)((m - L * n) * 2);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) off[q] += delta;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int2 k = M.key[V][4 * q + kg];
+                const int m = min(max(k.y + z0 + L * n, 0), dp - L);
+                off[q] = (uint32_t)k.x + (uint32_t)(m * 2);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s[q] = MxDwords<L / 2>::load(r, off[q], soff);
+}
+
+// D = the blends of slots 0 .. 31 of scan V, whose samples are s
+template <typename T, int L, typename S>
+__device__ __forceinline__ void mx_blend(f32x4 (&D)[L], const S (&s)[8], const MxLds<T, L>& M, int V, int lane)
+{
+    const i32x4 a0 = M.w[V].a[0][lane], a1 = M.w[V].a[1][lane], a2 = M.w[V].a[2][lane];
+#pragma unroll
+    for (int p = 0; p < L / 2; ++p) {
+        i32x4 b0, b1;
+        mx_pack(s, p, b0, b1);
+        D[2 * p] = MxOps<T>::mfma(a0, b0, D[2 * p]);
+        D[2 * p + 1] = MxOps<T>::mfma(a0, b1, D[2 * p + 1]);
+        D[2 * p] = MxOps<T>::mfma(a1, b0, D[2 * p]);
+        D[2 * p + 1] = MxOps<T>::mfma(a1, b1, D[2 * p + 1]);
+        D[2 * p] = MxOps<T>::mfma(a2, b0, D[2 * p]);
+        D[2 * p + 1] = MxOps<T>::mfma(a2, b1, D[2 * p + 1]);
+    }
+}
+
+// D += the blends of slots 32 .. 47 (only where a tile has them)
+template <typename T, int L>
+__device__ __forceinline__ void mx_rest(f32x4 (&D)[L], const MxLds<T, L>& M, int V, __amdgpu_buffer_rsrc_t r, int step,
+                                        int dp, int lane)
+{
+    typedef MxGeo<L> Geo;
+    const int n = lane & 15, kg = lane >> 4, z0 = Geo::kOut * step;
+    typename MxDwords<L / 2>::type s[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int2 k = M.key[V][32 + 4 * q + kg];
+        const int m = min(max(k.y + z0 + L * n, 0), dp - L);
+        s[q] = MxDwords<L / 2>::load(r, (uint32_t)k.x + (uint32_t)(m * 2), 0);
+    }
+    const i32x2 a0 = M.w[V].a1[0][lane], a1 = M.w[V].a1[1][lane], a2 = M.w[V].a1[2][lane];
+#pragma unroll
+    for (int p = 0; p < L / 2; ++p) {
+        i32x2 b0, b1;
+        mx_pack(s, p, b0, b1);
+        D[2 * p] = MxOps<T>::mfma(a0, b0, D[2 * p]);
+        D[2 * p + 1] = MxOps<T>::mfma(a0, b1, D[2 * p + 1]);
+        D[2 * p] = MxOps<T>::mfma(a1, b0, D[2 * p]);
+        D[2 * p + 1] = MxOps<T>::mfma(a1, b1, D[2 * p + 1]);
+        D[2 * p] = MxOps<T>::mfma(a2, b0, D[2 * p]);
+        D[2 * p + 1] = MxOps<T>::mfma(a2, b1, D[2 * p + 1]);
+    }
+}
+
+// L samples read at clamp(m, 0, dp - L), moved to m .. m + L - 1 with the edge
+// value beyond the A-scan: every wanted sample is among the lane's own, so the
+// move is an indexed read of them (through the lane's column of sh).
+template <int L>
+__device__ __forceinline__ void mx_edge(float (&v)[L], const int (&at)[L], float (*sh)[64], int lane)
+{
+#pragma unroll
+    for (int i = 0; i < L; ++i) sh[i][lane] = v[i];
+    mx_lds_fence();
+#pragma unroll
+    for (int i = 0; i < L; ++i) v[i] = sh[at[i]][lane];
+    mx_lds_fence();
+}
+
+// v moved K samples down (from the next lane's first ones) where `on`
+template <int K, int L>
+__device__ __forceinline__ void mx_move(float (&v)[L], bool on)
+{
+    float nx[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) nx[i] = row_next(v[i]);
+#pragma unroll
+    for (int i = 0; i < L; ++i) v[i] = on ? (i + K < L ? v[i + K < L ? i + K : 0] : nx[i + K >= L ? i + K - L : 0]) : v[i];
+}
+
+// The lateral blends (value, x and y derivative) of this lane's A-scan at its L
+// positions: the edge values beyond the A-scan, then (MOVE) the window's shift.
+template <typename T, int L, bool MOVE>
+__device__ __forceinline__ void mx_rows(float (&v)[L], float (&vx)[L], float (&vy)[L], const f32x4 (&D)[L],
+                                        const MxScan& S, MxLds<T, L>& M, int step, int dp, int lane)
+{
+    typedef MxGeo<L> Geo;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+        v[i] = D[i][0];
+        vx[i] = D[i][1];
+        vy[i] = D[i][2];
+    }
+    if (!mx_inside<Geo>(S, step, dp)) {
+        const int m = S.zb + Geo::kOut * step + L * (lane & 15), mc = min(max(m, 0), dp - L);
+        int at[L];
+#pragma unroll
+        for (int i = 0; i < L; ++i) at[i] = min(max(m + i, 0), dp - 1) - mc;
+        mx_edge<L>(v, at, M.edge, lane);
+        mx_edge<L>(vx, at, M.edge, lane);
+        mx_edge<L>(vy, at, M.edge, lane);
+    }
+    if (MOVE && (S.any & 1)) {
+        mx_move<1>(v, S.sh & 1);
+        mx_move<1>(vx, S.sh & 1);
+        mx_move<1>(vy, S.sh & 1);
+    }
+    if (MOVE && (S.any & 2)) {
+        mx_move<2>(v, S.sh & 2);
+        mx_move<2>(vx, S.sh & 2);
+        mx_move<2>(vy, S.sh & 2);
+    }
+}
+
+// sum_c w[c] x[i + c] (x: this lane's positions and three of the next lane's)
+template <int N>
+__device__ __forceinline__ float mx_fir(const float (&w)[4], const float (&x)[N], int i)
+{
+    float s = w[0] * x[i];
+#pragma unroll
+    for (int c = 1; c < 4; ++c) s = fmaf(w[c], x[i + c], s);
+    return s;
+}
+
+// The seven sums of an A-scan, one part of them per lane of its row.
+struct MxSums {
+    float lam = 0.f, gxx = 0.f, gyx = 0.f, gzx = 0.f, gxy = 0.f, gyy = 0.f, gzy = 0.f;
+    __device__ __forceinline__ void reduce()  // to the row's last lane
+    {
+        lam = row_sum_last(lam);
+        gxx = row_sum_last(gxx);
+        gyx = row_sum_last(gyx);
+        gzx = row_sum_last(gzx);
+        gxy = row_sum_last(gxy);
+        gyy = row_sum_last(gyy);
+        gzy = row_sum_last(gzy);
+    }
+    __device__ __forceinline__ bool finite() const
+    {
+        return __builtin_isfinite(((lam + gxx) + (gyx + gzx)) + ((gxy + gyy) + gzy));
+    }
+    __device__ __forceinline__ void store(float* p) const
+    {
+        float4* o = reinterpret_cast<float4*>(p);
+        o[0] = make_float4(lam, gxx, gyx, gzx);
+        o[1] = make_float4(gxy, gyy, gzy, 0.f);
+    }
+};
+
+// The depth work of one step on the lateral blends of both scans (value x, y
+// with three positions of the next lane; x and y derivatives xx, xy, yx, yy).
+// ie_lo, ie_hi: 1 / eps for the first two positions and the others, or 0.
+// ends (wave-uniform): only those of the outputs o0 + i that are 0 .. d - 1 count.
+template <int L>
+__device__ __forceinline__ void mx_depth(MxSums& A, const float (&x)[L + 3], const float (&xx)[L], const float (&xy)[L],
+                                         const float (&y)[L + 3], const float (&yx)[L], const float (&yy)[L],
+                                         const float (&wx)[4], const float (&dwx)[4], const float (&wy)[4],
+                                         const float (&dwy)[4], float ie_lo, float ie_hi, bool ends, int o0,
+                                         int d)
+{
+    // depth interpolation (Eq. 2) and residual over eps
+    float u[L];
+#pragma unroll
+    for (int i = 0; i < L; ++i) u[i] = (mx_fir(wx, x, i) - mx_fir(wy, y, i)) * (i < 2 ? ie_lo : ie_hi);
+    if (ends) {
+#pragma unroll
+        for (int i = 0; i < L; ++i) u[i] = (unsigned)(o0 + i) < (unsigned)d ? u[i] : 0.f;
+    }
+    // pseudo-Huber loss (Eq. 4) eps u^2 / (sqrt(1 + u^2) + 1) and its derivative u / sqrt(1 + u^2)
+    float G[L + 3];  // G[3 + i]: this lane's position i; G[0 .. 2]: the lane before
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+        const float q = u[i] * u[i];
+        const float rs = __builtin_amdgcn_rsqf(1.f + q), sq = (1.f + q) * rs;
+        A.lam = fmaf(q, __builtin_amdgcn_rcpf(sq + 1.f), A.lam);
+        G[3 + i] = u[i] * rs;
+        A.gzx = fmaf(G[3 + i], mx_fir(dwx, x, i), A.gzx);
+        A.gzy = fmaf(G[3 + i], mx_fir(dwy, y, i), A.gzy);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) G[i] = row_prev(G[L + i]);
+    // adjoint of the depth interpolation: position p collects the outputs p - 3 .. p
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+        float hx = wx[0] * G[3 + i], hy = wy[0] * G[3 + i];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) {
+            hx = fmaf(wx[c], G[3 + i - c], hx);
+            hy = fmaf(wy[c], G[3 + i - c], hy);
+        }
+        A.gxx = fmaf(hx, xx[i], A.gxx);
+        A.gyx = fmaf(hx, xy[i], A.gyx);
+        A.gxy = fmaf(hy, yx[i], A.gxy);
+        A.gyy = fmaf(hy, yy[i], A.gyy);
+    }
+}
+
+// The tile of a wave: 4 x 4 A-scans per workgroup in 8 bands of block rows (one
+// per XCD when the job fills the grid), swept column by column, so that the
+// rows a block reads are still in that XCD's L2 when the next column reads
+// them.  False: a whole block beyond the job's, or a wave outside the scan.
+__device__ __forceinline__ bool mx_tile(const StructJob& J, int t, int wv, int& i0, int& j0)
+{
+    const int bpr = (J.w + 3) >> 2;
+    const int brows = (J.h + 3) >> 2;
+    const int rpb = (brows + 7) >> 3;
+    const int band = t / (rpb * bpr), tb = t - band * (rpb * bpr);
+    const int brow = band * rpb + tb % rpb;
+    i0 = 4 * (tb / rpb) + 2 * (wv & 1);
+    j0 = 4 * brow + 2 * (wv >> 1);
+    return t < 8 * rpb * bpr && brow < brows && i0 < J.w && j0 < J.h;
+}
+
+// Bound by vector issue: a step of eight depths per lane takes some 440 vector
+// and 48 matrix instructions (16 cycles each, partly overlapped), of which the
+// depth work is 46 per sample pair and the operand packing 8.  Three waves per
+// SIMD: 168 registers; two waves with the next step's samples loaded ahead
+// measured 25 % slower, and so did one workgroup barrier per step to share L1
+// lines.  The lateral blends and their adjoint took k_struct2 128 FMAs and 64
+// conversions per 122 outputs of one A-scan, and its 64 loads of 256 bytes per
+// step of a tile are 16 of 1 KB here.  500 x 500 x 800 in BF16: 1.058 -> 0.578
+// ms (66 TFLOP/s of the method's operations), 500 x 500 x 465 in FP16: 0.645 ->
+// 0.386, 300 x 300 x 233 in BF16 0.160 -> 0.098 ms.
+template <typename T, int L>
+__global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
+{
+    if (jobs.skip && *jobs.skip) return;
+    __shared__ MxLds<T, L> lds[4];
+    const int wv = uni((int)(threadIdx.x >> 6));
+    MxLds<T, L>& M = lds[wv];
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
+    int jid = -1;
+    for (int q = 0; q < jobs.n; ++q)
+        if (lb >= jobs.j[q].blk_begin) jid = q;
+    if (jid < 0) return;  // whole block
+    const StructJob& J = jobs.j[jid];
+    const int w = J.w, h = J.h, d = J.d, dp = J.dp;
+    int i0, j0;
+    if (!mx_tile(J, lb - J.blk_begin, wv, i0, j0)) return;
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.sx), (short)0, (int)J.vol_bytes, kRsrcWord3);
+    const __amdgpu_buffer_rsrc_t ry =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.sy), (short)0, (int)J.vol_bytes, kRsrcWord3);
+    typedef MxGeo<L> Geo;
+    const float eps = J.eps_h;
+    const float inv_eps = 1.0f / J.eps_h;
+    // The groups of the tile evaluated together: all four; two where the four
+    // need too many slots; one at a time where a sample is not finite, since
+    // it reaches every A-scan of the tile through the weights 0.
+    int groups = 15;
+    for (;;) {
+        // opaque to the compiler, which otherwise keeps the set-up's addresses
+        // for a second round in registers it does not have
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int g = lane >> 4;
+        const bool last = (lane & 15) == 15;
+        const int p0 = L * (lane & 15);  // this lane's first position
+        // an A-scan outside the scan repeats its neighbour and is not written
+        const int2 pg = make_int2(min(i0 + (g & 1), w - 1), min(j0 + (g >> 1), h - 1));
+        const bool inscan = i0 + (g & 1) < w && j0 + (g >> 1) < h;
+        const int ag = pg.y * w + pg.x;
+        // 1 / eps for this lane's first two positions and the others, 0 where they
+        // are no outputs: no residual, loss or derivative there
+        static_assert(Geo::kOut % L == 0 || Geo::kOut % L == 2, "two classes of positions");
+        const float ie_lo = p0 < Geo::kOut ? inv_eps : 0.f, ie_hi = p0 + 2 < Geo::kOut ? inv_eps : 0.f;
+        MxScan SX, SY;
+        mx_setup<T, L>(SX, M, 0, J.disp, ag, pg, 0, w, h, dp, lane, groups);
+        mx_setup<T, L>(SY, M, 1, J.disp + (size_t)J.na * 3, ag, pg, SX.sh, w, h, dp, lane, groups);
+        if (max(SX.ns, SY.ns) > kMxSlots) {  // only four groups can
+            groups = 3;
+            continue;
+        }
+        MxSums A;
+        const int nsteps = (d + SX.any + Geo::kOut - 1) / Geo::kOut;  // the last output's position: at most d - 1 + any
+        for (int s = 0; s < nsteps; ++s) {
+            float x[L + 3], xx[L], xy[L], y[L + 3], yx[L], yy[L];
+            {
+                typename MxDwords<L / 2>::type qx[8], qy[8];
+                mx_load<T, L>(qx, SX, M, 0, rx, s, dp, lane);
+                mx_load<T, L>(qy, SY, M, 1, ry, s, dp, lane);
+                float v[L];
+                f32x4 D[L] = {};
+                mx_blend<T, L>(D, qx, M, 0, lane);
+                if (SX.ns > 32) mx_rest<T, L>(D, M, 0, rx, s, dp, lane);
+                mx_rows<T, L, false>(v, xx, xy, D, SX, M, s, dp, lane);
+#pragma unroll
+                for (int i = 0; i < L; ++i) x[i] = v[i];
+                f32x4 E[L] = {};
+                mx_blend<T, L>(E, qy, M, 1, lane);
+                if (SY.ns > 32) mx_rest<T, L>(E, M, 1, ry, s, dp, lane);
+                mx_rows<T, L, true>(v, yx, yy, E, SY, M, s, dp, lane);
+#pragma unroll
+                for (int i = 0; i < L; ++i) y[i] = v[i];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                x[L + i] = row_next(x[i]);
+                y[L + i] = row_next(y[i]);
+            }
+            mx_depth<L>(A, x, xx, xy, y, yx, yy, SX.wz, SX.dwz, SY.wz, SY.dwz, ie_lo, ie_hi,
+                        s == 0 || Geo::kOut * (s + 1) > d, Geo::kOut * s + p0 - SX.sh, d);
+        }
+        A.lam *= eps;
+        A.reduce();
+        const bool active = groups >> g & 1;
+        if (last && inscan && active) A.store(J.part + (size_t)ag * 8);
+        const bool bad = __ballot(last && active && !A.finite()) != 0;
+        if (groups & (groups - 1)) {  // several groups
+            if (bad) groups = 1;
+            else if (groups == 3) groups = 12;
+            else return;
+        } else {
+            if (groups == 8) return;
+            groups <<= 1;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // deterministic block reduction helpers
 
 template <int N>
@@ -1354,34 +2020,48 @@ hipError_t launch_sum(const SumJobs& jobs, int total_blocks, hipStream_t s)
     return hipGetLastError();
 }
 
+// The kernel that serves a job of 16-bit volumes (0 .. 3).  The choice is made
+// by the job's own sizes, so its result does not depend on the other jobs of
+// its launch; each kernel's jobs have their own grid (a multiple of the 8 XCDs).
+//   k_struct_mx needs some thousands of tiles to fill the device; with fewer,
+//   the one-A-scan kernels, whose waves are shorter, are as fast or faster
+//   (64 x 64 x 128: 14 against 18 us, 64 x 64 x 400: 18 against 25, 90 x 90 x
+//   400: 31 against 29, 128 x 128 x 256: 43 against 32).
+//   Its depths per lane: eight, since a 128-bit load brings twice the samples
+//   of a 64-bit one in the same time, unless windows of four leave enough
+//   fewer positions unused (a window of four costs 1.2 times half of one of
+//   eight); four where an A-scan has fewer than eight samples.
+//   k_struct2 loads sample pairs, 32-bit aligned at an even storage pitch
+//   (every level of a pair); an odd pitch (volumes in the caller's layout)
+//   takes one sample per lane.
+constexpr int kMxMinAscans = 8192;
+enum { kByMx8, kByMx4, kByPairs, kBySamples };
+static int struct_form(const StructJob& J, bool axial)
+{
+    if (axial || J.na < kMxMinAscans) return J.dp % 2 == 0 ? kByPairs : kBySamples;
+    const int n8 = (J.d + MxGeo<8>::kOut - 1) / MxGeo<8>::kOut, n4 = (J.d + MxGeo<4>::kOut - 1) / MxGeo<4>::kOut;
+    return J.dp >= 8 && 17 * n8 <= 10 * n4 ? kByMx8 : kByMx4;
+}
+
 template <typename T, bool AXIAL>
 static hipError_t launch_struct_subsets(const StructJobs& jobs, hipStream_t s)
 {
-    // 16-bit storage: two samples per lane for the jobs whose storage pitch
-    // is even (every level of a pair: an odd depth is stored with one padding
-    // sample); an odd pitch (volumes in the caller's layout with an odd depth)
-    // keeps one sample per lane, since its sample pairs would not all be
-    // 32-bit aligned.  The kernel is chosen per job, so a job's result does not
-    // depend on the other jobs of its launch; each subset has its own grid (a
-    // multiple of the 8 XCDs).
-    StructJobs even{}, odd{};
-    even.skip = odd.skip = jobs.skip;
-    int be = 0, bo = 0;
+    StructJobs part[4]{};
+    int nb[4] = {0, 0, 0, 0};
     for (int q = 0; q < jobs.n; ++q) {
         StructJob J = jobs.j[q];
-        const int nb = struct_blocks(J.w, J.h);
-        if (J.dp % 2 == 0) {
-            J.blk_begin = be;
-            be += nb;
-            even.j[even.n++] = J;
-        } else {
-            J.blk_begin = bo;
-            bo += nb;
-            odd.j[odd.n++] = J;
-        }
+        const int k = struct_form(J, AXIAL);
+        J.blk_begin = nb[k];
+        nb[k] += k <= kByMx4 ? struct_mx_blocks(J.w, J.h) : struct_blocks(J.w, J.h);
+        part[k].j[part[k].n++] = J;
     }
-    if (even.n) hipLaunchKernelGGL((k_struct2<T, AXIAL>), dim3((be + 7) / 8 * 8), dim3(256), 0, s, even);
-    if (odd.n) hipLaunchKernelGGL((k_struct<T, AXIAL>), dim3((bo + 7) / 8 * 8), dim3(256), 0, s, odd);
+    for (auto& P : part) P.skip = jobs.skip;
+    if constexpr (!AXIAL) {
+        if (nb[kByMx8]) hipLaunchKernelGGL((k_struct_mx<T, 8>), dim3(nb[kByMx8]), dim3(256), 0, s, part[kByMx8]);
+        if (nb[kByMx4]) hipLaunchKernelGGL((k_struct_mx<T, 4>), dim3(nb[kByMx4]), dim3(256), 0, s, part[kByMx4]);
+    }
+    if (nb[kByPairs]) hipLaunchKernelGGL((k_struct2<T, AXIAL>), dim3(nb[kByPairs]), dim3(256), 0, s, part[kByPairs]);
+    if (nb[kBySamples]) hipLaunchKernelGGL((k_struct<T, AXIAL>), dim3(nb[kBySamples]), dim3(256), 0, s, part[kBySamples]);
     return hipGetLastError();
 }
 

@@ -141,6 +141,9 @@ struct StructJobs {
 // Blocks of one structural job: one 2 x 2 tile of A-scans per block, in 8
 // bands of whole tile rows (one per XCD).
 inline int struct_blocks(int w, int h) { return 8 * (((h + 1) / 2 + 7) / 8) * ((w + 1) / 2); }
+// Blocks of one job of the matrix-core structural kernel: 4 x 4 A-scans per
+// block (a 2 x 2 tile per wave), in 8 bands of whole block rows.
+inline int struct_mx_blocks(int w, int h) { return 8 * (((h + 3) / 4 + 7) / 8) * ((w + 3) / 4); }
 
 // Hot path, step 0: sum of the displacements (for the mean term M), as one
 // row of block partials per block (summed in a fixed order by its readers).
