@@ -11,8 +11,9 @@
 //             depth is stored with one padding sample)
 //   k_struct_mx the same for 16-bit volumes of many A-scans, the lateral
 //             resampling on the matrix cores
-//   k_struct_multi, k_struct_multi1  the structural partials of every volume
-//             pair of n = 3 or 4 volumes, each volume resampled once
+//   k_struct_multi, k_struct_multi1, k_multi_mx  the structural partials of
+//             every volume pair of n = 3 or 4 volumes, each volume resampled
+//             once (16-bit, float32, many A-scans of 16-bit)
 //   k_combine per output A-scan: en face residual (Eq. 7), resampled
 //             validity (Eq. 5), weight delta (Eq. 8), combination with eta
 //             (Eq. 9), scan-order regulariser, mean term, gradient; float64
@@ -733,6 +734,7 @@ __global__ __launch_bounds__(256) void k_struct2(const StructJobs jobs)
 // residual, loss of Eq. 4, its adjoint) runs on the vector units in that
 // layout, the neighbouring depths coming from the next lane of the row (DPP).
 constexpr int kMxSlots = 48;
+constexpr int kMxRest = 2;  // volumes of a tile that may have more than 32 slots
 constexpr int kMxLimit = 1 << 28;  // positions beyond this lie outside every volume
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -846,15 +848,14 @@ struct MxOps<f16_t> {
     }
 };
 
-// Per-wave LDS of k_struct_mx.
-template <typename T, int L>
+// Per-wave LDS of the kernels below, for N volumes.
+template <int N, int L>
 struct MxLds {
-    struct Scan {
-        i32x4 a[3][64];   // weights of slots 0 .. 31, per part
-        i32x2 a1[3][64];  // weights of slots 32 .. 47
-    } w[2];
+    i32x4 a[N][3][64];         // weights of a volume's slots 0 .. 31, per part
+    i32x2 rest[kMxRest][3][64];  // of slots 32 .. 47, for the volumes that have them
     float edge[L][64];
-    int2 key[2][64];
+    int2 key[N][64];  // per slot: byte offset of the column, first source depth of the window
+    i32x4 off[N][4][2];  // [kg][q]: slot 4 q + kg, the column's byte offset at the tile's first window start, zlo
 };
 
 // The lanes of a wave exchange data through their own part of the LDS, whose
@@ -885,27 +886,29 @@ __device__ __forceinline__ float row_sum_last(float x)
 
 // Per-scan state of one wave's tile.
 struct MxScan {
-    uint32_t off[8];     // byte offset of this lane's samples in the columns of slots 4 q + kg at depth zlo
     float wz[4], dwz[4]; // depth taps of this lane's A-scan and their derivatives
     int zb;              // source depth of window position 0 of this lane's A-scan at step 0
     int sh;              // position of the first depth tap
     int any;             // sh of the tile's A-scans, or-ed (wave-uniform)
     int zlo, zhi;        // smallest and largest zb of the tile (wave-uniform)
     int ns;              // slots (wave-uniform)
+    int rest;            // index of the weights of slots 32 .. 47 (wave-uniform)
 };
 
 // The slots, weights and depth taps of one scan.  Lane 16 g + n stands for tap
 // n of A-scan ag (at pg) of group g.  disp: the scan's field [na][3]; lead:
 // position of the A-scan's output 0 (the window is laid out as if its first tap
 // lay that much earlier); groups: bit mask of the groups whose stencils are
+// laid out; nrest: the tile's volumes with more than 32 slots so far.  False:
+// the tile needs more slots than there is room for, and fewer groups are to be
 // laid out.
-template <typename T, int L>
-__device__ __forceinline__ void mx_setup(MxScan& S, MxLds<T, L>& M, int V, const float* disp, int ag, int2 pg, int lead,
-                                         int w, int h, int dp, int lane, int groups)
+template <typename T, int N, int L>
+__device__ __forceinline__ bool mx_setup(MxScan& S, MxLds<N, L>& M, int V, const float* disp, int ag, int2 pg, int lead,
+                                         int w, int h, int dp, int lane, int groups, int& nrest)
 {
     typedef MxGeo<L> Geo;
     typedef MxOps<T> Ops;
-    const int g = lane >> 4, n = lane & 15, kg = g;
+    const int g = lane >> 4, n = lane & 15;
     int nx, ny, nz;
     float tx, ty, tz;
     split(pg.x, disp[(size_t)ag * 3], nx, tx);
@@ -961,24 +964,29 @@ __device__ __forceinline__ void mx_setup(MxScan& S, MxLds<T, L>& M, int V, const
     const bool mine = active & (owner == lane);
     const unsigned long long mask = __ballot(mine);
     S.ns = uni((int)__popcll(mask));
-    if (S.ns > kMxSlots) return;  // the caller takes fewer groups
+    S.rest = nrest;
+    if (S.ns > 32) ++nrest;
+    if (S.ns > kMxSlots || nrest > kMxRest) return false;
     const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
     const int slot = __builtin_amdgcn_ds_bpermute(4 * owner, rank);
     // weights: 0 but for the rows of an A-scan in the slots of its columns.
     // Unused slots: an offset beyond the volume, whose loads return 0.
-    typename MxLds<T, L>::Scan& W = M.w[V];
     const i32x4 zero = {0, 0, 0, 0};
 #pragma unroll
-    for (int k = 0; k < 3; ++k) W.a[k][lane] = zero;
+    for (int k = 0; k < 3; ++k) M.a[V][k][lane] = zero;
     if (S.ns > 32) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) W.a1[k][lane] = i32x2{0, 0};
+        for (int k = 0; k < 3; ++k) M.rest[S.rest][k][lane] = i32x2{0, 0};
     }
     M.key[V][lane] = make_int2((int)0x80000000u, (int)0x80000000u);
+    int* const off = reinterpret_cast<int*>(&M.off[V][0][0]);
+    if (lane < 32) off[lane] = (int)0x80000000u;
     mx_lds_fence();
     if (mine) {
         const int col = min(max(cy, 0), h - 1) * w + min(max(cx, 0), w - 1);
-        M.key[V][slot] = make_int2((int)((uint32_t)col * (uint32_t)dp * 2u), S.zb);
+        const int x = (int)((uint32_t)col * (uint32_t)dp * 2u);
+        M.key[V][slot] = make_int2(x, S.zb);
+        if (slot < 32) off[(slot & 3) * 8 + (slot >> 2)] = x + 2 * (S.zb - S.zlo);
     }
     {
         float wx[4], dwx[4], wy[4], dwy[4];
@@ -995,8 +1003,8 @@ __device__ __forceinline__ void mx_setup(MxScan& S, MxLds<T, L>& M, int V, const
         }
         const float wt[3] = {vx * vy, gx * vy, vx * gy};
         const int q = (slot & 31) >> 2, row = 16 * (slot & 3) + 4 * g;
-        unsigned short* a0 = reinterpret_cast<unsigned short*>(&W.a[0][0]) + row * 8 + q;
-        unsigned short* a1 = reinterpret_cast<unsigned short*>(&W.a1[0][0]) + row * 4 + q;
+        unsigned short* a0 = reinterpret_cast<unsigned short*>(&M.a[V][0][0]) + row * 8 + q;
+        unsigned short* a1 = reinterpret_cast<unsigned short*>(&M.rest[S.rest][0][0]) + row * 4 + q;
         unsigned short p[3][3];
 #pragma unroll
         for (int o = 0; o < 3; ++o) Ops::split_weight(wt[o], p[o]);
@@ -1014,11 +1022,7 @@ __device__ __forceinline__ void mx_setup(MxScan& S, MxLds<T, L>& M, int V, const
         }
     }
     mx_lds_fence();
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int2 k = M.key[V][4 * q + kg];
-        S.off[q] = (uint32_t)k.x + (uint32_t)((max(k.y, S.zlo) - S.zlo + L * n) * 2);
-    }
+    return true;
 }
 
 // wave-uniform: no window of the tile reaches over an end of the A-scans
@@ -1029,41 +1033,36 @@ __device__ __forceinline__ bool mx_inside(const MxScan& S, int step, int dp)
 }
 
 // The samples of one depth step of one scan: kL depths of slots 4 q + kg.
-template <typename T, int L>
+template <int N, int L>
 __device__ __forceinline__ void mx_load(typename MxDwords<L / 2>::type (&s)[8], const MxScan& S,
-                                        const MxLds<T, L>& M, int V, __amdgpu_buffer_rsrc_t r, int step, int dp, int lane)
+                                        const MxLds<N, L>& M, int V, __amdgpu_buffer_rsrc_t r, int step, int dp, int lane)
 {
     typedef MxGeo<L> Geo;
     const int n = lane & 15, kg = lane >> 4, z0 = Geo::kOut * step;
-    const bool inside = mx_inside<Geo>(S, step, dp);
-    const uint32_t soff = (uint32_t)uni(inside ? (S.zlo + z0) * 2 : 0);
     uint32_t off[8];
+    const i32x4 t0 = M.off[V][kg][0], t1 = M.off[V][kg][1];
+    const uint32_t lo = 2u * (uint32_t)min(max(S.zlo + z0 + L * n, 0), dp - L);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) off[q] = S.off[q];
-    if (!inside) {
-        if (S.zlo == S.zhi) {  // one window start: the clamped depth replaces the lane's own
-            const int m = min(max(S.zlo + z0 + L * n, 0), dp - L);
-            const uint32_t delta = (uint32_t)((m - L * n) * 2);
+    for (int q = 0; q < 4; ++q) {
+        off[q] = (uint32_t)t0[q] + lo;
+        off[4 + q] = (uint32_t)t1[q] + lo;
+    }
+    if (S.zlo != S.zhi && !mx_inside<Geo>(S, step, dp)) {  // windows that start apart are clamped one by one
 #pragma unroll
-            for (int q = 0; q < 8; ++q) off[q] += delta;
-        } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int2 k = M.key[V][4 * q + kg];
-                const int m = min(max(k.y + z0 + L * n, 0), dp - L);
-                off[q] = (uint32_t)k.x + (uint32_t)(m * 2);
-            }
+        for (int q = 0; q < 8; ++q) {
+            const int2 k = M.key[V][4 * q + kg];
+            off[q] = (uint32_t)k.x + 2u * (uint32_t)min(max(k.y + z0 + L * n, 0), dp - L);
         }
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) s[q] = MxDwords<L / 2>::load(r, off[q], soff);
+    for (int q = 0; q < 8; ++q) s[q] = MxDwords<L / 2>::load(r, off[q], 0);
 }
 
 // D = the blends of slots 0 .. 31 of scan V, whose samples are s
-template <typename T, int L, typename S>
-__device__ __forceinline__ void mx_blend(f32x4 (&D)[L], const S (&s)[8], const MxLds<T, L>& M, int V, int lane)
+template <typename T, int N, int L, typename S>
+__device__ __forceinline__ void mx_blend(f32x4 (&D)[L], const S (&s)[8], const MxLds<N, L>& M, int V, int lane)
 {
-    const i32x4 a0 = M.w[V].a[0][lane], a1 = M.w[V].a[1][lane], a2 = M.w[V].a[2][lane];
+    const i32x4 a0 = M.a[V][0][lane], a1 = M.a[V][1][lane], a2 = M.a[V][2][lane];
 #pragma unroll
     for (int p = 0; p < L / 2; ++p) {
         i32x4 b0, b1;
@@ -1078,9 +1077,9 @@ __device__ __forceinline__ void mx_blend(f32x4 (&D)[L], const S (&s)[8], const M
 }
 
 // D += the blends of slots 32 .. 47 (only where a tile has them)
-template <typename T, int L>
-__device__ __forceinline__ void mx_rest(f32x4 (&D)[L], const MxLds<T, L>& M, int V, __amdgpu_buffer_rsrc_t r, int step,
-                                        int dp, int lane)
+template <typename T, int N, int L>
+__device__ __forceinline__ void mx_rest(f32x4 (&D)[L], const MxScan& S, const MxLds<N, L>& M, int V,
+                                        __amdgpu_buffer_rsrc_t r, int step, int dp, int lane)
 {
     typedef MxGeo<L> Geo;
     const int n = lane & 15, kg = lane >> 4, z0 = Geo::kOut * step;
@@ -1091,7 +1090,7 @@ __device__ __forceinline__ void mx_rest(f32x4 (&D)[L], const MxLds<T, L>& M, int
         const int m = min(max(k.y + z0 + L * n, 0), dp - L);
         s[q] = MxDwords<L / 2>::load(r, (uint32_t)k.x + (uint32_t)(m * 2), 0);
     }
-    const i32x2 a0 = M.w[V].a1[0][lane], a1 = M.w[V].a1[1][lane], a2 = M.w[V].a1[2][lane];
+    const i32x2 a0 = M.rest[S.rest][0][lane], a1 = M.rest[S.rest][1][lane], a2 = M.rest[S.rest][2][lane];
 #pragma unroll
     for (int p = 0; p < L / 2; ++p) {
         i32x2 b0, b1;
@@ -1132,9 +1131,9 @@ __device__ __forceinline__ void mx_move(float (&v)[L], bool on)
 
 // The lateral blends (value, x and y derivative) of this lane's A-scan at its L
 // positions: the edge values beyond the A-scan, then (MOVE) the window's shift.
-template <typename T, int L, bool MOVE>
+template <int N, int L, bool MOVE>
 __device__ __forceinline__ void mx_rows(float (&v)[L], float (&vx)[L], float (&vy)[L], const f32x4 (&D)[L],
-                                        const MxScan& S, MxLds<T, L>& M, int step, int dp, int lane)
+                                        const MxScan& S, MxLds<N, L>& M, int step, int dp, int lane)
 {
     typedef MxGeo<L> Geo;
 #pragma unroll
@@ -1172,6 +1171,13 @@ __device__ __forceinline__ float mx_fir(const float (&w)[4], const float (&x)[N]
 #pragma unroll
     for (int c = 1; c < 4; ++c) s = fmaf(w[c], x[i + c], s);
     return s;
+}
+
+// The groups to evaluate after `groups` (0: done).  bad: a sum was not finite.
+__device__ __forceinline__ int mx_next(int groups, bool bad)
+{
+    if (groups & (groups - 1)) return bad ? 1 : (groups == 3 ? 12 : 0);  // several groups
+    return groups == 8 ? 0 : groups << 1;
 }
 
 // The seven sums of an A-scan, one part of them per lane of its row.
@@ -1251,16 +1257,16 @@ __device__ __forceinline__ void mx_depth(MxSums& A, const float (&x)[L + 3], con
 // per XCD when the job fills the grid), swept column by column, so that the
 // rows a block reads are still in that XCD's L2 when the next column reads
 // them.  False: a whole block beyond the job's, or a wave outside the scan.
-__device__ __forceinline__ bool mx_tile(const StructJob& J, int t, int wv, int& i0, int& j0)
+__device__ __forceinline__ bool mx_tile(int w, int h, int t, int wv, int& i0, int& j0)
 {
-    const int bpr = (J.w + 3) >> 2;
-    const int brows = (J.h + 3) >> 2;
+    const int bpr = (w + 3) >> 2;
+    const int brows = (h + 3) >> 2;
     const int rpb = (brows + 7) >> 3;
     const int band = t / (rpb * bpr), tb = t - band * (rpb * bpr);
     const int brow = band * rpb + tb % rpb;
     i0 = 4 * (tb / rpb) + 2 * (wv & 1);
     j0 = 4 * brow + 2 * (wv >> 1);
-    return t < 8 * rpb * bpr && brow < brows && i0 < J.w && j0 < J.h;
+    return t < 8 * rpb * bpr && brow < brows && i0 < w && j0 < h;
 }
 
 // Bound by vector issue: a step of eight depths per lane takes some 440 vector
@@ -1268,18 +1274,19 @@ __device__ __forceinline__ bool mx_tile(const StructJob& J, int t, int wv, int& 
 // depth work is 46 per sample pair and the operand packing 8.  Three waves per
 // SIMD: 168 registers; two waves with the next step's samples loaded ahead
 // measured 25 % slower, and so did one workgroup barrier per step to share L1
-// lines.  The lateral blends and their adjoint took k_struct2 128 FMAs and 64
+// lines; the column offsets are read from the LDS at each step, which saves
+// 16 registers and with them the spills.  The lateral blends and their adjoint took k_struct2 128 FMAs and 64
 // conversions per 122 outputs of one A-scan, and its 64 loads of 256 bytes per
-// step of a tile are 16 of 1 KB here.  500 x 500 x 800 in BF16: 1.058 -> 0.578
-// ms (66 TFLOP/s of the method's operations), 500 x 500 x 465 in FP16: 0.645 ->
-// 0.386, 300 x 300 x 233 in BF16 0.160 -> 0.098 ms.
+// step of a tile are 16 of 1 KB here.  500 x 500 x 800 in BF16: 1.058 -> 0.563
+// ms (68 TFLOP/s of the method's operations), 500 x 500 x 465 in FP16: 0.645 ->
+// 0.367, 300 x 300 x 233 in BF16 0.160 -> 0.092 ms.
 template <typename T, int L>
 __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
 {
     if (jobs.skip && *jobs.skip) return;
-    __shared__ MxLds<T, L> lds[4];
+    __shared__ MxLds<2, L> lds[4];
     const int wv = uni((int)(threadIdx.x >> 6));
-    MxLds<T, L>& M = lds[wv];
+    MxLds<2, L>& M = lds[wv];
     const int lb = xcd_block(blockIdx.x, gridDim.x);
     int jid = -1;
     for (int q = 0; q < jobs.n; ++q)
@@ -1288,7 +1295,7 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
     const StructJob& J = jobs.j[jid];
     const int w = J.w, h = J.h, d = J.d, dp = J.dp;
     int i0, j0;
-    if (!mx_tile(J, lb - J.blk_begin, wv, i0, j0)) return;
+    if (!mx_tile(w, h, lb - J.blk_begin, wv, i0, j0)) return;
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.sx), (short)0, (int)J.vol_bytes, kRsrcWord3);
     const __amdgpu_buffer_rsrc_t ry =
@@ -1317,10 +1324,10 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
         static_assert(Geo::kOut % L == 0 || Geo::kOut % L == 2, "two classes of positions");
         const float ie_lo = p0 < Geo::kOut ? inv_eps : 0.f, ie_hi = p0 + 2 < Geo::kOut ? inv_eps : 0.f;
         MxScan SX, SY;
-        mx_setup<T, L>(SX, M, 0, J.disp, ag, pg, 0, w, h, dp, lane, groups);
-        mx_setup<T, L>(SY, M, 1, J.disp + (size_t)J.na * 3, ag, pg, SX.sh, w, h, dp, lane, groups);
-        if (max(SX.ns, SY.ns) > kMxSlots) {  // only four groups can
-            groups = 3;
+        int nrest = 0;
+        if (!mx_setup<T>(SX, M, 0, J.disp, ag, pg, 0, w, h, dp, lane, groups, nrest) ||
+            !mx_setup<T>(SY, M, 1, J.disp + (size_t)J.na * 3, ag, pg, SX.sh, w, h, dp, lane, groups, nrest)) {
+            groups = 3;  // two groups never need more than 32 slots
             continue;
         }
         MxSums A;
@@ -1329,19 +1336,19 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
             float x[L + 3], xx[L], xy[L], y[L + 3], yx[L], yy[L];
             {
                 typename MxDwords<L / 2>::type qx[8], qy[8];
-                mx_load<T, L>(qx, SX, M, 0, rx, s, dp, lane);
-                mx_load<T, L>(qy, SY, M, 1, ry, s, dp, lane);
+                mx_load(qx, SX, M, 0, rx, s, dp, lane);
+                mx_load(qy, SY, M, 1, ry, s, dp, lane);
                 float v[L];
                 f32x4 D[L] = {};
-                mx_blend<T, L>(D, qx, M, 0, lane);
-                if (SX.ns > 32) mx_rest<T, L>(D, M, 0, rx, s, dp, lane);
-                mx_rows<T, L, false>(v, xx, xy, D, SX, M, s, dp, lane);
+                mx_blend<T>(D, qx, M, 0, lane);
+                if (SX.ns > 32) mx_rest<T>(D, SX, M, 0, rx, s, dp, lane);
+                mx_rows<2, L, false>(v, xx, xy, D, SX, M, s, dp, lane);
 #pragma unroll
                 for (int i = 0; i < L; ++i) x[i] = v[i];
                 f32x4 E[L] = {};
-                mx_blend<T, L>(E, qy, M, 1, lane);
-                if (SY.ns > 32) mx_rest<T, L>(E, M, 1, ry, s, dp, lane);
-                mx_rows<T, L, true>(v, yx, yy, E, SY, M, s, dp, lane);
+                mx_blend<T>(E, qy, M, 1, lane);
+                if (SY.ns > 32) mx_rest<T>(E, SY, M, 1, ry, s, dp, lane);
+                mx_rows<2, L, true>(v, yx, yy, E, SY, M, s, dp, lane);
 #pragma unroll
                 for (int i = 0; i < L; ++i) y[i] = v[i];
             }
@@ -1358,14 +1365,8 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
         const bool active = groups >> g & 1;
         if (last && inscan && active) A.store(J.part + (size_t)ag * 8);
         const bool bad = __ballot(last && active && !A.finite()) != 0;
-        if (groups & (groups - 1)) {  // several groups
-            if (bad) groups = 1;
-            else if (groups == 3) groups = 12;
-            else return;
-        } else {
-            if (groups == 8) return;
-            groups <<= 1;
-        }
+        groups = mx_next(groups, bad);
+        if (!groups) return;
     }
 }
 
@@ -1906,6 +1907,159 @@ __global__ __launch_bounds__(256) void k_struct_multi(const StructMultiJob<N> J)
     }
 }
 
+// k_multi_mx: k_struct_multi on the matrix cores (16-bit storage), with the
+// tiles, set-up and layout of k_struct_mx.  Every volume's blends are moved to
+// the positions of the first volume's; a lane then holds the value and the x, y,
+// z derivatives of all N volumes at four depths (four rather than eight, since
+// 16 N registers hold them), and the pairs are formed from those.
+// Bound by vector issue: with N = 4 a step takes some 900 vector instructions
+// for 58 outputs of four A-scans, where k_struct_multi takes 996 for 122 of one.
+// Two waves per SIMD (256 registers); the depth taps and the column offsets are
+// read from the LDS at each step, which leaves registers to load one volume
+// ahead.  Four volumes of 300 x 300 x 640 in BF16: 1230 -> 850 us per
+// evaluation (1013 without loading ahead, 880 with the offsets in registers).
+template <typename T, int N>
+__global__ __launch_bounds__(256, 2) void k_multi_mx(const StructMultiJob<N> J)
+{
+    if (J.skip && *J.skip) return;
+    constexpr int NP = N * (N - 1) / 2, L = 4;
+    typedef MxGeo<L> Geo;
+    __shared__ MxLds<N, L> lds[4];
+    __shared__ f32x4 taps[4][N][4][2];  // per wave, volume and A-scan: the depth taps and their derivatives
+    const int wv = uni((int)(threadIdx.x >> 6));
+    MxLds<N, L>& M = lds[wv];
+    const int w = J.w, h = J.h, d = J.d, dp = J.dp;
+    int i0, j0;
+    if (!mx_tile(w, h, xcd_block(blockIdx.x, gridDim.x), wv, i0, j0)) return;
+    __amdgpu_buffer_rsrc_t rs[N];
+#pragma unroll
+    for (int V = 0; V < N; ++V)
+        rs[V] = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.vol[V]), (short)0, (int)J.vol_bytes, kRsrcWord3);
+    const float inv_eps = 1.0f / J.eps_h;
+    int groups = 15;  // as k_struct_mx
+    for (;;) {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int g = lane >> 4;
+        const bool last = (lane & 15) == 15;
+        const int p0 = L * (lane & 15);
+        const int2 pg = make_int2(min(i0 + (g & 1), w - 1), min(j0 + (g >> 1), h - 1));
+        const bool inscan = i0 + (g & 1) < w && j0 + (g >> 1) < h;
+        const int ag = pg.y * w + pg.x;
+        const float ie_lo = p0 < Geo::kOut ? inv_eps : 0.f, ie_hi = p0 + 2 < Geo::kOut ? inv_eps : 0.f;
+        MxScan S[N];
+        int nrest = 0;
+        bool fits = true;
+#pragma unroll
+        for (int V = 0; V < N; ++V) {
+            fits = fits && mx_setup<T>(S[V], M, V, J.disp + (size_t)V * J.na * 3, ag, pg, V ? S[0].sh : 0, w, h, dp, lane,
+                                       groups, nrest);
+            if ((lane & 15) == 0) {
+                taps[wv][V][g][0] = f32x4{S[V].wz[0], S[V].wz[1], S[V].wz[2], S[V].wz[3]};
+                taps[wv][V][g][1] = f32x4{S[V].dwz[0], S[V].dwz[1], S[V].dwz[2], S[V].dwz[3]};
+            }
+        }
+        mx_lds_fence();
+        if (!fits) {
+            groups = 3;
+            continue;
+        }
+        float acc[NP][7];
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+#pragma unroll
+            for (int c = 0; c < 7; ++c) acc[q][c] = 0.f;
+        const int nsteps = (d + S[0].any + Geo::kOut - 1) / Geo::kOut;
+        typename MxDwords<L / 2>::type next[8];
+        mx_load(next, S[0], M, 0, rs[0], 0, dp, lane);
+        for (int s = 0; s < nsteps; ++s) {
+            float I[N][L], X[N][L], Y[N][L], Z[N][L];
+#pragma unroll
+            for (int V = 0; V < N; ++V) {
+                // the next volume's samples are loaded while this one is blended
+                typename MxDwords<L / 2>::type q[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) q[k] = next[k];
+                if (V + 1 < N) mx_load(next, S[V + 1], M, V + 1, rs[V + 1], s, dp, lane);
+                else if (s + 1 < nsteps) mx_load(next, S[0], M, 0, rs[0], s + 1, dp, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                f32x4 D[L] = {};
+                mx_blend<T>(D, q, M, V, lane);
+                if (S[V].ns > 32) mx_rest<T>(D, S[V], M, V, rs[V], s, dp, lane);
+                float v[L], vx[L], vy[L];
+                if (V == 0) mx_rows<N, L, false>(v, vx, vy, D, S[V], M, s, dp, lane);
+                else mx_rows<N, L, true>(v, vx, vy, D, S[V], M, s, dp, lane);
+                float e[L + 3], ex[L + 3], ey[L + 3];
+#pragma unroll
+                for (int i = 0; i < L; ++i) {
+                    e[i] = v[i];
+                    ex[i] = vx[i];
+                    ey[i] = vy[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    e[L + i] = row_next(v[i]);
+                    ex[L + i] = row_next(vx[i]);
+                    ey[L + i] = row_next(vy[i]);
+                }
+                const f32x4 t0 = taps[wv][V][g][0], t1 = taps[wv][V][g][1];
+                const float wz[4] = {t0[0], t0[1], t0[2], t0[3]}, dwz[4] = {t1[0], t1[1], t1[2], t1[3]};
+#pragma unroll
+                for (int i = 0; i < L; ++i) {
+                    I[V][i] = mx_fir(wz, e, i);
+                    Z[V][i] = mx_fir(dwz, e, i);
+                    X[V][i] = mx_fir(wz, ex, i);
+                    Y[V][i] = mx_fir(wz, ey, i);
+                }
+                __builtin_amdgcn_sched_barrier(0);  // no volume's loads earlier than that: registers
+            }
+            const int o0 = Geo::kOut * s + p0 - S[0].sh;
+            float ie[L];
+#pragma unroll
+            for (int i = 0; i < L; ++i) ie[i] = i < 2 ? ie_lo : ie_hi;
+            if (s == 0 || Geo::kOut * (s + 1) > d) {
+#pragma unroll
+                for (int i = 0; i < L; ++i) ie[i] = (unsigned)(o0 + i) < (unsigned)d ? ie[i] : 0.f;
+            }
+            int q = 0;
+#pragma unroll
+            for (int P = 0; P < N; ++P)
+#pragma unroll
+                for (int Q = P + 1; Q < N; ++Q, ++q)
+#pragma unroll
+                    for (int i = 0; i < L; ++i) {
+                        const float u = (I[P][i] - I[Q][i]) * ie[i], uu = u * u;
+                        const float rsq = __builtin_amdgcn_rsqf(1.f + uu), sq = (1.f + uu) * rsq;
+                        const float G = u * rsq;
+                        acc[q][0] = fmaf(uu, __builtin_amdgcn_rcpf(sq + 1.f), acc[q][0]);
+                        acc[q][1] = fmaf(G, X[P][i], acc[q][1]);
+                        acc[q][2] = fmaf(G, Y[P][i], acc[q][2]);
+                        acc[q][3] = fmaf(G, Z[P][i], acc[q][3]);
+                        acc[q][4] = fmaf(G, X[Q][i], acc[q][4]);
+                        acc[q][5] = fmaf(G, Y[Q][i], acc[q][5]);
+                        acc[q][6] = fmaf(G, Z[Q][i], acc[q][6]);
+                    }
+        }
+        const bool active = groups >> g & 1;
+        bool finite = true;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            float v[7];
+#pragma unroll
+            for (int c = 0; c < 7; ++c) v[c] = row_sum_last(acc[q][c]);
+            v[0] *= J.eps_h;
+            finite = finite && __builtin_isfinite(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + v[6]));
+            if (last && inscan && active) {
+                float4* o = reinterpret_cast<float4*>(J.part[q] + (size_t)ag * 8);
+                o[0] = make_float4(v[0], v[1], v[2], v[3]);
+                o[1] = make_float4(v[4], v[5], v[6], 0.f);
+            }
+        }
+        groups = mx_next(groups, __ballot(last && active && !finite) != 0);
+        if (!groups) return;
+    }
+}
+
 // The same pass for float32 storage (any depth): one sample per lane, lane l
 // holding source sample base_V + 61 n + l of volume V, as in k_struct; the
 // depth interpolation of output lane l (< 61) reads source lanes l .. l + 3,
@@ -2093,6 +2247,11 @@ hipError_t launch_combine(const CombineJobs& jobs, int total_blocks, hipStream_t
     return hipGetLastError();
 }
 
+// k_multi_mx with fewer A-scans than this leaves the device's registers and LDS
+// (two workgroups per CU) without tiles: four volumes of 96 x 96 x 200 in BF16
+// 99 against k_struct_multi's 87 us per evaluation, 128 x 128 x 256 141 against
+// 153.
+constexpr int kMxMultiMinAscans = 16384;
 template <int N>
 static hipError_t launch_struct_multi_n(const void* const* vol, const float* disp, float* const* part, int w, int h,
                                         int d, int dp, uint32_t vol_bytes, float eps_h, octmc_dtype dt,
@@ -2111,8 +2270,13 @@ static hipError_t launch_struct_multi_n(const void* const* vol, const float* dis
     J.vol_bytes = vol_bytes;
     J.eps_h = eps_h;
     const int blocks = (struct_blocks(w, h) + 7) / 8 * 8;  // a multiple of the 8 XCDs
+    const int mx = struct_mx_blocks(w, h);
     if (dt == OCTMC_F32)
         hipLaunchKernelGGL((k_struct_multi1<N>), dim3(blocks), dim3(256), 0, s, J);
+    else if (J.na >= kMxMultiMinAscans && dt == OCTMC_BF16)
+        hipLaunchKernelGGL((k_multi_mx<bf16_t, N>), dim3(mx), dim3(256), 0, s, J);
+    else if (J.na >= kMxMultiMinAscans)
+        hipLaunchKernelGGL((k_multi_mx<f16_t, N>), dim3(mx), dim3(256), 0, s, J);
     else if (dt == OCTMC_BF16)
         hipLaunchKernelGGL((k_struct_multi<bf16_t, N>), dim3(blocks), dim3(256), 0, s, J);
     else

@@ -1,5 +1,5 @@
-"""The matrix-core structural kernel (16-bit volumes of at least 8192 A-scans)
-against the FP64 oracle, at the sizes and fields where its tiling can go wrong:
+"""The matrix-core structural kernels (16-bit volumes of at least 8192 A-scans; a
+pair, and three or four volumes) against the FP64 oracle, at the sizes and fields where its tiling can go wrong:
 scans that are no multiple of its 4 x 4 blocks and 2 x 2 tiles, depths around
 its windows of 16 x 4 and 16 x 8 samples (58 and 122 outputs a step, the
 smallest depths), tiles whose A-scans share all, some or none of their source
@@ -24,23 +24,23 @@ def octmc():
     return m
 
 
-def _inputs(n, d, dtype, seed):
+def _inputs(n, d, dtype, seed, count=2):
     """Speckled layers, en face images and validity with one invalid B-scan each."""
     rng = np.random.default_rng(seed)
     z = np.arange(d)[None, None, :]
     edge = 0.4 * d + 2 * np.sin(np.arange(n) / 7.0)[:, None, None] + 2 * np.cos(np.arange(n) / 5.0)[None, :, None]
-    vol = [(0.1 + 0.8 / (1 + np.exp(-(z - edge) / 2.0))) * np.exp(0.4 * rng.normal(size=(n, n, d))) for _ in range(2)]
+    vol = [(0.1 + 0.8 / (1 + np.exp(-(z - edge) / 2.0))) * np.exp(0.4 * rng.normal(size=(n, n, d))) for _ in range(count)]
     S = [round_storage(torch.from_numpy(v.astype(np.float32)), dtype) for v in vol]
-    A = [torch.from_numpy(rng.uniform(0, 1, (n, n)).astype(np.float32)) for _ in range(2)]
-    V = [torch.ones(n) for _ in range(2)]
-    V[0][n // 3] = 0.0
-    V[1][n // 2] = 0.0
+    A = [torch.from_numpy(rng.uniform(0, 1, (n, n)).astype(np.float32)) for _ in range(count)]
+    V = [torch.ones(n) for _ in range(count)]
+    for q in range(count):
+        V[q][n // (3 - q % 2)] = 0.0
     return S, A, V
 
 
-def _field(case, n, seed):
+def _field(case, n, seed, count=2):
     rng = np.random.default_rng(seed + 100)
-    D = np.zeros((2, n, n, 3))
+    D = np.zeros((count, n, n, 3))
     if case == "shift":      # whole samples: every fraction 0, odd and even depth offsets
         D[0] += (1.0, -2.0, 3.0)
         D[1] += (-1.0, 0.0, -2.0)
@@ -107,3 +107,29 @@ def test_not_finite_stays_local(octmc, value):
             hit |= (np.clip(jj + f[..., 1] - 1 + b, 0, n - 1) == r) & (np.clip(ii + f[..., 0] - 1 + a, 0, n - 1) == c)
     bad = ~np.isfinite(g).all(axis=(0, 3))
     assert hit.sum() > 4 and (bad == hit).all()
+
+
+@pytest.mark.parametrize("n,d,dtype,count,case", [
+    (91, 58, "bf16", 3, "noise"), (92, 59, "f16", 4, "depth"), (93, 117, "bf16", 4, "apart"), (91, 4, "f16", 3, "depth"),
+    (94, 130, "bf16", 4, "noise"),
+])
+def test_parity_multi(octmc, n, d, dtype, count, case):
+    log(f"matrix-core structural kernel of {count} volumes n={n} d={d} {dtype} {case}")
+    S, A, V = _inputs(n, d, dtype, n + d, count)
+    D = _field(case, n, n + d, count)
+    orient = [0, 1, 0, 1][:count]
+    M = octmc.Multi(S, orient, enface=A, valid=V, dtype=dtype, levels=1, delta0=0.0)
+    terms, g = M.eval(0, D.cuda(), eta_mode=0)
+    t = octmc.terms_dict(terms)
+    g = g.double().cpu().numpy()
+    M.close()
+    prm = oracle.Params(levels=1, delta0=0.0)
+    om = oracle.Multi([s.double().numpy() for s in S], orient, [a.double().numpy() for a in A],
+                      [v.double().numpy() for v in V])
+    D64 = D.double().numpy()
+    _, p05, _ = oracle.evaluate_multi(om, D64, prm, None, grad=False)
+    eta = np.sqrt(p05[:, 1] / p05[:, 0])
+    ref, _, gref = oracle.evaluate_multi(om, D64, prm, eta)
+    for k in ("F", "data", "str", "str05"):
+        assert rel(t[k], ref[k]) < TOL, (k, t[k], ref[k])
+    assert grad_err(g, gref) < TOL
