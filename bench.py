@@ -60,15 +60,15 @@ def warm_clock(torch, step, seconds=None):
 
 
 def source_sha():
-    """Hash of the structural kernels' source (the part of kernels_eval.hip
-    before the reduction helpers: stencils, k_struct, k_struct2), so that
-    counter figures go stale only when those kernels change."""
-    p = os.path.join(ROOT, "paper_2010_06931_amd", "csrc", "kernels_eval.hip")
-    text = open(p, "rb").read()
+    """Hash of the structural kernels' source (tile_blend.h and the part of
+    kernels_eval.hip before the reduction helpers), so that counter figures go
+    stale only when those kernels change."""
+    csrc = os.path.join(ROOT, "paper_2010_06931_amd", "csrc")
+    text = open(os.path.join(csrc, "kernels_eval.hip"), "rb").read()
     cut = text.find(b"// deterministic block reduction helpers")
     if cut < 0:
         raise RuntimeError("kernels_eval.hip: reduction helpers marker not found")
-    return hashlib.sha256(text[:cut]).hexdigest()[:16]
+    return hashlib.sha256(open(os.path.join(csrc, "tile_blend.h"), "rb").read() + text[:cut]).hexdigest()[:16]
 
 
 def load_traffic(dtype):

@@ -24,43 +24,11 @@
 #include <hip/hip_runtime.h>
 
 #include "octmc_internal.h"
+#include "tile_blend.h"
 
 namespace octmc {
 
 namespace {
-
-__device__ __forceinline__ float uni(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
-}
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Cubic Hermite spline with central-difference tangents (Catmull-Rom), the
-// C1 "Hermitian" interpolator of Eq. 2: weights of the samples at n-1 .. n+2
-// for the fraction t in [0, 1), and their derivatives.
-__device__ __forceinline__ void cr_taps(float t, float w[4], float dw[4])
-{
-    const float t2 = t * t, t3 = t2 * t;
-    w[0] = 0.5f * (-t3 + 2.f * t2 - t);
-    w[1] = 0.5f * (3.f * t3 - 5.f * t2 + 2.f);
-    w[2] = 0.5f * (-3.f * t3 + 4.f * t2 + t);
-    w[3] = 0.5f * (t3 - t2);
-    dw[0] = 0.5f * (-3.f * t2 + 4.f * t - 1.f);
-    dw[1] = 0.5f * (9.f * t2 - 10.f * t);
-    dw[2] = 0.5f * (-9.f * t2 + 8.f * t + 1.f);
-    dw[3] = 0.5f * (3.f * t2 - 2.f * t);
-}
-
-// Split an integer grid coordinate plus a displacement into the integer base
-// and the fraction without rounding: dv = floor(dv) + frac exactly.
-__device__ __forceinline__ void split(int idx, float dv, int& n, float& t)
-{
-    const float f = floorf(dv);
-    t = dv - f;
-    n = idx + (int)f;
-}
-
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 template <typename T>
 __device__ __forceinline__ float ldv(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff);
@@ -69,8 +37,6 @@ __device__ __forceinline__ float ldv<float>(__amdgpu_buffer_rsrc_t r, uint32_t v
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
-struct bf16_t {};
-struct f16_t {};
 template <>
 __device__ __forceinline__ float ldv<bf16_t>(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
@@ -83,11 +49,6 @@ __device__ __forceinline__ float ldv<f16_t>(__amdgpu_buffer_rsrc_t r, uint32_t v
     const unsigned short b = __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
     return (float)__builtin_bit_cast(_Float16, b);
 }
-template <typename T> struct esize { static constexpr uint32_t v = 2; };
-template <> struct esize<float> { static constexpr uint32_t v = 4; };
-
-constexpr uint32_t kRsrcWord3 = 0x00020000u;
-
 // Stage 1 (rough axial prealignment) evaluates at dx = dy = 0, where the
 // lateral weights are (0, 1, 0, 0) in x and y: the blend of the 16 columns
 // is exactly the centre column (index 5; every other product is an exact 0),
@@ -292,12 +253,6 @@ __device__ __forceinline__ float shr1(float v)
 // row broadcasts (rows 1 and 3 add the last lane of the row before them, then
 // rows 2 and 3 add lane 31): (r3 + r2) + (r1 + r0).  Six DPP additions, no
 // lane reads.
-template <int S>
-__device__ __forceinline__ float row_shr_add(float v)
-{
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x110 | S, 0xF,
-                                                                     0xF, true));
-}
 __device__ __forceinline__ float wave_sum_last(float x)
 {
     float v = row_shr_add<1>(x);
@@ -312,14 +267,6 @@ __device__ __forceinline__ float wave_sum_last(float x)
 __device__ __forceinline__ float wave_sum(float x)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_last(x)), 63));
-}
-
-// Logical block of a physical one: workgroups are dispatched to the 8 XCDs
-// round robin, so give every XCD a contiguous range of tiles (neighbouring
-// A-scans then share that XCD's L2).  The grid is a multiple of 8.
-__device__ __forceinline__ int xcd_block(int b, int nb)
-{
-    return (b & 7) * (nb >> 3) + (b >> 3);
 }
 
 template <typename T, bool AXIAL>
@@ -709,476 +656,11 @@ __global__ __launch_bounds__(256) void k_struct2(const StructJobs jobs)
 // ---------------------------------------------------------------------------
 // k_struct_mx: the structural data term on the matrix cores.
 //
-// One wave evaluates a 2 x 2 tile of output A-scans.  Per scan the distinct
-// source columns of the tile's four 4 x 4 lateral stencils (25 for a smooth
-// field instead of 64) are the inner dimension of a small contraction,
-//   D[4 g + o][k] = sum_slot W[4 g + o][slot] V[slot][k],
-// whose rows are the lateral blends o = value, x derivative, y derivative of
-// A-scan g and whose columns are source depths.  W holds the Catmull-Rom
-// products; a slot outside an A-scan's stencil has weight 0, so any set of
-// displacements is served: 32 slots take one matrix product per depth tile,
-// up to 48 a second one, and a tile with more (disjoint stencils) is evaluated
-// two A-scans at a time.
-// The products are v_mfma_f32_16x16x32 on the stored 16-bit samples.  The
-// float32 weights enter as three 16-bit parts, each the rest rounded to
-// nearest, whose sum is the weight exactly (BF16: three times 8 bits; FP16: 11 +
-// 11 + 2 bits of the weight times 2^12, undone in the depth taps), so the
-// products are those of a float32 blend and no sample is converted.  The
-// leading parts are summed first: an addend smaller than the products it is
-// added to loses bits to truncation, a larger one is rounded to nearest
-// (measured on S_str of 500 x 500 x 800 in BF16, against 64 bits: 1.3e-8 off;
-// leading parts last and split by truncation, -0.8e-8; the vector kernels
-// 1.8e-8, which is the reciprocals' of the loss).
-// Lane 16 g + n then holds the blends of A-scan g at L consecutive source
-// depths of a window, and everything along depth (interpolation of Eq. 2,
-// residual, loss of Eq. 4, its adjoint) runs on the vector units in that
-// layout, the neighbouring depths coming from the next lane of the row (DPP).
-constexpr int kMxSlots = 48;
-constexpr int kMxRest = 2;  // volumes of a tile that may have more than 32 slots
-constexpr int kMxLimit = 1 << 28;  // positions beyond this lie outside every volume
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-// Depth windows: a lane holds L consecutive source depths (one load per
-// column), a row of 16 lanes a window of 16 L.  An A-scan's window starts
-// sh = 0 .. 3 samples before its first depth tap, at an even depth (loads off a
-// 4-byte boundary take up to four times as long); A-scans with a common start
-// share their columns' loads.  Position p of the X-fast scan's window holds the
-// first tap of output kOut step + p - sh; the Y-fast scan's blends are moved to
-// the same positions.
-template <int L>
-struct MxGeo {
-    static constexpr int kWin = 16 * L;
-    static constexpr int kShift = 3;
-    static constexpr int kOut = kWin - 3 - kShift;  // outputs per step (four taps, the move), even
-};
-
-// A lane's samples of one column.
-template <int N>
-struct MxDwords;
-template <>
-struct MxDwords<2> {
-    typedef i32x2 type;
-    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-    {
-        return __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
-    }
-};
-template <>
-struct MxDwords<4> {
-    typedef i32x4 type;
-    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-    {
-        return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
-    }
-};
-
-// Matrix products.  A operands live in the LDS: of slot 4 q + kg (q = 0 .. 7)
-// row m is element q of lane 16 kg + m; slots 32 .. 47 likewise with q = 0 .. 3.
-template <typename T>
-struct MxOps;
-
-// the two samples of dword p of slots 2 t, 2 t + 1 of a lane, as the B operands of their depths
-template <int NQ, typename S, typename B>
-__device__ __forceinline__ void mx_pack(const S (&v)[NQ], int p, B& b0, B& b1)
-{
-#pragma unroll
-    for (int t = 0; t < NQ / 2; ++t) {
-        const unsigned lo = (unsigned)v[2 * t][p], hi = (unsigned)v[2 * t + 1][p];
-        b0[t] = (int)__builtin_amdgcn_perm(hi, lo, 0x05040100u);
-        b1[t] = (int)__builtin_amdgcn_perm(hi, lo, 0x07060302u);
-    }
-}
-
-template <>
-struct MxOps<bf16_t> {
-    static constexpr float kUnscale = 1.f;
-    static __device__ __forceinline__ void split_weight(float w, unsigned short (&p)[3])
-    {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const __bf16 hp = (__bf16)w;
-            p[k] = __builtin_bit_cast(unsigned short, hp);
-            w -= (float)hp;
-        }
-    }
-    static __device__ __forceinline__ f32x4 mfma(i32x4 a, i32x4 b, f32x4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                       0, 0, 0);
-    }
-    static __device__ __forceinline__ f32x4 mfma(i32x2 a, i32x2 b, f32x4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c,
-                                                         0, 0, 0);
-    }
-};
-
-template <>
-struct MxOps<f16_t> {
-    // binary16 has no room below 2^-24 for the trailing bits of a weight: the
-    // weights are scaled by 2^12 (the largest is below 2) and the depth taps
-    // by 2^-12, both exact
-    static constexpr float kUnscale = 1.f / 4096.f;
-    static __device__ __forceinline__ void split_weight(float w, unsigned short (&p)[3])
-    {
-        float r = w * 4096.f;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const _Float16 hp = (_Float16)r;
-            p[k] = __builtin_bit_cast(unsigned short, hp);
-            r -= (float)hp;
-        }
-    }
-    static __device__ __forceinline__ f32x4 mfma(i32x4 a, i32x4 b, f32x4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
-                                                      0, 0);
-    }
-    static __device__ __forceinline__ f32x4 mfma(i32x2 a, i32x2 b, f32x4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0,
-                                                     0, 0);
-    }
-};
-
-// Per-wave LDS of the kernels below, for N volumes.
-template <int N, int L>
-struct MxLds {
-    i32x4 a[N][3][64];         // weights of a volume's slots 0 .. 31, per part
-    i32x2 rest[kMxRest][3][64];  // of slots 32 .. 47, for the volumes that have them
-    float edge[L][64];
-    int2 key[N][64];  // per slot: byte offset of the column, first source depth of the window
-    i32x4 off[N][4][2];  // [kg][q]: slot 4 q + kg, the column's byte offset at the tile's first window start, zlo
-};
-
-// The lanes of a wave exchange data through their own part of the LDS, whose
-// accesses complete in order: only the compiler has to keep that order.
-__device__ __forceinline__ void mx_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Lane shifts within a row of 16 lanes (DPP); the row's end reads 0.
-__device__ __forceinline__ float row_next(float v)  // lane l gets lane l + 1's value
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x101, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float row_prev(float v)  // lane l gets lane l - 1's value
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x111, 0xF, 0xF, true));
-}
-// sum over a row of 16 lanes, left in its last lane
-__device__ __forceinline__ float row_sum_last(float x)
-{
-    float v = row_shr_add<1>(x);
-    v = row_shr_add<2>(v);
-    v = row_shr_add<4>(v);
-    return row_shr_add<8>(v);
-}
-
-// Per-scan state of one wave's tile.
-struct MxScan {
-    float wz[4], dwz[4]; // depth taps of this lane's A-scan and their derivatives
-    int zb;              // source depth of window position 0 of this lane's A-scan at step 0
-    int sh;              // position of the first depth tap
-    int any;             // sh of the tile's A-scans, or-ed (wave-uniform)
-    int zlo, zhi;        // smallest and largest zb of the tile (wave-uniform)
-    int ns;              // slots (wave-uniform)
-    int rest;            // index of the weights of slots 32 .. 47 (wave-uniform)
-};
-
-// The slots, weights and depth taps of one scan.  Lane 16 g + n stands for tap
-// n of A-scan ag (at pg) of group g.  disp: the scan's field [na][3]; lead:
-// position of the A-scan's output 0 (the window is laid out as if its first tap
-// lay that much earlier); groups: bit mask of the groups whose stencils are
-// laid out; nrest: the tile's volumes with more than 32 slots so far.  False:
-// the tile needs more slots than there is room for, and fewer groups are to be
-// laid out.
-template <typename T, int N, int L>
-__device__ __forceinline__ bool mx_setup(MxScan& S, MxLds<N, L>& M, int V, const float* disp, int ag, int2 pg, int lead,
-                                         int w, int h, int dp, int lane, int groups, int& nrest)
-{
-    typedef MxGeo<L> Geo;
-    typedef MxOps<T> Ops;
-    const int g = lane >> 4, n = lane & 15;
-    int nx, ny, nz;
-    float tx, ty, tz;
-    split(pg.x, disp[(size_t)ag * 3], nx, tx);
-    split(pg.y, disp[(size_t)ag * 3 + 1], ny, ty);
-    split(0, disp[(size_t)ag * 3 + 2], nz, tz);
-    nx = min(max(nx, -kMxLimit), kMxLimit);
-    ny = min(max(ny, -kMxLimit), kMxLimit);
-    nz = min(max(nz, -kMxLimit), kMxLimit) - 1 - lead;  // source sample of the first tap of output 0, less lead
-    // the tile's stencil origins, wave-uniform
-    int ox[4], oy[4], oz[4], zb[4];
-    int zmin = kMxLimit;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        ox[q] = __builtin_amdgcn_readlane(nx, 16 * q) - 1;
-        oy[q] = __builtin_amdgcn_readlane(ny, 16 * q) - 1;
-        oz[q] = __builtin_amdgcn_readlane(nz, 16 * q);
-        if (groups >> q & 1) zmin = min(zmin, oz[q]);
-    }
-    zmin &= -2;
-    S.any = 0;
-    S.zlo = kMxLimit;
-    S.zhi = -2 * kMxLimit;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int sh = (oz[q] - zmin) & Geo::kShift;
-        zb[q] = oz[q] - sh;
-        S.any |= sh;
-        S.zlo = min(S.zlo, zb[q]);
-        S.zhi = max(S.zhi, zb[q]);
-    }
-    S.any = uni(S.any);
-    S.zlo = uni(S.zlo);
-    S.zhi = uni(S.zhi);
-    S.sh = (nz - zmin) & Geo::kShift;
-    S.zb = nz - S.sh;
-    cr_taps(tz, S.wz, S.dwz);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        S.wz[c] *= Ops::kUnscale;
-        S.dwz[c] *= Ops::kUnscale;
-    }
-    // Distinct columns: a lane's column is that of the first group's lane that
-    // reaches the same column with the same window.
-    const int cx = nx - 1 + (n & 3), cy = ny - 1 + (n >> 2);
-    int owner = lane;
-#pragma unroll
-    for (int q = 2; q >= 0; --q) {
-        const int a = cx - ox[q], b = cy - oy[q];
-        const bool same = (q < g) & ((groups >> q & 1) != 0) & ((unsigned)a < 4u) & ((unsigned)b < 4u) & (S.zb == zb[q]);
-        owner = same ? 16 * q + 4 * b + a : owner;
-    }
-    const bool active = (groups >> g & 1) != 0;
-    const bool mine = active & (owner == lane);
-    const unsigned long long mask = __ballot(mine);
-    S.ns = uni((int)__popcll(mask));
-    S.rest = nrest;
-    if (S.ns > 32) ++nrest;
-    if (S.ns > kMxSlots || nrest > kMxRest) return false;
-    const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-    const int slot = __builtin_amdgcn_ds_bpermute(4 * owner, rank);
-    // weights: 0 but for the rows of an A-scan in the slots of its columns.
-    // Unused slots: an offset beyond the volume, whose loads return 0.
-    const i32x4 zero = {0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) M.a[V][k][lane] = zero;
-    if (S.ns > 32) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) M.rest[S.rest][k][lane] = i32x2{0, 0};
-    }
-    M.key[V][lane] = make_int2((int)0x80000000u, (int)0x80000000u);
-    int* const off = reinterpret_cast<int*>(&M.off[V][0][0]);
-    if (lane < 32) off[lane] = (int)0x80000000u;
-    mx_lds_fence();
-    if (mine) {
-        const int col = min(max(cy, 0), h - 1) * w + min(max(cx, 0), w - 1);
-        const int x = (int)((uint32_t)col * (uint32_t)dp * 2u);
-        M.key[V][slot] = make_int2(x, S.zb);
-        if (slot < 32) off[(slot & 3) * 8 + (slot >> 2)] = x + 2 * (S.zb - S.zlo);
-    }
-    {
-        float wx[4], dwx[4], wy[4], dwy[4];
-        cr_taps(tx, wx, dwx);
-        cr_taps(ty, wy, dwy);
-        const int a = n & 3, b = n >> 2;
-        float vx = wx[0], gx = dwx[0], vy = wy[0], gy = dwy[0];
-#pragma unroll
-        for (int c = 1; c < 4; ++c) {
-            vx = a == c ? wx[c] : vx;
-            gx = a == c ? dwx[c] : gx;
-            vy = b == c ? wy[c] : vy;
-            gy = b == c ? dwy[c] : gy;
-        }
-        const float wt[3] = {vx * vy, gx * vy, vx * gy};
-        const int q = (slot & 31) >> 2, row = 16 * (slot & 3) + 4 * g;
-        unsigned short* a0 = reinterpret_cast<unsigned short*>(&M.a[V][0][0]) + row * 8 + q;
-        unsigned short* a1 = reinterpret_cast<unsigned short*>(&M.rest[S.rest][0][0]) + row * 4 + q;
-        unsigned short p[3][3];
-#pragma unroll
-        for (int o = 0; o < 3; ++o) Ops::split_weight(wt[o], p[o]);
-        if (active & (slot < 32)) {
-#pragma unroll
-            for (int o = 0; o < 3; ++o)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) a0[(k * 64 + o) * 8] = p[o][k];
-        }
-        if (active & (slot >= 32)) {
-#pragma unroll
-            for (int o = 0; o < 3; ++o)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) a1[(k * 64 + o) * 4] = p[o][k];
-        }
-    }
-    mx_lds_fence();
-    return true;
-}
-
-// wave-uniform: no window of the tile reaches over an end of the A-scans
-template <typename Geo>
-__device__ __forceinline__ bool mx_inside(const MxScan& S, int step, int dp)
-{
-    return S.zlo + Geo::kOut * step >= 0 && S.zhi + Geo::kOut * step + Geo::kWin <= dp;
-}
-
-// The samples of one depth step of one scan: kL depths of slots 4 q + kg.
-template <int N, int L>
-__device__ __forceinline__ void mx_load(typename MxDwords<L / 2>::type (&s)[8], const MxScan& S,
-                                        const MxLds<N, L>& M, int V, __amdgpu_buffer_rsrc_t r, int step, int dp, int lane)
-{
-    typedef MxGeo<L> Geo;
-    const int n = lane & 15, kg = lane >> 4, z0 = Geo::kOut * step;
-    uint32_t off[8];
-    const i32x4 t0 = M.off[V][kg][0], t1 = M.off[V][kg][1];
-    const uint32_t lo = 2u * (uint32_t)min(max(S.zlo + z0 + L * n, 0), dp - L);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        off[q] = (uint32_t)t0[q] + lo;
-        off[4 + q] = (uint32_t)t1[q] + lo;
-    }
-    if (S.zlo != S.zhi && !mx_inside<Geo>(S, step, dp)) {  // windows that start apart are clamped one by one
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int2 k = M.key[V][4 * q + kg];
-            off[q] = (uint32_t)k.x + 2u * (uint32_t)min(max(k.y + z0 + L * n, 0), dp - L);
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) s[q] = MxDwords<L / 2>::load(r, off[q], 0);
-}
-
-// D = the blends of slots 0 .. 31 of scan V, whose samples are s
-template <typename T, int N, int L, typename S>
-__device__ __forceinline__ void mx_blend(f32x4 (&D)[L], const S (&s)[8], const MxLds<N, L>& M, int V, int lane)
-{
-    const i32x4 a0 = M.a[V][0][lane], a1 = M.a[V][1][lane], a2 = M.a[V][2][lane];
-#pragma unroll
-    for (int p = 0; p < L / 2; ++p) {
-        i32x4 b0, b1;
-        mx_pack(s, p, b0, b1);
-        D[2 * p] = MxOps<T>::mfma(a0, b0, D[2 * p]);
-        D[2 * p + 1] = MxOps<T>::mfma(a0, b1, D[2 * p + 1]);
-        D[2 * p] = MxOps<T>::mfma(a1, b0, D[2 * p]);
-        D[2 * p + 1] = MxOps<T>::mfma(a1, b1, D[2 * p + 1]);
-        D[2 * p] = MxOps<T>::mfma(a2, b0, D[2 * p]);
-        D[2 * p + 1] = MxOps<T>::mfma(a2, b1, D[2 * p + 1]);
-    }
-}
-
-// D += the blends of slots 32 .. 47 (only where a tile has them)
-template <typename T, int N, int L>
-__device__ __forceinline__ void mx_rest(f32x4 (&D)[L], const MxScan& S, const MxLds<N, L>& M, int V,
-                                        __amdgpu_buffer_rsrc_t r, int step, int dp, int lane)
-{
-    typedef MxGeo<L> Geo;
-    const int n = lane & 15, kg = lane >> 4, z0 = Geo::kOut * step;
-    typename MxDwords<L / 2>::type s[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int2 k = M.key[V][32 + 4 * q + kg];
-        const int m = min(max(k.y + z0 + L * n, 0), dp - L);
-        s[q] = MxDwords<L / 2>::load(r, (uint32_t)k.x + (uint32_t)(m * 2), 0);
-    }
-    const i32x2 a0 = M.rest[S.rest][0][lane], a1 = M.rest[S.rest][1][lane], a2 = M.rest[S.rest][2][lane];
-#pragma unroll
-    for (int p = 0; p < L / 2; ++p) {
-        i32x2 b0, b1;
-        mx_pack(s, p, b0, b1);
-        D[2 * p] = MxOps<T>::mfma(a0, b0, D[2 * p]);
-        D[2 * p + 1] = MxOps<T>::mfma(a0, b1, D[2 * p + 1]);
-        D[2 * p] = MxOps<T>::mfma(a1, b0, D[2 * p]);
-        D[2 * p + 1] = MxOps<T>::mfma(a1, b1, D[2 * p + 1]);
-        D[2 * p] = MxOps<T>::mfma(a2, b0, D[2 * p]);
-        D[2 * p + 1] = MxOps<T>::mfma(a2, b1, D[2 * p + 1]);
-    }
-}
-
-// L samples read at clamp(m, 0, dp - L), moved to m .. m + L - 1 with the edge
-// value beyond the A-scan: every wanted sample is among the lane's own, so the
-// move is an indexed read of them (through the lane's column of sh).
-template <int L>
-__device__ __forceinline__ void mx_edge(float (&v)[L], const int (&at)[L], float (*sh)[64], int lane)
-{
-#pragma unroll
-    for (int i = 0; i < L; ++i) sh[i][lane] = v[i];
-    mx_lds_fence();
-#pragma unroll
-    for (int i = 0; i < L; ++i) v[i] = sh[at[i]][lane];
-    mx_lds_fence();
-}
-
-// v moved K samples down (from the next lane's first ones) where `on`
-template <int K, int L>
-__device__ __forceinline__ void mx_move(float (&v)[L], bool on)
-{
-    float nx[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) nx[i] = row_next(v[i]);
-#pragma unroll
-    for (int i = 0; i < L; ++i) v[i] = on ? (i + K < L ? v[i + K < L ? i + K : 0] : nx[i + K >= L ? i + K - L : 0]) : v[i];
-}
-
-// The lateral blends (value, x and y derivative) of this lane's A-scan at its L
-// positions: the edge values beyond the A-scan, then (MOVE) the window's shift.
-template <int N, int L, bool MOVE>
-__device__ __forceinline__ void mx_rows(float (&v)[L], float (&vx)[L], float (&vy)[L], const f32x4 (&D)[L],
-                                        const MxScan& S, MxLds<N, L>& M, int step, int dp, int lane)
-{
-    typedef MxGeo<L> Geo;
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-        v[i] = D[i][0];
-        vx[i] = D[i][1];
-        vy[i] = D[i][2];
-    }
-    if (!mx_inside<Geo>(S, step, dp)) {
-        const int m = S.zb + Geo::kOut * step + L * (lane & 15), mc = min(max(m, 0), dp - L);
-        int at[L];
-#pragma unroll
-        for (int i = 0; i < L; ++i) at[i] = min(max(m + i, 0), dp - 1) - mc;
-        mx_edge<L>(v, at, M.edge, lane);
-        mx_edge<L>(vx, at, M.edge, lane);
-        mx_edge<L>(vy, at, M.edge, lane);
-    }
-    if (MOVE && (S.any & 1)) {
-        mx_move<1>(v, S.sh & 1);
-        mx_move<1>(vx, S.sh & 1);
-        mx_move<1>(vy, S.sh & 1);
-    }
-    if (MOVE && (S.any & 2)) {
-        mx_move<2>(v, S.sh & 2);
-        mx_move<2>(vx, S.sh & 2);
-        mx_move<2>(vy, S.sh & 2);
-    }
-}
-
-// sum_c w[c] x[i + c] (x: this lane's positions and three of the next lane's)
-template <int N>
-__device__ __forceinline__ float mx_fir(const float (&w)[4], const float (&x)[N], int i)
-{
-    float s = w[0] * x[i];
-#pragma unroll
-    for (int c = 1; c < 4; ++c) s = fmaf(w[c], x[i + c], s);
-    return s;
-}
-
-// The groups to evaluate after `groups` (0: done).  bad: a sum was not finite.
-__device__ __forceinline__ int mx_next(int groups, bool bad)
-{
-    if (groups & (groups - 1)) return bad ? 1 : (groups == 3 ? 12 : 0);  // several groups
-    return groups == 8 ? 0 : groups << 1;
-}
+// One wave evaluates a 2 x 2 tile of output A-scans (tile_blend.h).  Lane 16 g +
+// n holds the lateral blends (value, x and y derivative) of A-scan g at L
+// consecutive source depths, and everything along depth (interpolation of Eq. 2,
+// residual, loss of Eq. 4, its adjoint) runs on the vector units in that layout,
+// the neighbouring depths coming from the next lane of the row (DPP).
 
 // The seven sums of an A-scan, one part of them per lane of its row.
 struct MxSums {
@@ -1253,22 +735,6 @@ __device__ __forceinline__ void mx_depth(MxSums& A, const float (&x)[L + 3], con
     }
 }
 
-// The tile of a wave: 4 x 4 A-scans per workgroup in 8 bands of block rows (one
-// per XCD when the job fills the grid), swept column by column, so that the
-// rows a block reads are still in that XCD's L2 when the next column reads
-// them.  False: a whole block beyond the job's, or a wave outside the scan.
-__device__ __forceinline__ bool mx_tile(int w, int h, int t, int wv, int& i0, int& j0)
-{
-    const int bpr = (w + 3) >> 2;
-    const int brows = (h + 3) >> 2;
-    const int rpb = (brows + 7) >> 3;
-    const int band = t / (rpb * bpr), tb = t - band * (rpb * bpr);
-    const int brow = band * rpb + tb % rpb;
-    i0 = 4 * (tb / rpb) + 2 * (wv & 1);
-    j0 = 4 * brow + 2 * (wv >> 1);
-    return t < 8 * rpb * bpr && brow < brows && i0 < w && j0 < h;
-}
-
 // Bound by vector issue: a step of eight depths per lane takes some 440 vector
 // and 48 matrix instructions (16 cycles each, partly overlapped), of which the
 // depth work is 46 per sample pair and the operand packing 8.  Three waves per
@@ -1284,9 +750,9 @@ template <typename T, int L>
 __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
 {
     if (jobs.skip && *jobs.skip) return;
-    __shared__ MxLds<2, L> lds[4];
+    __shared__ MxLds<2, 2, L> lds[4];
     const int wv = uni((int)(threadIdx.x >> 6));
-    MxLds<2, L>& M = lds[wv];
+    MxLds<2, 2, L>& M = lds[wv];
     const int lb = xcd_block(blockIdx.x, gridDim.x);
     int jid = -1;
     for (int q = 0; q < jobs.n; ++q)
@@ -1300,7 +766,7 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.sx), (short)0, (int)J.vol_bytes, kRsrcWord3);
     const __amdgpu_buffer_rsrc_t ry =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.sy), (short)0, (int)J.vol_bytes, kRsrcWord3);
-    typedef MxGeo<L> Geo;
+    typedef MxGeo<2, L> Geo;
     const float eps = J.eps_h;
     const float inv_eps = 1.0f / J.eps_h;
     // The groups of the tile evaluated together: all four; two where the four
@@ -1325,8 +791,8 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
         const float ie_lo = p0 < Geo::kOut ? inv_eps : 0.f, ie_hi = p0 + 2 < Geo::kOut ? inv_eps : 0.f;
         MxScan SX, SY;
         int nrest = 0;
-        if (!mx_setup<T>(SX, M, 0, J.disp, ag, pg, 0, w, h, dp, lane, groups, nrest) ||
-            !mx_setup<T>(SY, M, 1, J.disp + (size_t)J.na * 3, ag, pg, SX.sh, w, h, dp, lane, groups, nrest)) {
+        if (!mx_setup<T, 3>(SX, M, 0, J.disp, ag, pg, 0, w, h, dp, lane, groups, nrest) ||
+            !mx_setup<T, 3>(SY, M, 1, J.disp + (size_t)J.na * 3, ag, pg, SX.sh, w, h, dp, lane, groups, nrest)) {
             groups = 3;  // two groups never need more than 32 slots
             continue;
         }
@@ -1335,22 +801,30 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
         for (int s = 0; s < nsteps; ++s) {
             float x[L + 3], xx[L], xy[L], y[L + 3], yx[L], yy[L];
             {
-                typename MxDwords<L / 2>::type qx[8], qy[8];
+                typename MxDwords<Geo::kDw>::type qx[8], qy[8];
                 mx_load(qx, SX, M, 0, rx, s, dp, lane);
                 mx_load(qy, SY, M, 1, ry, s, dp, lane);
-                float v[L];
+                float v[3][L];
                 f32x4 D[L] = {};
                 mx_blend<T>(D, qx, M, 0, lane);
                 if (SX.ns > 32) mx_rest<T>(D, SX, M, 0, rx, s, dp, lane);
-                mx_rows<2, L, false>(v, xx, xy, D, SX, M, s, dp, lane);
+                mx_rows<false>(v, D, SX, M, s, dp, lane);
 #pragma unroll
-                for (int i = 0; i < L; ++i) x[i] = v[i];
+                for (int i = 0; i < L; ++i) {
+                    x[i] = v[0][i];
+                    xx[i] = v[1][i];
+                    xy[i] = v[2][i];
+                }
                 f32x4 E[L] = {};
                 mx_blend<T>(E, qy, M, 1, lane);
                 if (SY.ns > 32) mx_rest<T>(E, SY, M, 1, ry, s, dp, lane);
-                mx_rows<2, L, true>(v, yx, yy, E, SY, M, s, dp, lane);
+                mx_rows<true>(v, E, SY, M, s, dp, lane);
 #pragma unroll
-                for (int i = 0; i < L; ++i) y[i] = v[i];
+                for (int i = 0; i < L; ++i) {
+                    y[i] = v[0][i];
+                    yx[i] = v[1][i];
+                    yy[i] = v[2][i];
+                }
             }
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
@@ -1923,11 +1397,11 @@ __global__ __launch_bounds__(256, 2) void k_multi_mx(const StructMultiJob<N> J)
 {
     if (J.skip && *J.skip) return;
     constexpr int NP = N * (N - 1) / 2, L = 4;
-    typedef MxGeo<L> Geo;
-    __shared__ MxLds<N, L> lds[4];
+    typedef MxGeo<2, L> Geo;
+    __shared__ MxLds<2, N, L> lds[4];
     __shared__ f32x4 taps[4][N][4][2];  // per wave, volume and A-scan: the depth taps and their derivatives
     const int wv = uni((int)(threadIdx.x >> 6));
-    MxLds<N, L>& M = lds[wv];
+    MxLds<2, N, L>& M = lds[wv];
     const int w = J.w, h = J.h, d = J.d, dp = J.dp;
     int i0, j0;
     if (!mx_tile(w, h, xcd_block(blockIdx.x, gridDim.x), wv, i0, j0)) return;
@@ -1952,7 +1426,7 @@ __global__ __launch_bounds__(256, 2) void k_multi_mx(const StructMultiJob<N> J)
         bool fits = true;
 #pragma unroll
         for (int V = 0; V < N; ++V) {
-            fits = fits && mx_setup<T>(S[V], M, V, J.disp + (size_t)V * J.na * 3, ag, pg, V ? S[0].sh : 0, w, h, dp, lane,
+            fits = fits && mx_setup<T, 3>(S[V], M, V, J.disp + (size_t)V * J.na * 3, ag, pg, V ? S[0].sh : 0, w, h, dp, lane,
                                        groups, nrest);
             if ((lane & 15) == 0) {
                 taps[wv][V][g][0] = f32x4{S[V].wz[0], S[V].wz[1], S[V].wz[2], S[V].wz[3]};
@@ -1970,14 +1444,14 @@ __global__ __launch_bounds__(256, 2) void k_multi_mx(const StructMultiJob<N> J)
 #pragma unroll
             for (int c = 0; c < 7; ++c) acc[q][c] = 0.f;
         const int nsteps = (d + S[0].any + Geo::kOut - 1) / Geo::kOut;
-        typename MxDwords<L / 2>::type next[8];
+        typename MxDwords<Geo::kDw>::type next[8];
         mx_load(next, S[0], M, 0, rs[0], 0, dp, lane);
         for (int s = 0; s < nsteps; ++s) {
             float I[N][L], X[N][L], Y[N][L], Z[N][L];
 #pragma unroll
             for (int V = 0; V < N; ++V) {
                 // the next volume's samples are loaded while this one is blended
-                typename MxDwords<L / 2>::type q[8];
+                typename MxDwords<Geo::kDw>::type q[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) q[k] = next[k];
                 if (V + 1 < N) mx_load(next, S[V + 1], M, V + 1, rs[V + 1], s, dp, lane);
@@ -1986,21 +1460,21 @@ __global__ __launch_bounds__(256, 2) void k_multi_mx(const StructMultiJob<N> J)
                 f32x4 D[L] = {};
                 mx_blend<T>(D, q, M, V, lane);
                 if (S[V].ns > 32) mx_rest<T>(D, S[V], M, V, rs[V], s, dp, lane);
-                float v[L], vx[L], vy[L];
-                if (V == 0) mx_rows<N, L, false>(v, vx, vy, D, S[V], M, s, dp, lane);
-                else mx_rows<N, L, true>(v, vx, vy, D, S[V], M, s, dp, lane);
+                float v[3][L];
+                if (V == 0) mx_rows<false>(v, D, S[V], M, s, dp, lane);
+                else mx_rows<true>(v, D, S[V], M, s, dp, lane);
                 float e[L + 3], ex[L + 3], ey[L + 3];
 #pragma unroll
                 for (int i = 0; i < L; ++i) {
-                    e[i] = v[i];
-                    ex[i] = vx[i];
-                    ey[i] = vy[i];
+                    e[i] = v[0][i];
+                    ex[i] = v[1][i];
+                    ey[i] = v[2][i];
                 }
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    e[L + i] = row_next(v[i]);
-                    ex[L + i] = row_next(vx[i]);
-                    ey[L + i] = row_next(vy[i]);
+                    e[L + i] = row_next(e[i]);
+                    ex[L + i] = row_next(ex[i]);
+                    ey[L + i] = row_next(ey[i]);
                 }
                 const f32x4 t0 = taps[wv][V][g][0], t1 = taps[wv][V][g][1];
                 const float wz[4] = {t0[0], t0[1], t0[2], t0[3]}, dwz[4] = {t1[0], t1[1], t1[2], t1[3]};
@@ -2181,10 +1655,6 @@ hipError_t launch_sum(const SumJobs& jobs, int total_blocks, hipStream_t s)
 //   the one-A-scan kernels, whose waves are shorter, are as fast or faster
 //   (64 x 64 x 128: 14 against 18 us, 64 x 64 x 400: 18 against 25, 90 x 90 x
 //   400: 31 against 29, 128 x 128 x 256: 43 against 32).
-//   Its depths per lane: eight, since a 128-bit load brings twice the samples
-//   of a 64-bit one in the same time, unless windows of four leave enough
-//   fewer positions unused (a window of four costs 1.2 times half of one of
-//   eight); four where an A-scan has fewer than eight samples.
 //   k_struct2 loads sample pairs, 32-bit aligned at an even storage pitch
 //   (every level of a pair); an odd pitch (volumes in the caller's layout)
 //   takes one sample per lane.
@@ -2193,8 +1663,7 @@ enum { kByMx8, kByMx4, kByPairs, kBySamples };
 static int struct_form(const StructJob& J, bool axial)
 {
     if (axial || J.na < kMxMinAscans) return J.dp % 2 == 0 ? kByPairs : kBySamples;
-    const int n8 = (J.d + MxGeo<8>::kOut - 1) / MxGeo<8>::kOut, n4 = (J.d + MxGeo<4>::kOut - 1) / MxGeo<4>::kOut;
-    return J.dp >= 8 && 17 * n8 <= 10 * n4 ? kByMx8 : kByMx4;
+    return mx_eight(J.d, J.dp) ? kByMx8 : kByMx4;
 }
 
 template <typename T, bool AXIAL>

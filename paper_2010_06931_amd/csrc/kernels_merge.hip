@@ -10,17 +10,17 @@
 //                   validity (Eq. 5); where both vanish, OCT keeps the scan with
 //                   the lower density and OCTA is 0
 //   k_merge_volume  resample both scans with their fields (Eq. 2 interpolator,
-//                   value only) and write the weighted sum
+//                   value only) and write the weighted sum; k_merge_tile the
+//                   same on the matrix cores, for volumes of many A-scans
 #include <hip/hip_runtime.h>
 
 #include "octmc_internal.h"
+#include "tile_blend.h"
 
 namespace octmc {
 namespace {
 
 constexpr double kFix = 4294967296.0;  // 2^32
-
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 __device__ __forceinline__ void bilin(float x, float y, int w, int h, int& x0, int& y0, int& x1, int& y1, float& fx,
                                       float& fy)
@@ -124,8 +124,6 @@ template <typename T>
 __device__ __forceinline__ float ld(const void* p, size_t q);
 template <>
 __device__ __forceinline__ float ld<float>(const void* p, size_t q) { return static_cast<const float*>(p)[q]; }
-struct bf16_t {};
-struct f16_t {};
 template <>
 __device__ __forceinline__ float ld<bf16_t>(const void* p, size_t q)
 {
@@ -155,8 +153,6 @@ __device__ __forceinline__ float ldb<f16_t>(__amdgpu_buffer_rsrc_t r, uint32_t v
 {
     return (float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0));
 }
-template <typename T> struct bytes_of { static constexpr uint32_t v = 2; };
-template <> struct bytes_of<float> { static constexpr uint32_t v = 4; };
 
 // value of the next lane (DPP whole-wave shift; lane 63 reads 0 by bound control)
 __device__ __forceinline__ float next_lane(float v)
@@ -208,7 +204,7 @@ __global__ __launch_bounds__(256) void k_merge_volume(const void* __restrict__ s
             for (int c = 0; c < 4; ++c) {
                 off[V][b * 4 + c] = (uint32_t)__builtin_amdgcn_readfirstlane(
                     (int)((uint32_t)(clampi(ny - 1 + b, 0, h - 1) * w + clampi(nx - 1 + c, 0, w - 1)) * (uint32_t)dp *
-                          bytes_of<T>::v));
+                          esize<T>::v));
                 wl[V][b * 4 + c] = wx[c] * wy[b];
             }
         base[V] = nz - 1;
@@ -218,7 +214,7 @@ __global__ __launch_bounds__(256) void k_merge_volume(const void* __restrict__ s
         float res = 0.f;
 #pragma unroll
         for (int V = 0; V < 2; ++V) {
-            const uint32_t voff = (uint32_t)clampi(base[V] + kMergeStep * n + lane, 0, d - 1) * bytes_of<T>::v;
+            const uint32_t voff = (uint32_t)clampi(base[V] + kMergeStep * n + lane, 0, d - 1) * esize<T>::v;
             float c = 0.f;
 #pragma unroll
             for (int q = 0; q < 16; ++q) c = fmaf(wl[V][q], ldb<T>(rs[V], voff, off[V][q]), c);
@@ -232,6 +228,97 @@ __global__ __launch_bounds__(256) void k_merge_volume(const void* __restrict__ s
         }
         const int k = kMergeStep * n + lane;
         if (lane < kMergeStep && k < d) out[(size_t)a * d + k] = res;
+    }
+}
+
+// k_merge_volume on the matrix cores: one wave per 2 x 2 tile of A-scans
+// (tile_blend.h), L depths per lane.  k_merge_volume loads every column of a
+// tile up to four times, one sample per lane and load, and keeps the texture
+// path busy with that; here a tile's columns are loaded once, 16 bytes per lane.
+// 500 x 500 x 465: 1.50 -> 0.46 ms from BF16 volumes, 1.61 -> 0.84 ms from
+// float32 ones.
+template <typename T, int L>
+__global__ __launch_bounds__(256, 3) void k_merge_tile(const void* __restrict__ sx, const void* __restrict__ sy,
+                                                       const float* __restrict__ disp, const float4* __restrict__ wts,
+                                                       int which, int w, int h, int d, int dp, uint32_t vol_bytes,
+                                                       float* __restrict__ out)
+{
+    constexpr int es = (int)esize<T>::v;
+    typedef MxGeo<es, L> Geo;
+    __shared__ MxLds<es, 2, L> lds[4];
+    const int wv = uni((int)(threadIdx.x >> 6));
+    MxLds<es, 2, L>& M = lds[wv];
+    int i0, j0;
+    if (!mx_tile(w, h, xcd_block(blockIdx.x, gridDim.x), wv, i0, j0)) return;
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(sx), (short)0, (int)vol_bytes, kRsrcWord3);
+    const __amdgpu_buffer_rsrc_t ry =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(sy), (short)0, (int)vol_bytes, kRsrcWord3);
+    const size_t na = (size_t)w * h;
+    int groups = 15;  // of the tile's A-scans, as in the structural kernel
+    for (;;) {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int g = lane >> 4, p0 = L * (lane & 15);
+        const int2 pg = make_int2(min(i0 + (g & 1), w - 1), min(j0 + (g >> 1), h - 1));
+        const int ag = pg.y * w + pg.x;
+        const bool write = i0 + (g & 1) < w && j0 + (g >> 1) < h && (groups >> g & 1);
+        MxScan SX, SY;
+        int nrest = 0;
+        if (!mx_setup<T, 1>(SX, M, 0, disp, ag, pg, 0, w, h, dp, lane, groups, nrest) ||
+            !mx_setup<T, 1>(SY, M, 1, disp + na * 3, ag, pg, SX.sh, w, h, dp, lane, groups, nrest)) {
+            groups = 3;
+            continue;
+        }
+        const float4 wt = wts[ag];
+        const float wx = which ? wt.z : wt.x, wy = which ? wt.w : wt.y;
+        float* const o = out + (size_t)ag * d;
+        float bad = 0.f;  // not a number once an output was not finite
+        const int nsteps = (d + SX.any + Geo::kOut - 1) / Geo::kOut;
+        for (int s = 0; s < nsteps; ++s) {
+            typename MxDwords<Geo::kDw>::type qx[8], qy[8];
+            mx_load(qx, SX, M, 0, rx, s, dp, lane);
+            mx_load(qy, SY, M, 1, ry, s, dp, lane);
+            float x[L + 3], y[L + 3], v[1][L];
+            f32x4 D[L] = {};
+            mx_blend<T>(D, qx, M, 0, lane);
+            if (SX.ns > 32) mx_rest<T>(D, SX, M, 0, rx, s, dp, lane);
+            mx_rows<false>(v, D, SX, M, s, dp, lane);
+#pragma unroll
+            for (int i = 0; i < L; ++i) x[i] = v[0][i];
+            f32x4 E[L] = {};
+            mx_blend<T>(E, qy, M, 1, lane);
+            if (SY.ns > 32) mx_rest<T>(E, SY, M, 1, ry, s, dp, lane);
+            mx_rows<true>(v, E, SY, M, s, dp, lane);
+#pragma unroll
+            for (int i = 0; i < L; ++i) y[i] = v[0][i];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                x[L + i] = row_next(x[i]);
+                y[L + i] = row_next(y[i]);
+            }
+            float r[L];
+#pragma unroll
+            for (int i = 0; i < L; ++i) {
+                r[i] = fmaf(wy, mx_fir(SY.wz, y, i), wx * mx_fir(SX.wz, x, i));
+                bad = fmaf(r[i], 0.f, bad);
+            }
+            const int k0 = Geo::kOut * s + p0 - SX.sh;  // output of position 0
+            if (write) {
+                if (p0 + L <= Geo::kOut && k0 >= 0 && k0 + L <= d) {
+                    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+                    for (int i = 0; i < L; i += 4)
+                        *reinterpret_cast<f32x4u*>(o + k0 + i) = f32x4u{r[i], r[i + 1], r[i + 2], r[i + 3]};
+                } else {
+#pragma unroll
+                    for (int i = 0; i < L; ++i)
+                        if (p0 + i < Geo::kOut && (unsigned)(k0 + i) < (unsigned)d) o[k0 + i] = r[i];
+                }
+            }
+        }
+        groups = mx_next(groups, __ballot(bad != 0.f) != 0);
+        if (!groups) return;
     }
 }
 
@@ -368,30 +455,41 @@ hipError_t launch_merge_weights(const float* disp, int w, int h, const unsigned 
                        kappa, tau, wts);
     return hipGetLastError();
 }
-hipError_t launch_merge_volume(const void* vx_, const void* vy_, octmc_dtype dt, const float* disp,
-                               const float4* wts, int which, int w, int h, int d, int dp, float* out, hipStream_t s)
+// With fewer A-scans the tiles do not fill the device and the merge takes
+// k_merge_volume.
+constexpr int kMergeTileMinAscans = 8192;
+
+template <typename T, int L>
+static hipError_t launch_merge_t(const void* vx, const void* vy, const float* disp, const float4* wts, int which, int w,
+                                 int h, int d, int dp, float* out, hipStream_t s)
 {
-    const int blocks = (w * h + 3) / 4;
-    const size_t bytes = (size_t)w * h * dp * (dt == OCTMC_F32 ? 4 : 2);
+    const size_t bytes = (size_t)w * h * dp * esize<T>::v;
     if (bytes >= (1ull << 31)) return hipErrorInvalidValue;  // 32-bit buffer offsets
-    const uint32_t vb = (uint32_t)bytes;
+    if (w * h >= kMergeTileMinAscans)
+        hipLaunchKernelGGL((k_merge_tile<T, L>), dim3(struct_mx_blocks(w, h)), dim3(256), 0, s, vx, vy, disp, wts, which,
+                           w, h, d, dp, (uint32_t)bytes, out);
+    else
+        hipLaunchKernelGGL(k_merge_volume<T>, dim3((w * h + 3) / 4), dim3(256), 0, s, vx, vy, disp, wts, which, w, h, d,
+                           dp, (uint32_t)bytes, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_merge_volume(const void* vx, const void* vy, octmc_dtype dt, const float* disp, const float4* wts,
+                               int which, int w, int h, int d, int dp, float* out, hipStream_t s)
+{
+    const bool eight = mx_eight(d, dp);
     switch (dt) {
     case OCTMC_F32:
-        hipLaunchKernelGGL(k_merge_volume<float>, dim3(blocks), dim3(256), 0, s, vx_, vy_, disp, wts, which, w, h, d, dp,
-                           vb, out);
-        break;
+        return launch_merge_t<float, 4>(vx, vy, disp, wts, which, w, h, d, dp, out, s);
     case OCTMC_BF16:
-        hipLaunchKernelGGL(k_merge_volume<bf16_t>, dim3(blocks), dim3(256), 0, s, vx_, vy_, disp, wts, which, w, h,
-                           d, dp, vb, out);
-        break;
+        return eight ? launch_merge_t<bf16_t, 8>(vx, vy, disp, wts, which, w, h, d, dp, out, s)
+                     : launch_merge_t<bf16_t, 4>(vx, vy, disp, wts, which, w, h, d, dp, out, s);
     case OCTMC_F16:
-        hipLaunchKernelGGL(k_merge_volume<f16_t>, dim3(blocks), dim3(256), 0, s, vx_, vy_, disp, wts, which, w, h,
-                           d, dp, vb, out);
-        break;
+        return eight ? launch_merge_t<f16_t, 8>(vx, vy, disp, wts, which, w, h, d, dp, out, s)
+                     : launch_merge_t<f16_t, 4>(vx, vy, disp, wts, which, w, h, d, dp, out, s);
     default:
         return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace octmc

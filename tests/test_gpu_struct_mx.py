@@ -1,5 +1,6 @@
 """The matrix-core structural kernels (16-bit volumes of at least 8192 A-scans; a
-pair, and three or four volumes) against the FP64 oracle, at the sizes and fields where its tiling can go wrong:
+pair, and three or four volumes) and merge (volumes of at least 8192 A-scans)
+against the FP64 oracle, at the sizes and fields where its tiling can go wrong:
 scans that are no multiple of its 4 x 4 blocks and 2 x 2 tiles, depths around
 its windows of 16 x 4 and 16 x 8 samples (58 and 122 outputs a step, the
 smallest depths), tiles whose A-scans share all, some or none of their source
@@ -133,3 +134,46 @@ def test_parity_multi(octmc, n, d, dtype, count, case):
     for k in ("F", "data", "str", "str05"):
         assert rel(t[k], ref[k]) < TOL, (k, t[k], ref[k])
     assert grad_err(g, gref) < TOL
+
+
+@pytest.mark.parametrize("n,d,dtype,case", [
+    (91, 122, "bf16", "noise"), (92, 123, "f16", "apart"), (93, 60, "f32", "noise"), (94, 121, "f32", "apart"),
+    (91, 59, "bf16", "depth"), (91, 4, "f32", "depth"), (92, 7, "f16", "noise"), (93, 233, "f32", "shift"),
+])
+def test_parity_merge(octmc, n, d, dtype, case):
+    log(f"matrix-core merge n={n} d={d} {dtype} {case}")
+    S, A, V = _inputs(n, d, dtype, n + d)
+    O, _, _ = _inputs(n, d, "f32", n + d + 1)
+    D = _field(case, n, n + d)
+    P = octmc.Pair(S[0], S[1], ox=O[0], oy=O[1], vx=V[0], vy=V[1], dtype=dtype, levels=1)
+    mo, ma = P.merge(D.cuda(), octa=True)
+    mo, ma = mo.double().cpu().numpy(), ma.double().cpu().numpy()
+    P.close()
+    Os = [oracle.substitute_invalid(O[q], V[q], q) for q in range(2)]
+    ro, ra, _, _ = oracle.merge(S[0].double(), S[1].double(), D.double(), Os[0], Os[1], V[0].double(), V[1].double(),
+                                P.params.merge_kappa, P.params.merge_tau)
+    # float32 positions of order 100 put the densities, and with them the
+    # weights, some 1e-5 off; the bar of every merge
+    assert np.abs(mo - ro).max() < TOL * max(1.0, np.abs(ro).max())
+    assert np.abs(ma - ra).max() < TOL * max(1.0, np.abs(ra).max())
+
+
+def test_merge_not_finite_stays_local(octmc):
+    n, d = 91, 130
+    log("matrix-core merge with a sample that is not a number")
+    S, A, V = _inputs(n, d, "bf16", 5)
+    D = _field("noise", n, 5)
+    r, c = 40, 33
+    S[0][r, c, 60] = float("nan")
+    P = octmc.Pair(S[0], S[1], ax=A[0], ay=A[1], vx=V[0], vy=V[1], dtype="bf16", levels=1)
+    mo, _ = P.merge(D.cuda())
+    mo = mo.cpu().numpy()
+    P.close()
+    f = np.floor(D[0].double().numpy()).astype(int)
+    jj, ii = np.mgrid[0:n, 0:n]
+    hit = np.zeros((n, n), bool)
+    for b in range(4):
+        for a in range(4):
+            hit |= (np.clip(jj + f[..., 1] - 1 + b, 0, n - 1) == r) & (np.clip(ii + f[..., 0] - 1 + a, 0, n - 1) == c)
+    bad = np.isnan(mo)
+    assert hit.sum() > 4 and (bad.any(axis=2) == hit).all() and (bad[hit].sum(axis=1) == 4).all()
