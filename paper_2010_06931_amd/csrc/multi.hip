@@ -30,22 +30,6 @@ constexpr int kMBlocks = 512;  // block partials of the reductions here
 
 size_t esz(octmc_dtype dt) { return dt == OCTMC_F32 ? 4 : 2; }
 
-// device temporaries freed with the list
-struct DevBufList {
-    std::vector<void*> p;
-    ~DevBufList()
-    {
-        for (void* q : p) (void)hipFree(q);
-    }
-    void* get(size_t bytes)
-    {
-        void* q = nullptr;
-        if (hipMalloc(&q, bytes ? bytes : 16) != hipSuccess) return nullptr;
-        p.push_back(q);
-        return q;
-    }
-};
-
 struct VolumePyr {
     int orient = 0;
     void* s[OCTMC_MAX_LEVELS] = {};   // structural volume, storage type
@@ -210,24 +194,16 @@ struct octmc_multi {
     double* sum_blk = nullptr;
     double* fsum = nullptr;  // [3] sum of all fields
     double* gp_blk = nullptr;
-    std::vector<void*> owned;
+    Blocks mem;
     std::atomic<int> busy{0};  // a solve holds the object (taken by compare-and-swap)
 
     template <typename T>
     hipError_t alloc(T** p, size_t bytes)
     {
-        void* q = nullptr;
-        hipError_t e = hipMalloc(&q, bytes ? bytes : 16);
-        if (e == hipSuccess) {
-            owned.push_back(q);
-            *p = static_cast<T*>(q);
-        }
-        return e;
-    }
-    ~octmc_multi()
-    {
-        views.clear();
-        for (void* p : owned) (void)hipFree(p);
+        void* q = mem.get(bytes);
+        if (!q) return mem.err;
+        *p = static_cast<T*>(q);
+        return hipSuccess;
     }
 };
 
@@ -315,16 +291,21 @@ struct MultiEvaluator final : Evaluator {
 // ingest one volume: staging, validity, en face image, OCTA substitution,
 // pyramid
 int ingest_volume(octmc_multi* M, int V, const octmc_shape* shape, const float* oct, const float* octa,
-                  const float* enface, const float* valid, hipStream_t s, DevBufList& tmp)
+                  const float* enface, const float* valid, hipStream_t s, Blocks& tmp)
 {
     VolumePyr& P = M->vol[V];
     const int w = shape->w, h = shape->h, d = shape->d, o = P.orient;
     const int nb = o == 0 ? h : w;
     const size_t na = (size_t)w * h, nv = na * d;
     const hipMemcpyKind kind = shape->mem == OCTMC_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-    float* f32 = (float*)tmp.get(nv * 4);
-    if (!f32) return fail(OCTMC_E_OOM, "out of device memory (staging)");
-    HIP_TRY(hipMemcpyAsync(f32, oct, nv * 4, kind, s));
+    // an input on the device is only read, before the creation returns
+    const float* f32 = oct;
+    if (shape->mem == OCTMC_MEM_HOST) {
+        float* copy = (float*)tmp.get(nv * 4);
+        if (!copy) return fail(OCTMC_E_OOM, "out of device memory (staging)");
+        HIP_TRY(hipMemcpyAsync(copy, oct, nv * 4, kind, s));
+        f32 = copy;
+    }
     const octmc_params& pr = M->params;
     if (pr.flags & OCTMC_CHECK_NAN) {
         unsigned* ctr = (unsigned*)tmp.get(64);
@@ -395,7 +376,7 @@ int ingest_volume(octmc_multi* M, int V, const octmc_shape* shape, const float* 
     }
     if (enface) HIP_TRY(hipMemcpyAsync(enf, enface, na * 4, kind, s));
     // pyramid
-    float* cur = f32;
+    const float* cur = f32;
     float* cen = enf;
     float* cv = vd;
     for (int l = 0; l < M->nlev; ++l) {
@@ -428,7 +409,7 @@ int merge_multi_impl(octmc_multi* M, const float* disp, float* merged_oct, float
 {
     const int w = M->w[0], h = M->h[0], d = M->d[0];
     const size_t na = (size_t)w * h;
-    DevBufList tmp;
+    Blocks tmp(M->ctx->cache);
     auto* grid = (unsigned long long*)tmp.get((size_t)M->n * na * 8);
     float* wo = (float*)tmp.get((size_t)M->n * na * 4);
     float* wa = (float*)tmp.get((size_t)M->n * na * 4);
@@ -448,7 +429,7 @@ int merge_multi_impl(octmc_multi* M, const float* disp, float* merged_oct, float
         for (int V = 0; V < M->n; ++V) mv.vol[V] = M->vol[V].octa;
         HIP_TRY(launch_merge_volume_multi(mv, OCTMC_F32, disp, wa, w, h, d, d, merged_octa, s));
     }
-    HIP_TRY(hipStreamSynchronize(s));  // the temporaries are freed on return
+    HIP_TRY(tmp.settle(s));
     return OCTMC_OK;
 }
 
@@ -486,6 +467,7 @@ int octmc_multi_create(octmc_ctx* ctx, const octmc_params* params_in, const octm
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto M = std::make_unique<octmc_multi>();
     M->ctx = ctx;
+    M->mem.cache = ctx->cache;
     M->params = *params;
     M->dtype = shape->dtype;
     M->n = n;
@@ -498,7 +480,7 @@ int octmc_multi_create(octmc_ctx* ctx, const octmc_params* params_in, const octm
         M->h[l] = (M->h[l - 1] + 1) / 2;
         M->d[l] = (M->d[l - 1] + 1) / 2;
     }
-    DevBufList tmp;
+    Blocks tmp(ctx->cache);
     for (int V = 0; V < n; ++V) {
         M->vol[V].orient = orient[V];
         OCTMC_TRY(ingest_volume(M.get(), V, shape, oct[V], octa ? octa[V] : nullptr, enface ? enface[V] : nullptr,
@@ -513,6 +495,7 @@ int octmc_multi_create(octmc_ctx* ctx, const octmc_params* params_in, const octm
         for (int Q = P + 1; Q < n; ++Q) {
             auto vp = std::make_unique<octmc_pair>();
             vp->ctx = ctx;
+            vp->mem.cache = ctx->cache;
             vp->params = pv;
             vp->dtype = M->dtype;
             vp->nlev = M->nlev;
@@ -543,7 +526,7 @@ int octmc_multi_create(octmc_ctx* ctx, const octmc_params* params_in, const octm
     HIP_TRY(M->alloc(&M->sum_blk, (size_t)kMBlocks * 3 * 8));
     HIP_TRY(M->alloc(&M->gp_blk, (size_t)kMBlocks * 8));
     HIP_TRY(M->alloc(&M->fsum, 3 * 8));
-    HIP_TRY(hipStreamSynchronize(s));  // staging is freed on return
+    HIP_TRY(tmp.settle(s));
     *out = M.release();
     return OCTMC_OK;
 }
@@ -552,7 +535,9 @@ int octmc_multi_destroy(octmc_multi* m)
 {
     if (m) {
         (void)hipSetDevice(ctx_device(m->ctx));
-        (void)hipDeviceSynchronize();
+        const bool idle = hipDeviceSynchronize() == hipSuccess;
+        m->mem.idle = idle;
+        for (auto& v : m->views) v->mem.idle = idle;
     }
     delete m;
     return OCTMC_OK;
@@ -590,7 +575,7 @@ int octmc_multi_register(octmc_multi* m, float* disp_out, float* merged_oct, flo
     const size_t n0 = (size_t)3 * m->n * m->w[0] * m->h[0];
     Solver sv;
     sv.m = pr.lbfgs_m;
-    DevBufList mem;
+    Blocks mem(m->ctx->cache);
     double** vecs[] = {&sv.x, &sv.g, &sv.p, &sv.xt, &sv.xprev, &sv.sc, &sv.gt, &sv.yc};
     for (double** v : vecs) {
         *v = (double*)mem.get(n0 * 8);
@@ -603,18 +588,8 @@ int octmc_multi_register(octmc_multi* m, float* disp_out, float* merged_oct, flo
     }
     sv.xt32 = (float*)mem.get(n0 * 4);
     if (!sv.xt32) return fail(OCTMC_E_OOM, "out of device memory (solver)");
-    double *h_terms = nullptr, *h_dots = nullptr;
-    HIP_TRY(hipHostMalloc(&h_terms, OCTMC_NTERMS * 8, hipHostMallocDefault));
-    struct HostFree {
-        double** a;
-        double** b;
-        ~HostFree()
-        {
-            if (*a) (void)hipHostFree(*a);
-            if (*b) (void)hipHostFree(*b);
-        }
-    } hf{&h_terms, &h_dots};
-    HIP_TRY(hipHostMalloc(&h_dots, (kMaxDots + 1) * 8, hipHostMallocDefault));
+    double *h_terms = mem.get_host(OCTMC_NTERMS), *h_dots = mem.get_host(kMaxDots + 1);
+    HIP_TRY(h_terms && h_dots ? hipSuccess : mem.err);
     if (rep) {
         std::memset(rep, 0, sizeof(*rep));
         rep->nlevels = m->nlev;
@@ -652,7 +627,7 @@ int octmc_multi_register(octmc_multi* m, float* disp_out, float* merged_oct, flo
     }
     HIP_TRY(launch_to_f32(sv.x, disp_out, n0, s));
     if (merged_oct) OCTMC_TRY(merge_multi_impl(m, disp_out, merged_oct, merged_octa, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(mem.settle(s));
     return OCTMC_OK;
 }
 

@@ -109,6 +109,7 @@ int register_impl(octmc_pair* pair, float* disp_out, float* merged_oct, float* m
 int merge_impl(octmc_pair* pair, const float* disp, float* merged_oct, float* merged_octa, hipStream_t s,
                Slab* slab);
 int ctx_device(const octmc_ctx* ctx);
+void ctx_trim(octmc_ctx* ctx);  // gives the idle device blocks of its device back
 
 constexpr int kMaxJobs = 8;     // jobs (pairs) per grouped launch
 

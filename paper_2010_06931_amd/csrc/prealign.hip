@@ -25,19 +25,12 @@
 namespace octmc {
 namespace {
 
-struct DevMem {
-    std::vector<void*> p;
-    ~DevMem()
-    {
-        for (void* q : p) (void)hipFree(q);
-    }
+struct DevMem : Blocks {
+    using Blocks::Blocks;
     template <typename T>
     T* get(size_t n)
     {
-        void* q = nullptr;
-        if (hipMalloc(&q, n * sizeof(T) ? n * sizeof(T) : 16) != hipSuccess) return nullptr;
-        p.push_back(q);
-        return static_cast<T*>(q);
+        return static_cast<T*>(Blocks::get(n * sizeof(T)));
     }
 };
 
@@ -101,13 +94,17 @@ struct StageEvaluator final : Evaluator {
 // vectors, sized for the finest level.
 struct StageMem {
     DevMem mem;
+    double *h_terms = nullptr, *h_dots = nullptr;  // pinned
     Solver sv;
     double* terms_d = nullptr;
     double* T_d = nullptr;
     float* disp = nullptr;
     float* grad = nullptr;
+    explicit StageMem(std::shared_ptr<BlockCache> c) : mem(std::move(c)) {}
     int alloc(size_t na, size_t nth, int m)
     {
+        h_terms = mem.get_host(OCTMC_NTERMS);
+        h_dots = mem.get_host(kMaxDots + 1);
         terms_d = mem.get<double>(OCTMC_NTERMS);
         T_d = mem.get<double>(1);
         disp = mem.get<float>(2 * na * 3);
@@ -115,7 +112,7 @@ struct StageMem {
         sv.m = m;
         double** vecs[] = {&sv.x, &sv.g, &sv.p, &sv.xt, &sv.xprev, &sv.sc, &sv.yc, &sv.gt};
         for (double** v : vecs) *v = mem.get<double>(nth);
-        bool ok = terms_d && T_d && disp && grad;
+        bool ok = h_terms && h_dots && terms_d && T_d && disp && grad;
         for (double** v : vecs) ok = ok && *v;
         for (int k = 0; k < m; ++k) {
             sv.S[k] = mem.get<double>(nth);
@@ -125,22 +122,6 @@ struct StageMem {
         sv.xt32 = mem.get<float>(nth);
         ok = ok && sv.xt32;
         return ok ? OCTMC_OK : fail(OCTMC_E_OOM, "out of device memory (stage 1)");
-    }
-};
-
-struct PinnedScratch {
-    double* terms = nullptr;
-    double* dots = nullptr;
-    int alloc()
-    {
-        HIP_TRY(hipHostMalloc(&terms, OCTMC_NTERMS * 8, hipHostMallocDefault));
-        HIP_TRY(hipHostMalloc(&dots, (kMaxDots + 1) * 8, hipHostMallocDefault));
-        return OCTMC_OK;
-    }
-    ~PinnedScratch()
-    {
-        if (terms) (void)hipHostFree(terms);
-        if (dots) (void)hipHostFree(dots);
     }
 };
 
@@ -162,10 +143,8 @@ int prealign_solve(octmc_pair* pair, double gamma, int iters, std::vector<double
     const size_t na0 = (size_t)w0 * h0, nth0 = 2 * (size_t)(w0 + h0);
     octmc_params pr = pair_params(pair);
     pr.iters_per_level = iters;
-    StageMem sm;
+    StageMem sm(pair->ctx->cache);
     OCTMC_TRY(sm.alloc(na0, nth0, pr.lbfgs_m));
-    PinnedScratch hs;
-    OCTMC_TRY(hs.alloc());
     const bool device_ls = !(pr.flags & OCTMC_HOST_LINE_SEARCH) && pr.lbfgs_m <= kLbMaxM;
     std::vector<double> th;
     int wc = 0, hc = 0;
@@ -178,7 +157,7 @@ int prealign_solve(octmc_pair* pair, double gamma, int iters, std::vector<double
         HIP_TRY(hipMemcpyAsync(sm.sv.x, th.data(), n * 8, hipMemcpyHostToDevice, s));
         sm.sv.n = n;
         StageEvaluator ev(pair, w, h, d, gamma, sm.terms_d, sm.T_d, sm.disp, sm.grad);
-        LevelRun run{pair, l, &sm.sv, s, n, hs.terms, hs.dots, &ev};
+        LevelRun run{pair, l, &sm.sv, s, n, sm.h_terms, sm.h_dots, &ev};
         LevelStats st{};
         if (device_ls)
             OCTMC_TRY(run.run_device(pr, st));
@@ -201,6 +180,7 @@ int prealign_solve(octmc_pair* pair, double gamma, int iters, std::vector<double
         hc = h;
     }
     theta = th;
+    sm.mem.idle = true;  // the last level ended with a wait for the stream
     return OCTMC_OK;
 }
 
@@ -221,7 +201,7 @@ int octmc_prealign_eval(octmc_pair* pair, int32_t level, const double* theta, do
     int w, h, d;
     OCTMC_TRY(octmc_pair_level_shape(pair, level, &w, &h, &d));
     const size_t na = (size_t)w * h, nth = 2 * (size_t)(w + h);
-    DevMem mem;
+    DevMem mem(pair->ctx->cache);
     double* th_d = mem.get<double>(nth);
     double* gth_d = mem.get<double>(nth);
     double* terms_d = mem.get<double>(2 * OCTMC_NTERMS + 1);
@@ -237,7 +217,7 @@ int octmc_prealign_eval(octmc_pair* pair, int32_t level, const double* theta, do
     std::vector<double> out(2 * OCTMC_NTERMS + 1);
     HIP_TRY(hipMemcpyAsync(out.data(), terms_d, out.size() * 8, hipMemcpyDeviceToHost, s));
     if (grad_theta) HIP_TRY(hipMemcpyAsync(grad_theta, gth_d, nth * 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(mem.settle(s));
     if (!std::isfinite(out[OCTMC_NTERMS + OCTMC_TERM_F])) return fail(OCTMC_E_NAN, "non-finite stage-1 objective");
     for (int q = 0; q < OCTMC_NTERMS; ++q) terms[q] = out[q];  // the field objective's terms, without T
     if (tilt_term_out) *tilt_term_out = out[2 * OCTMC_NTERMS];
@@ -275,12 +255,12 @@ int octmc_pair_prealignment(const octmc_pair* pair, double* theta_out, float* dz
     if (dz_out) {
         HIP_TRY(hipSetDevice(pair_device(pair)));
         hipStream_t s = static_cast<hipStream_t>(stream);
-        DevMem mem;
+        DevMem mem(pair->ctx->cache);
         double* th_d = mem.get<double>(th.size());
         if (!th_d) return fail(OCTMC_E_OOM, "out of device memory");
         HIP_TRY(hipMemcpyAsync(th_d, th.data(), th.size() * 8, hipMemcpyHostToDevice, s));
         HIP_TRY(launch_tilt_expand(th_d, w, h, nullptr, dz_out, s));
-        HIP_TRY(hipStreamSynchronize(s));  // th_d is freed on return
+        HIP_TRY(mem.settle(s));
     }
     return OCTMC_OK;
 }
@@ -297,7 +277,7 @@ int octmc_resample_axial(octmc_ctx* ctx, const octmc_shape* shape, const float* 
     if (nv * 4 >= (1ull << 31)) return fail(OCTMC_E_SHAPE, "volume larger than 2^31 bytes");
     HIP_TRY(hipSetDevice(ctx_device(ctx)));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    DevMem mem;
+    DevMem mem(ctx->cache);
     const float *v = vol, *z = dz;
     if (shape->mem == OCTMC_MEM_HOST) {
         float* q = mem.get<float>(nv + na);
@@ -308,7 +288,7 @@ int octmc_resample_axial(octmc_ctx* ctx, const octmc_shape* shape, const float* 
         z = q + nv;
     }
     HIP_TRY(launch_resample_z(v, z, na, d, out, s));
-    if (!mem.p.empty()) HIP_TRY(hipStreamSynchronize(s));  // the copies are freed on return
+    if (!mem.dev.empty()) HIP_TRY(mem.settle(s));
     return OCTMC_OK;
 }
 

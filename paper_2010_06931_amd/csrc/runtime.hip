@@ -73,14 +73,6 @@ int scratch_address(int device, void** out)
     return OCTMC_OK;
 }
 
-struct DevBuf {
-    std::vector<void*> ptrs;
-    ~DevBuf()
-    {
-        for (void* p : ptrs) (void)hipFree(p);
-    }
-};
-
 }  // namespace
 
 #include "runtime_types.h"
@@ -249,6 +241,7 @@ int octmc::pair_device(const octmc_pair* pair) { return pair->ctx->device; }
 const std::vector<double>& octmc::pair_theta(const octmc_pair* pair) { return pair->theta; }
 
 int octmc::ctx_device(const octmc_ctx* ctx) { return ctx->device; }
+void octmc::ctx_trim(octmc_ctx* ctx) { ctx->cache->trim(); }
 
 octmc_params octmc::resolve_levels(const octmc_params& p, const octmc_shape& shape)
 {
@@ -395,7 +388,7 @@ int octmc_create(int device_ordinal, octmc_ctx** out)
     HIP_TRY(hipSetDevice(device_ordinal));
     void* scr = nullptr;
     OCTMC_TRY(scratch_address(device_ordinal, &scr));
-    *out = new octmc_ctx{device_ordinal, scr};
+    *out = new octmc_ctx{device_ordinal, scr, BlockCache::of(device_ordinal)};
     return OCTMC_OK;
 }
 
@@ -422,22 +415,18 @@ int octmc::prealign_create(octmc_ctx* ctx, const octmc_params* params, const oct
     const bool host = shape->mem == OCTMC_MEM_HOST;
     const hipMemcpyKind kind = host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
     const bool have_octa = octa_x && octa_y;
-    DevBuf tmp;
-    auto dalloc = [&](size_t bytes) -> float* {
-        void* q = nullptr;
-        if (hipMalloc(&q, bytes) != hipSuccess) return nullptr;
-        tmp.ptrs.push_back(q);
-        return static_cast<float*>(q);
-    };
+    Blocks tmp(ctx->cache);
+    auto dalloc = [&](size_t bytes) { return static_cast<float*>(tmp.get(bytes)); };
     const int nvol = have_octa ? 4 : 2;
     const float* src[4] = {oct_x, oct_y, octa_x, octa_y};
-    float* in[4] = {nullptr, nullptr, nullptr, nullptr};
+    const float* in[4] = {nullptr, nullptr, nullptr, nullptr};
     float* pre[4] = {nullptr, nullptr, nullptr, nullptr};
     for (int q = 0; q < nvol; ++q) {
-        in[q] = dalloc(nv * 4);
+        float* copy = host ? dalloc(nv * 4) : nullptr;  // device inputs are read where they are
         pre[q] = dalloc(nv * 4);
-        if (!in[q] || !pre[q]) return fail(OCTMC_E_OOM, "out of device memory (prealignment)");
-        HIP_TRY(hipMemcpyAsync(in[q], src[q], nv * 4, kind, s));
+        if ((host && !copy) || !pre[q]) return fail(OCTMC_E_OOM, "out of device memory (prealignment)");
+        if (host) HIP_TRY(hipMemcpyAsync(copy, src[q], nv * 4, kind, s));
+        in[q] = host ? copy : src[q];
     }
     float* zero = dalloc(na * 4);
     float* dz = dalloc(2 * na * 4);
@@ -456,6 +445,7 @@ int octmc::prealign_create(octmc_ctx* ctx, const octmc_params* params, const oct
                                    nullptr, &P1));
         std::unique_ptr<octmc_pair> g1(P1);
         OCTMC_TRY(prealign_solve(P1, params->gamma_tilt, params->prealign_iters, th, nullptr, s));
+        HIP_TRY(P1->mem.settle(s));
     }
     HIP_TRY(hipMemcpyAsync(th_d, th.data(), th.size() * 8, hipMemcpyHostToDevice, s));
     HIP_TRY(launch_tilt_expand(th_d, w, h, nullptr, dz, s));
@@ -485,6 +475,7 @@ int octmc::prealign_create(octmc_ctx* ctx, const octmc_params* params, const oct
                                have_octa ? pre[3] : nullptr, enf[0], enf[1], val[0], val[1], s, nullptr, &P));
     P->theta = th;
     *out = P;
+    tmp.idle = true;  // pair_create_impl has waited for the stream
     return OCTMC_OK;
 }
 
@@ -518,25 +509,27 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
     std::unique_ptr<octmc_pair> guard(P);
     P->slab = slab;
     P->ctx = ctx;
+    P->mem.cache = ctx->cache;
     P->params = *params;
     P->dtype = shape->dtype;
     P->nlev = params->levels;
     const size_t na = (size_t)w * h, nv = na * d;
     const bool host = shape->mem == OCTMC_MEM_HOST;
     const hipMemcpyKind kind = host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-    DevBuf tmp;
+    Blocks tmp(ctx->cache);
     auto talloc = [&](size_t bytes) -> void* {
-        void* q = nullptr;
-        if (slab) return slab->take(bytes);  // temporaries stay in the slab until the pair is released
-        if (hipMalloc(&q, bytes) != hipSuccess) return nullptr;
-        tmp.ptrs.push_back(q);
-        return q;
+        // temporaries stay in the slab until the pair is released
+        return slab ? slab->take(bytes) : tmp.get(bytes);
     };
-    // float32 copies of the inputs
-    float* f32[2] = {(float*)talloc(nv * 4), (float*)talloc(nv * 4)};
-    if (!f32[0] || !f32[1]) return fail(OCTMC_E_OOM, "out of device memory (input staging)");
-    HIP_TRY(hipMemcpyAsync(f32[0], oct_x, nv * 4, kind, s));
-    HIP_TRY(hipMemcpyAsync(f32[1], oct_y, nv * 4, kind, s));
+    // the structural inputs on the device: those that are there are only read,
+    // and this call returns after its last reader
+    const float* f32[2] = {oct_x, oct_y};
+    for (int V = 0; host && V < 2; ++V) {
+        float* copy = (float*)talloc(nv * 4);
+        if (!copy) return fail(OCTMC_E_OOM, "out of device memory (input staging)");
+        HIP_TRY(hipMemcpyAsync(copy, f32[V], nv * 4, kind, s));
+        f32[V] = copy;
+    }
     std::vector<float> hvx(h, 1.0f), hvy(w, 1.0f);
     if (valid_x) {
         HIP_TRY(hipMemcpyAsync(hvx.data(), valid_x, h * 4, host ? hipMemcpyHostToHost : hipMemcpyDeviceToHost, s));
@@ -618,7 +611,7 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
         HIP_TRY(hipMemcpyAsync(enf[1], enface_y, na * 4, kind, s));
     }
     // pyramid: float32 at every level, stored in the storage type
-    float* cur[2] = {f32[0], f32[1]};
+    const float* cur[2] = {f32[0], f32[1]};
     float* cen[2] = {enf[0], enf[1]};
     float *cvx = nullptr, *cvy = nullptr;
     HIP_TRY(P->alloc(&cvx, h * 4));
@@ -678,7 +671,7 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
         }
     }
     OCTMC_TRY(pair_alloc_scratch(P, na, s));
-    HIP_TRY(hipStreamSynchronize(s));  // temporaries are freed on return
+    HIP_TRY(tmp.settle(s));
     *out = guard.release();
     return OCTMC_OK;
 }
@@ -709,20 +702,18 @@ int octmc_validity_from_octa(octmc_ctx* ctx, const octmc_shape* shape, const flo
     if (nv * 4 >= (1ull << 31)) return fail(OCTMC_E_SHAPE, "volume larger than 2^31 bytes");
     HIP_TRY(hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    DevBuf tmp;
+    Blocks tmp(ctx->cache);
     const float* vol = octa;
     if (shape->mem == OCTMC_MEM_HOST) {
-        void* q = nullptr;
-        HIP_TRY(hipMalloc(&q, nv * 4));
-        tmp.ptrs.push_back(q);
+        void* q = tmp.get(nv * 4);
+        HIP_TRY(q ? hipSuccess : tmp.err);
         HIP_TRY(hipMemcpyAsync(q, octa, nv * 4, hipMemcpyHostToDevice, s));
         vol = static_cast<const float*>(q);
     }
-    void* means = nullptr;
-    HIP_TRY(hipMalloc(&means, (size_t)(scan == 0 ? h : w) * 8));
-    tmp.ptrs.push_back(means);
+    void* means = tmp.get((size_t)(scan == 0 ? h : w) * 8);
+    HIP_TRY(means ? hipSuccess : tmp.err);
     HIP_TRY(launch_validity(vol, w, h, d, scan, static_cast<double*>(means), valid_out, s));
-    HIP_TRY(hipStreamSynchronize(s));  // the temporaries are freed on return
+    HIP_TRY(tmp.settle(s));
     return OCTMC_OK;
 }
 
@@ -751,13 +742,8 @@ int octmc_enface_project(octmc_ctx* ctx, const octmc_shape* shape, const float* 
     if (fixed && !(fixed[0] == fixed[0] && fixed[1] == fixed[1])) return fail(OCTMC_E_INVALID, "fixed mapping is NaN");
     HIP_TRY(hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    DevBuf tmp;
-    auto dalloc = [&](size_t bytes) -> void* {
-        void* q = nullptr;
-        if (hipMalloc(&q, bytes) != hipSuccess) return nullptr;
-        tmp.ptrs.push_back(q);
-        return q;
-    };
+    Blocks tmp(ctx->cache);
+    auto dalloc = [&](size_t bytes) { return tmp.get(bytes); };
     if (workspace && workspace_bytes < enface_scratch_bytes(w, h, d))
         return fail(OCTMC_E_INVALID, "workspace smaller than octmc_enface_workspace_size");
     void* scratch = workspace ? workspace : dalloc(enface_scratch_bytes(w, h, d));
@@ -776,7 +762,7 @@ int octmc_enface_project(octmc_ctx* ctx, const octmc_shape* shape, const float* 
         }
     }
     HIP_TRY(launch_enface_project(o, a, w, h, d, scan, v, fixed, enface_out, count_out, stats_out, scratch, s));
-    if (!tmp.ptrs.empty() || stats_out) HIP_TRY(hipStreamSynchronize(s));  // temporaries are freed on return
+    if (!tmp.dev.empty() || stats_out) HIP_TRY(tmp.settle(s));
     return OCTMC_OK;
 }
 
@@ -784,7 +770,7 @@ int octmc_pair_destroy(octmc_pair* pair)
 {
     if (pair && !pair->slab) {  // a slab's owner orders its release after the pair's work
         (void)hipSetDevice(pair->ctx->device);
-        (void)hipDeviceSynchronize();
+        pair->mem.idle = hipDeviceSynchronize() == hipSuccess;
     }
     delete pair;
     return OCTMC_OK;
@@ -923,7 +909,7 @@ int octmc::merge_impl(octmc_pair* pair, const float* disp, float* merged_oct, fl
     if (merged_octa && !pair->octa[0]) return fail(OCTMC_E_INVALID, "no OCTA volumes were given at creation");
     HIP_TRY(hipSetDevice(pair->ctx->device));
     const Level& L = pair->lev[0];
-    DevBuf tmp;
+    Blocks tmp(pair->ctx->cache);
     unsigned long long* grid = nullptr;
     float4* wts = nullptr;
     if (slab) {
@@ -931,10 +917,9 @@ int octmc::merge_impl(octmc_pair* pair, const float* disp, float* merged_oct, fl
         wts = static_cast<float4*>(slab->take((size_t)L.na * 16));
         if (!grid || !wts) return fail(OCTMC_E_OOM, "slab exhausted (merge)");
     } else {
-        HIP_TRY(hipMalloc(&grid, (size_t)2 * L.na * 8));
-        tmp.ptrs.push_back(grid);
-        HIP_TRY(hipMalloc(&wts, (size_t)L.na * 16));
-        tmp.ptrs.push_back(wts);
+        grid = static_cast<unsigned long long*>(tmp.get((size_t)2 * L.na * 8));
+        wts = static_cast<float4*>(tmp.get((size_t)L.na * 16));
+        HIP_TRY(grid && wts ? hipSuccess : tmp.err);
     }
     HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(grid), 0u, (size_t)4 * L.na, s));
     HIP_TRY(launch_density(disp, L.w, L.h, grid, s));
@@ -944,7 +929,7 @@ int octmc::merge_impl(octmc_pair* pair, const float* disp, float* merged_oct, fl
     if (merged_octa)
         HIP_TRY(launch_merge_volume(pair->octa[0], pair->octa[1], OCTMC_F32, disp, wts, 1, L.w, L.h, L.d, L.d,
                                     merged_octa, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(tmp.settle(s));
     return OCTMC_OK;
 }
 
@@ -966,15 +951,15 @@ int octmc::register_impl(octmc_pair* pair, float* disp_out, float* merged_oct, f
     const size_t n0 = (size_t)6 * pair->lev[0].na;
     Solver sv;
     sv.m = pr.lbfgs_m;
-    DevBuf mem;
+    Blocks mem(pair->ctx->cache);
     auto dalloc = [&](double** p) -> int {
         if (slab) {
             *p = static_cast<double*>(slab->take(n0 * 8));
             if (!*p) return fail(OCTMC_E_OOM, "slab exhausted (solver)");
             return OCTMC_OK;
         }
-        HIP_TRY(hipMalloc(p, n0 * 8));
-        mem.ptrs.push_back(*p);
+        *p = static_cast<double*>(mem.get(n0 * 8));
+        HIP_TRY(*p ? hipSuccess : mem.err);
         return OCTMC_OK;
     };
     OCTMC_TRY(dalloc(&sv.x));
@@ -993,26 +978,13 @@ int octmc::register_impl(octmc_pair* pair, float* disp_out, float* merged_oct, f
         sv.xt32 = static_cast<float*>(slab->take(n0 * 4));
         if (!sv.xt32) return fail(OCTMC_E_OOM, "slab exhausted (solver)");
     } else {
-        HIP_TRY(hipMalloc(&sv.xt32, n0 * 4));
-        mem.ptrs.push_back(sv.xt32);
+        sv.xt32 = static_cast<float*>(mem.get(n0 * 4));
+        HIP_TRY(sv.xt32 ? hipSuccess : mem.err);
     }
     double *h_terms = h_terms_in, *h_dots = h_dots_in;
-    struct HostFree {
-        double *a = nullptr, *b = nullptr;
-        ~HostFree()
-        {
-            if (a) (void)hipHostFree(a);
-            if (b) (void)hipHostFree(b);
-        }
-    } hf;
-    if (!h_terms) {
-        HIP_TRY(hipHostMalloc(&h_terms, OCTMC_NTERMS * 8, hipHostMallocDefault));
-        hf.a = h_terms;
-    }
-    if (!h_dots) {
-        HIP_TRY(hipHostMalloc(&h_dots, (kMaxDots + 1) * 8, hipHostMallocDefault));
-        hf.b = h_dots;
-    }
+    if (!h_terms) h_terms = mem.get_host(OCTMC_NTERMS);
+    if (!h_dots) h_dots = mem.get_host(kMaxDots + 1);
+    HIP_TRY(h_terms && h_dots ? hipSuccess : mem.err);
     if (rep) {
         std::memset(rep, 0, sizeof(*rep));
         rep->nlevels = pair->nlev;
@@ -1051,7 +1023,7 @@ int octmc::register_impl(octmc_pair* pair, float* disp_out, float* merged_oct, f
     }
     HIP_TRY(launch_to_f32(sv.x, disp_out, n0, s));
     if (merged_oct) OCTMC_TRY(merge_impl(pair, disp_out, merged_oct, merged_octa, s, slab));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(mem.settle(s));
     return OCTMC_OK;
 }
 

@@ -11,6 +11,7 @@
 #include <deque>
 #include <vector>
 
+#include "block_cache.h"
 #include "octmc_internal.h"
 
 struct octmc_ctx {
@@ -18,6 +19,7 @@ struct octmc_ctx {
     // device address of the evaluation scratch of octmc_eval_noalloc (the
     // file-scope array of runtime.hip on this device), resolved at creation
     void* noalloc_scratch = nullptr;
+    std::shared_ptr<octmc::BlockCache> cache;  // device blocks of the objects and calls on this device
 };
 
 namespace octmc {
@@ -72,7 +74,7 @@ struct octmc_pair {
     double* dot_blk = nullptr;  // [512][kMaxDots + 1]
     double* dot_out = nullptr;  // [kMaxDots + 1]
     octmc::LbState* lb = nullptr;  // the device solver's state (LevelRun::run_device)
-    std::vector<void*> owned;
+    octmc::Blocks mem;
     octmc::Slab* slab = nullptr;  // when set, all device memory comes from it
     std::atomic<int> busy{0};  // a solve holds the pair (taken by compare-and-swap)
     std::vector<double> theta;  // stage-1 offsets and tilts (created with OCTMC_PREALIGN)
@@ -90,16 +92,10 @@ struct octmc_pair {
             *p = static_cast<T*>(q);
             return hipSuccess;
         }
-        hipError_t e = hipMalloc(&q, bytes ? bytes : 16);
-        if (e == hipSuccess) {
-            owned.push_back(q);
-            *p = static_cast<T*>(q);
-        }
-        return e;
-    }
-    ~octmc_pair()
-    {
-        for (void* p : owned) (void)hipFree(p);
+        q = mem.get(bytes);
+        if (!q) return mem.err;
+        *p = static_cast<T*>(q);
+        return hipSuccess;
     }
 };
 

@@ -393,7 +393,11 @@ int octmc_server_create(octmc_ctx* ctx, uint64_t hbm_budget_bytes, int32_t max_a
     HIP_TRY(hipSetDevice(S->device));
     S->budget = (size_t)hbm_budget_bytes & ~(size_t)255;
     void* mem = nullptr;
-    HIP_TRY(hipMalloc(&mem, S->budget));
+    if (hipMalloc(&mem, S->budget) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx_trim(ctx);  // the device's idle blocks make room
+        HIP_TRY(hipMalloc(&mem, S->budget));
+    }
     S->base = static_cast<char*>(mem);
     S->arena.reset(S->budget);
     for (int q = 0; q < 2; ++q) {
