@@ -3,9 +3,9 @@
 // Volumes are [h][w][d] float32 in the common frame (depth contiguous).  The
 // fast scan axis is x for the X-fast scan (V = 0) and y for the Y-fast scan
 // (V = 1); B-scans are rows j (V = 0) or columns i (V = 1).  Steps:
-//   k_median3      3-D median of radius 1 (clamped borders)
-//   k_rank15       width-15 rank filter keeping the 3rd smallest value, along
-//                  one lateral axis (run for the fast, then the slow axis)
+//   k_median_rank  3-D median of radius 1 (clamped borders) and the width-15 rank
+//                  filter keeping the 3rd smallest value along the fast axis
+//   k_rank15       the same rank filter along the slow axis
 //   k_radix_hist   three radix passes (11, 11, 10 bits; the first counted by
 //   k_radix_select the slow-axis rank filter) that select the two order
 //                  statistics on each side of the 5th and 95th percentile
@@ -27,7 +27,6 @@ namespace octmc {
 namespace {
 
 constexpr int kMedTile = 62;   // depth outputs per wave (64 lanes, one halo lane each side)
-constexpr int kMedSeg = 30;    // x positions per wave, a multiple of 3
 constexpr int kHistBins = 2048;
 constexpr int kHistBlocks = 2048;
 constexpr int kNoiseBlocks = 2048;
@@ -61,9 +60,9 @@ __device__ __forceinline__ void ce(float& a, float& b)
 // ---------------------------------------------------------------------------
 // 3-D median of radius 1.
 //
-// A wave owns one row j, 64 consecutive depths (62 outputs) and kMedSeg
-// consecutive x positions, which it walks in order.  For each x it sorts the
-// nine samples of the (j, k) plane at that x: the three rows j-1..j+1 are
+// A wave owns one line, 64 consecutive depths (62 outputs) and consecutive
+// positions x along the fast axis, which it walks in order.  For each x it sorts
+// the nine samples of the (line, k) plane at that x: the three lines j-1..j+1 are
 // loaded and sorted per lane, the neighbours k-1 and k+1 come from the
 // adjacent lanes, the three rank rows are sorted across k, and three more
 // 3-sorts complete the order of this rows-and-columns-sorted 3 x 3 grid.
@@ -80,11 +79,8 @@ struct Plane {
     float v[9];
 };
 
-__device__ __forceinline__ Plane sorted_plane(const float* __restrict__ in, size_t rm, size_t r0, size_t rp, int x,
-                                              int w, int d, int k)
+__device__ __forceinline__ Plane sorted_plane(float a, float b, float c)
 {
-    x = x < 0 ? 0 : (x >= w ? w - 1 : x);
-    float a = in[(rm + x) * d + k], b = in[(r0 + x) * d + k], c = in[(rp + x) * d + k];
     sort3(a, b, c);
     Plane p;
     p.v[0] = shr1(a);
@@ -128,35 +124,6 @@ __device__ __forceinline__ float median27(const Plane& A, const Plane& B, const 
     return __builtin_fminf(min3f(t, __builtin_fmaxf(x[4], y[1]), __builtin_fmaxf(x[5], y[0])), x[6]);
 }
 
-__global__ __launch_bounds__(256) void k_median3(const float* __restrict__ in, float* __restrict__ out, int w, int h,
-                                                 int d)
-{
-    const int lane = threadIdx.x & 63;
-    const int j = blockIdx.z * 4 + (threadIdx.x >> 6);
-    if (j >= h) return;  // uniform per wave; no barrier in this kernel
-    const int kk = blockIdx.x * kMedTile - 1 + lane;
-    const int k = kk < 0 ? 0 : (kk >= d ? d - 1 : kk);
-    const bool store = lane >= 1 && lane <= kMedTile && kk < d;
-    const int x0 = blockIdx.y * kMedSeg, x1 = min(x0 + kMedSeg, w);
-    const size_t rm = (size_t)max(j - 1, 0) * w, r0 = (size_t)j * w, rp = (size_t)min(j + 1, h - 1) * w;
-    Plane A = sorted_plane(in, rm, r0, rp, x0 - 1, w, d, k);
-    Plane B = sorted_plane(in, rm, r0, rp, x0, w, d, k);
-    for (int x = x0; x < x1; x += 3) {  // the three planes rotate roles
-        Plane C = sorted_plane(in, rm, r0, rp, x + 1, w, d, k);
-        float r = median27(A, B, C);
-        if (store) out[(r0 + x) * d + kk] = r;
-        if (x + 1 >= x1) break;
-        A = sorted_plane(in, rm, r0, rp, x + 2, w, d, k);
-        r = median27(B, C, A);
-        if (store) out[(r0 + x + 1) * d + kk] = r;
-        if (x + 2 >= x1) break;
-        B = sorted_plane(in, rm, r0, rp, x + 3, w, d, k);
-        r = median27(C, A, B);
-        if (store) out[(r0 + x + 2) * d + kk] = r;
-        // A and B now hold the planes of x + 2 and x + 3, as the next step needs
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Order statistics by radix selection on the order-preserving integer image
 // of the float values.  State lives in device memory so that the passes run
@@ -189,7 +156,7 @@ __device__ __forceinline__ float from_key(unsigned k)
 // Rank filter: the 3rd smallest of the 15 samples p-7 .. p+7 along one
 // lateral axis, clamped at the ends.
 //
-// A wave owns 64 consecutive depths of one line and a segment of kRankSeg
+// A wave owns 64 consecutive depths of one line and a segment of `len`
 // positions, which it walks in chunks of 15 aligned so that chunk c spans
 // p0-7+15c .. p0+7+15c.  The window of output p = p0+15c+t is the tail of
 // chunk c from offset t joined with the head of chunk c+1 up to offset t-1:
@@ -203,8 +170,11 @@ __device__ __forceinline__ float from_key(unsigned k)
 // kernel also counts bits 31..21 of every output of a valid B-scan: the
 // first radix pass of the percentile selection.  Along the walk a lane's
 // outputs change bin rarely, so each lane adds runs of equal bins.
-constexpr int kRankSeg = 120;  // a multiple of 15
-
+//
+// Neighbouring waves take neighbouring depths, then neighbouring lines: an
+// A-scan's rows are no whole cache lines, and waves that share one then run
+// together (500 x 500 x 465: 325 us with the segments of a line side by side,
+// 291 us so; 930 MB are read and written).
 struct Tri {
     float a, b, c;
 };
@@ -217,9 +187,98 @@ __device__ __forceinline__ float third_of_union(Tri s, Tri p)
     return min3f(__builtin_fminf(s.c, p.c), __builtin_fmaxf(s.a, p.b), __builtin_fmaxf(s.b, p.a));
 }
 
+// The suffix triples of a chunk.
+__device__ __forceinline__ void suffixes(const float (&u)[15], Tri (&s)[15])
+{
+    constexpr float inf = __builtin_inff();
+    s[14] = Tri{u[14], inf, inf};
+#pragma unroll
+    for (int t = 13; t >= 0; --t) s[t] = insert(s[t + 1], u[t]);
+}
+
+// Median and fast-axis rank filter in one walk: a wave owns one line, kMedTile
+// depths and `seg` positions along the fast axis (n of them, ws samples apart;
+// lines are ls apart), takes the medians in order and hands each to the rank
+// filter's chunks, so the median volume is never stored.  Bound by its 95 vector
+// instructions a position (326 us for 500 x 500 x 465 with every cycle used; 385
+// measured, 660 to 750 as two kernels); the planes are loaded three positions
+// ahead (one ahead: 468 us).
+__global__ __launch_bounds__(256, 4) void k_median_rank(const float* __restrict__ in, float* __restrict__ out, int n,
+                                                        int lines, size_t ws, size_t ls, int d, int seg)
+{
+    const int lane = threadIdx.x & 63;
+    const int o = blockIdx.z * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (o >= lines) return;  // uniform per wave; no barrier in this kernel
+    const int kk = blockIdx.x * kMedTile - 1 + lane;
+    const int k = kk < 0 ? 0 : (kk >= d ? d - 1 : kk);
+    const bool store = lane >= 1 && lane <= kMedTile && kk < d;
+    const int p0 = blockIdx.y * seg, p1 = min(p0 + seg, n);
+    const float* __restrict__ rm = in + (size_t)max(o - 1, 0) * ls;
+    const float* __restrict__ r0 = in + (size_t)o * ls;
+    const float* __restrict__ rp = in + (size_t)min(o + 1, lines - 1) * ls;
+    float* __restrict__ q = out + (size_t)o * ls;
+    float va[3], vb[3], vc[3];  // the next three planes, in flight
+    auto fetch = [&](int x, int e) {
+        const size_t at = (size_t)(x < 0 ? 0 : (x >= n ? n - 1 : x)) * ws;
+        va[e] = rm[at + k];
+        vb[e] = r0[at + k];
+        vc[e] = rp[at + k];
+    };
+    fetch(p0 - 8, 1);
+    fetch(p0 - 7, 2);
+    fetch(p0 - 6, 0);
+    Plane A = sorted_plane(va[1], vb[1], vc[1]);
+    fetch(p0 - 5, 1);
+    Plane B = sorted_plane(va[2], vb[2], vc[2]), C;
+    fetch(p0 - 4, 2);
+    float last = 0.0f;
+    // median at position r from the planes a, b of r - 1, r and the fetched one of r + 1
+    auto step = [&](int r, int e, const Plane& a, const Plane& b, Plane& c) {
+        c = sorted_plane(va[e], vb[e], vc[e]);
+        fetch(r + 4, e);
+        const float m = median27(a, b, c);
+        last = r < n ? m : last;  // positions are clamped: r >= n repeats n - 1
+        return last;
+    };
+    float u[15];
+    Tri s[15];
+#pragma unroll
+    for (int t = 0; t < 15; t += 3) {
+        const int r = p0 - 7 + t;
+        u[t] = step(r, 0, A, B, C);
+        u[t + 1] = step(r + 1, 1, B, C, A);
+        u[t + 2] = step(r + 2, 2, C, A, B);
+    }
+    if (p0 == 0) {
+#pragma unroll
+        for (int t = 0; t < 7; ++t) u[t] = u[7];  // and r < 0 is position 0
+    }
+    suffixes(u, s);
+    constexpr float inf = __builtin_inff();
+    for (int c0 = p0; c0 < p1; c0 += 15) {
+        Tri pre{inf, inf, inf};
+        auto emit = [&](int t, float v) {
+            if (c0 + t < p1) {  // uniform
+                const float r = third_of_union(s[t], pre);
+                if (store) q[(size_t)(c0 + t) * ws + kk] = r;
+            }
+            u[t] = v;
+            pre = insert(pre, v);
+        };
+#pragma unroll
+        for (int t = 0; t < 15; t += 3) {
+            const int r = c0 + 8 + t;
+            emit(t, step(r, 0, A, B, C));
+            emit(t + 1, step(r + 1, 1, B, C, A));
+            emit(t + 2, step(r + 2, 2, C, A, B));
+        }
+        suffixes(u, s);
+    }
+}
+
 template <bool kHist>
 __global__ __launch_bounds__(256) void k_rank15(const float* __restrict__ in, float* __restrict__ out, int w, int h,
-                                                int d, int axis, const float* __restrict__ valid,
+                                                int d, int axis, int len, const float* __restrict__ valid,
                                                 const SelState* __restrict__ st, unsigned* __restrict__ hist)
 {
     __shared__ unsigned lh[kHist ? kHistBins : 1];
@@ -230,16 +289,16 @@ __global__ __launch_bounds__(256) void k_rank15(const float* __restrict__ in, fl
     const int lane = threadIdx.x & 63;
     const int ktiles = (d + 63) >> 6;
     const int n = axis == 0 ? w : h;
-    const int nseg = (n + kRankSeg - 1) / kRankSeg;
+    const int nseg = (n + len - 1) / len;
     const int nlines = axis == 0 ? h : w;
     const int wid = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (wid < nlines * ktiles * nseg) {  // uniform per wave
-        const int seg = wid % nseg, rest = wid / nseg;
-        const int kt = rest % ktiles, o = rest / ktiles;
+        const int kt = wid % ktiles, rest = wid / ktiles;
+        const int o = rest % nlines, seg = rest / nlines;
         const int k = kt * 64 + lane;
         const int kc = k < d ? k : d - 1;
         const bool store = k < d;
-        const int p0 = seg * kRankSeg, p1 = min(p0 + kRankSeg, n);
+        const int p0 = seg * len, p1 = min(p0 + len, n);
         const size_t stride = axis == 0 ? (size_t)d : (size_t)w * d;
         const size_t base = (axis == 0 ? (size_t)o * w * d : (size_t)o * d) + kc;
         const float* __restrict__ p = in + base;
@@ -256,9 +315,7 @@ __global__ __launch_bounds__(256) void k_rank15(const float* __restrict__ in, fl
         Tri s[15];
 #pragma unroll
         for (int t = 0; t < 15; ++t) u[t] = ld(p0 - 7 + t);
-        s[14] = Tri{u[14], inf, inf};
-#pragma unroll
-        for (int t = 13; t >= 0; --t) s[t] = insert(s[t + 1], u[t]);
+        suffixes(u, s);
         for (int c0 = p0; c0 < p1; c0 += 15) {
 #pragma unroll
             for (int t = 0; t < 15; ++t) u[t] = ld(c0 + 8 + t);
@@ -281,9 +338,7 @@ __global__ __launch_bounds__(256) void k_rank15(const float* __restrict__ in, fl
                 }
                 pre = insert(pre, u[t]);
             }
-            s[14] = Tri{u[14], inf, inf};
-#pragma unroll
-            for (int t = 13; t >= 0; --t) s[t] = insert(s[t + 1], u[t]);
+            suffixes(u, s);
         }
         if (kHist && cur >= 0) atomicAdd(&lh[cur], run);
     }
@@ -640,6 +695,19 @@ __global__ void k_fill_ones(float* __restrict__ p, size_t n)
     if (t < n) p[t] = 1.0f;
 }
 
+// Positions of one wave's walk along an axis of n, a multiple of 15: the axis in
+// equal parts, as long as the walks reach `want` waves (the chip filled) and at
+// most `longest` (the first 15 positions of a walk are work done twice, the last
+// waves of long ones leave the chip idle), and at least 30.  Measured, median and
+// fast rank filter / slow one in us: 250 x 250 x 300, 30 long 83 / 57, 60 80 / 48,
+// 105 74 / 50 (120), 180 - / 58; 64 x 64 x 128, 30 13.6 / 13.2, 60 17.5 / 17.6, 105
+// 23 / 24; the slow one at 500 x 500 x 465, 120 347, 180 324, 255 333.
+int walk_length(int n, int lines, int want, int longest)
+{
+    const int parts = std::max((n + longest - 1) / longest, std::min((n + 29) / 30, (want + lines - 1) / lines));
+    return (n + 15 * parts - 1) / (15 * parts) * 15;
+}
+
 inline size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -680,22 +748,22 @@ hipError_t launch_enface_project(const float* oct, const float* octa, int w, int
     }
     hipLaunchKernelGGL(k_enface_init, dim3(1), dim3(256), 0, s, valid, (int)nb, from, st, hist);
     // filtering; the slow-axis pass also counts the first radix digit
-    const dim3 gm((d + kMedTile - 1) / kMedTile, (w + kMedSeg - 1) / kMedSeg, (h + 3) / 4);
-    hipLaunchKernelGGL(k_median3, gm, dim3(256), 0, s, octa, v0, w, h, d);
-    const int ktiles = (d + 63) / 64;
-    const int fast = V == 0 ? 0 : 1, slow = 1 - fast;
-    auto waves = [&](int axis) {
-        const int n = axis == 0 ? w : h, lines = axis == 0 ? h : w;
-        return lines * ktiles * ((n + kRankSeg - 1) / kRankSeg);
-    };
-    hipLaunchKernelGGL(k_rank15<false>, dim3((waves(fast) + 3) / 4), dim3(256), 0, s, v0, v1, w, h, d, fast, valid,
-                       st, hist);
+    const int fast = V == 0 ? 0 : 1, slow = 1 - fast, ktiles = (d + 63) / 64;
+    {
+        const int n = fast == 0 ? w : h, lines = fast == 0 ? h : w, mtiles = (d + kMedTile - 1) / kMedTile;
+        const size_t row = (size_t)w * d;
+        const int seg = walk_length(n, lines * mtiles, 3072, 105);
+        hipLaunchKernelGGL(k_median_rank, dim3(mtiles, (n + seg - 1) / seg, (lines + 3) / 4), dim3(256), 0, s, octa,
+                           v1, n, lines, fast == 0 ? (size_t)d : row, fast == 0 ? row : (size_t)d, d, seg);
+    }
+    const int rlen = walk_length((int)nb, (int)(na / nb) * ktiles, 6144, 180);
+    const dim3 gr(((unsigned)(na / nb) * ktiles * ((nb + rlen - 1) / rlen) + 3) / 4);
     if (fixed) {
-        hipLaunchKernelGGL(k_rank15<false>, dim3((waves(slow) + 3) / 4), dim3(256), 0, s, v1, v0, w, h, d, slow,
+        hipLaunchKernelGGL(k_rank15<false>, gr, dim3(256), 0, s, v1, v0, w, h, d, slow, rlen,
                            valid, st, hist);
         hipLaunchKernelGGL(k_set_fixed, dim3(1), dim3(1), 0, s, st, fixed[0], fixed[1]);
     } else {
-        hipLaunchKernelGGL(k_rank15<true>, dim3((waves(slow) + 3) / 4), dim3(256), 0, s, v1, v0, w, h, d, slow,
+        hipLaunchKernelGGL(k_rank15<true>, gr, dim3(256), 0, s, v1, v0, w, h, d, slow, rlen,
                            valid, st, hist);
         hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, s, hist, st, 0);
         for (int pass = 1; pass < 3; ++pass) {
