@@ -378,12 +378,95 @@ __global__ __launch_bounds__(256) void k_enface_init(const float* __restrict__ v
     }
 }
 
+// Sixteen lanes take an A-scan and a lane four consecutive samples of it at a
+// time, with one 16-byte load (4-byte alignment costs nothing), so that every
+// depth and alignment is read at the same rate; the loads of kRowLoads steps are
+// issued together.  500 x 500 x 465, one load at a time and a wave to an A-scan
+// before: a radix pass 158 -> 110 us (465 MB), the masked mean 362 -> 234 us (1.4
+// GB; 16-byte loads for whole multiples of 4 only before).  With the loads left to
+// an unrolled loop a radix pass took 193 us: the loop's remainder, one load at a
+// time, is where all of an A-scan falls.
+typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
+
+struct Quad {
+    quad_t v;
+    int first;  // the samples `first`.. 3 belong to this lane
+};
+// samples k .. k + 3 of a column of d; beyond its end, the last four from their
+// place on
+__device__ __forceinline__ Quad load_quad(const float* __restrict__ col, int k, int d)
+{
+    Quad q;
+    if (d >= 4) {  // uniform
+        const int at = k < d - 4 ? k : d - 4;
+        q.v = *reinterpret_cast<const quad_t*>(col + at);
+        q.first = k < d ? k - at : 4;
+    } else {
+        // the first d places hold nothing; their samples end at place 3
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q.v[e] = col[e - (4 - d) < 0 ? 0 : e - (4 - d)];
+        q.first = k < d ? 4 - d + k : 4;
+    }
+    return q;
+}
+constexpr int kRowLanes = 16;            // lanes of an A-scan
+constexpr int kRowStep = 4 * kRowLanes;  // samples they take at a time
+constexpr int kRowLoads = 8;             // of these steps are in flight together
+
 // Radix passes 1 and 2 over the filtered volume: pass 1 counts bits 20..10
 // of the samples whose bits 31..21 equal one of the distinct target
 // prefixes, pass 2 bits 9..0 of those whose bits 31..10 do; one histogram of
-// kHistBins counters per distinct prefix.  Few samples match, so each adds
-// its own count.  A wave walks A-scans with eight loads in flight per lane.
-// Pass 0 is counted by the slow-axis rank filter.
+// kHistBins counters per distinct prefix (kTargets of them at most).  Pass 0 is
+// counted by the slow-axis rank filter.  Prefixes and digits are taken from the
+// float's own bits, which the key inverts below zero: a prefix that is below
+// zero is compared inverted, and so is its digit.
+template <int kTargets>
+__device__ __forceinline__ void count_rows(const float* __restrict__ vol, int w, int h, int d, int V,
+                                           const float* __restrict__ valid, const SelState* __restrict__ st, int pass,
+                                           unsigned* lh)
+{
+    const unsigned any = st->any_valid, nu = st->nu;
+    const int shift = pass == 1 ? 21 : 10, dshift = pass == 1 ? 10 : 0, dbits = pass == 1 ? 11 : 10;
+    unsigned pre[kTargets], flip[kTargets];
+#pragma unroll
+    for (int t = 0; t < kTargets; ++t) {
+        const unsigned p = st->uprefix[t < (int)nu ? t : 0], top = 1u << (31 - shift);
+        pre[t] = p & top ? p ^ top : p ^ (2 * top - 1);
+        flip[t] = (unsigned)t * kHistBins | (p & top ? 0u : (1u << dbits) - 1);
+    }
+    const int part = threadIdx.x & (kRowLanes - 1);
+    const unsigned na = (unsigned)w * (unsigned)h, rows = gridDim.x * (blockDim.x / kRowLanes);
+    for (unsigned a = blockIdx.x * (blockDim.x / kRowLanes) + threadIdx.x / kRowLanes; a < na; a += rows) {
+        const unsigned j = a / (unsigned)w, i = a - j * (unsigned)w;
+        const unsigned b = V == 0 ? j : i;
+        if (any && !(valid[b] > 0.5f)) continue;
+        const float* __restrict__ col = vol + (size_t)a * d;
+        for (int k0 = 0; k0 < d; k0 += kRowLoads * kRowStep) {
+            Quad q[kRowLoads];
+#pragma unroll
+            for (int g = 0; g < kRowLoads; ++g)
+                if (k0 + g * kRowStep < d) q[g] = load_quad(col, k0 + g * kRowStep + 4 * part, d);
+#pragma unroll
+            for (int g = 0; g < kRowLoads; ++g) {
+                if (k0 + g * kRowStep >= d) break;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned u = __builtin_bit_cast(unsigned, (float)q[g].v[e]), hi = u >> shift;
+                    bool hit = hi == pre[0];
+                    unsigned f = flip[0];
+#pragma unroll
+                    for (int t = 1; t < kTargets; ++t) {
+                        const bool m = hi == pre[t];
+                        f = m && !hit ? flip[t] : f;
+                        hit |= m;
+                    }
+                    if (hit && e >= q[g].first) atomicAdd(&lh[((u >> dshift) & ((1u << dbits) - 1)) ^ f], 1u);
+                }
+            }
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_radix_hist(const float* __restrict__ vol, int w, int h, int d, int V,
                                                     const float* __restrict__ valid, const SelState* __restrict__ st,
                                                     int pass, unsigned* __restrict__ hist)
@@ -392,40 +475,10 @@ __global__ __launch_bounds__(256) void k_radix_hist(const float* __restrict__ vo
     const int nu = (int)st->nu;
     for (int t = threadIdx.x; t < nu * kHistBins; t += blockDim.x) lh[t] = 0u;
     __syncthreads();
-    const unsigned any = st->any_valid;
-    unsigned pre[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) pre[t] = t < nu ? st->uprefix[t] : 0xFFFFFFFFu;
-    const int shift = pass == 1 ? 21 : 10;
-    const unsigned dmask = pass == 1 ? 2047u : 1023u;
-    const int dshift = pass == 1 ? 10 : 0;
-    const int lane = threadIdx.x & 63;
-    const unsigned nwaves = gridDim.x * (blockDim.x >> 6);
-    const unsigned na = (unsigned)w * (unsigned)h;
-    for (unsigned a = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); a < na; a += nwaves) {
-        const unsigned j = a / (unsigned)w, i = a - j * (unsigned)w;
-        const unsigned b = V == 0 ? j : i;
-        if (any && !(valid[b] > 0.5f)) continue;  // uniform per wave
-        const float* __restrict__ col = vol + (size_t)a * d;
-        for (int k0 = 0; k0 < d; k0 += 512) {
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int kk = k0 + e * 64 + lane;
-                v[e] = kk < d ? col[kk] : 0.0f;
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if (k0 + e * 64 + lane < d) {
-                    const unsigned key = ord_key(v[e]);
-                    const unsigned hi = key >> shift;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        if (hi == pre[t]) atomicAdd(&lh[t * kHistBins + ((key >> dshift) & dmask)], 1u);
-                }
-            }
-        }
-    }
+    if (nu <= 2)  // both percentiles between neighbours of one prefix: the ordinary case
+        count_rows<2>(vol, w, h, d, V, valid, st, pass, lh);
+    else
+        count_rows<4>(vol, w, h, d, V, valid, st, pass, lh);
     __syncthreads();
     for (int t = threadIdx.x; t < nu * kHistBins; t += blockDim.x)
         if (lh[t]) atomicAdd(&hist[t], lh[t]);
@@ -596,52 +649,62 @@ __global__ __launch_bounds__(256) void k_noise_final(const double* __restrict__ 
     else st->thr_s = st->mu + 2.0 * sqrt(s / cnt);
 }
 
-// Both masks and the masked depth mean; one wave per A-scan.  kVec: four
-// depths per lane with 16-byte loads (d a multiple of 4, aligned volumes).
-template <bool kVec>
+// Sum over the sixteen lanes of an A-scan; every lane gets it.
+__device__ __forceinline__ double row_sum(double v)
+{
+#pragma unroll
+    for (int m = kRowLanes / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    return v;
+}
+__device__ __forceinline__ int row_sum(int v)
+{
+#pragma unroll
+    for (int m = kRowLanes / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    return v;
+}
+
+// Both masks and the masked depth mean.  The FP64 thresholds are compared as the
+// float32 values that part the samples alike: r < t if r < the least float not
+// below t, s > t if s > the largest not above it.
 __global__ __launch_bounds__(256) void k_mask_mean(const float* __restrict__ filt, const float* __restrict__ oct,
-                                                   const float* __restrict__ octa, size_t na, int d,
+                                                   const float* __restrict__ octa, unsigned na, int d,
                                                    const SelState* __restrict__ st, double* __restrict__ E,
                                                    int* __restrict__ cnt)
 {
-    const int lane = threadIdx.x & 63;
-    const double thr_r = st->thr_r, thr_s = st->thr_s;
-    const size_t nwaves = (size_t)gridDim.x * (blockDim.x >> 6);
-    for (size_t a = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); a < na; a += nwaves) {
-        const size_t o = a * d;
-        double acc = 0.0;
-        int c = 0;
-        if (kVec) {
-            const float4* __restrict__ r4 = reinterpret_cast<const float4*>(filt + o);
-            const float4* __restrict__ s4 = reinterpret_cast<const float4*>(oct + o);
-            const float4* __restrict__ a4 = reinterpret_cast<const float4*>(octa + o);
-            const int d4 = d >> 2;
-#pragma unroll 4
-            for (int k = lane; k < d4; k += 64) {
-                const float4 r = r4[k], s = s4[k], v = a4[k];
-                if ((double)r.x < thr_r && (double)s.x > thr_s) { acc += (double)v.x; ++c; }
-                if ((double)r.y < thr_r && (double)s.y > thr_s) { acc += (double)v.y; ++c; }
-                if ((double)r.z < thr_r && (double)s.z > thr_s) { acc += (double)v.z; ++c; }
-                if ((double)r.w < thr_r && (double)s.w > thr_s) { acc += (double)v.w; ++c; }
-            }
-        } else {
-            for (int k = lane; k < d; k += 64) {
-                const double r = filt[o + k], s = oct[o + k];
-                if (r < thr_r && s > thr_s) {
-                    acc += (double)octa[o + k];
-                    ++c;
-                }
-            }
+    const float thr_r = __double2float_ru(st->thr_r), thr_s = __double2float_rd(st->thr_s);
+    const int part = threadIdx.x & (kRowLanes - 1);
+    const unsigned a = blockIdx.x * (blockDim.x / kRowLanes) + threadIdx.x / kRowLanes;
+    if (a >= na) return;  // whole rows; the sums below stay within one
+    const size_t o = (size_t)a * d;
+    double acc = 0.0;
+    int c = 0;
+    constexpr int kLoads = kRowLoads / 2;  // of three volumes each
+    for (int k0 = 0; k0 < d; k0 += kLoads * kRowStep) {
+        Quad r[kLoads], s[kLoads], v[kLoads];
+#pragma unroll
+        for (int g = 0; g < kLoads; ++g) {
+            const int k = k0 + g * kRowStep;
+            if (k >= d) break;
+            r[g] = load_quad(filt + o, k + 4 * part, d);
+            s[g] = load_quad(oct + o, k + 4 * part, d);
+            v[g] = load_quad(octa + o, k + 4 * part, d);
         }
 #pragma unroll
-        for (int m = 32; m > 0; m >>= 1) {
-            acc += __shfl_xor(acc, m);
-            c += __shfl_xor(c, m);
+        for (int g = 0; g < kLoads; ++g) {
+            if (k0 + g * kRowStep >= d) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool m = e >= r[g].first && r[g].v[e] < thr_r && s[g].v[e] > thr_s;
+                acc += (double)(m ? v[g].v[e] : 0.0f);
+                c += m;
+            }
         }
-        if (lane == 0) {
-            E[a] = c ? acc / c : 0.0;
-            if (cnt) cnt[a] = c;
-        }
+    }
+    acc = row_sum(acc);
+    c = row_sum(c);
+    if (part == 0) {
+        E[a] = c ? acc / c : 0.0;
+        if (cnt) cnt[a] = c;
     }
 }
 
@@ -708,6 +771,17 @@ int walk_length(int n, int lines, int want, int longest)
     return (n + 15 * parts - 1) / (15 * parts) * 15;
 }
 
+// Blocks of a radix pass: each clears and adds its histograms, so four A-scans a
+// row of lanes if that leaves a block per CU.  Measured with 1 / 2 / 4 / 8: 62 500
+// A-scans of 300 35 / 34 / 25 / 28 us, 14 400 of 200 15 / 12 / 12 / 16, 4096 of
+// 128 6.2 / 6.3 / 7.8 / 12.4.
+unsigned hist_blocks(size_t na)
+{
+    constexpr size_t rows = 256 / kRowLanes;
+    const size_t most = std::min<size_t>((na + rows - 1) / rows, kHistBlocks);
+    return (unsigned)std::min(std::max<size_t>(na / (4 * rows), 256), most);
+}
+
 inline size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -767,7 +841,7 @@ hipError_t launch_enface_project(const float* oct, const float* octa, int w, int
                            valid, st, hist);
         hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, s, hist, st, 0);
         for (int pass = 1; pass < 3; ++pass) {
-            hipLaunchKernelGGL(k_radix_hist, dim3(kHistBlocks), dim3(256), 0, s, v0, w, h, d, V, valid, st, pass,
+            hipLaunchKernelGGL(k_radix_hist, dim3(hist_blocks(na)), dim3(256), 0, s, v0, w, h, d, V, valid, st, pass,
                                hist);
             hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, s, hist, st, pass);
         }
@@ -779,12 +853,8 @@ hipError_t launch_enface_project(const float* oct, const float* octa, int w, int
         hipLaunchKernelGGL(k_noise_final, dim3(1), dim3(256), 0, s, part, kNoiseBlocks, (double)na * nz, pass, st);
     }
     // masks, depth mean, B-scan median, substitution
-    const bool vec = (d & 3) == 0 && ((uintptr_t)oct & 15) == 0 && ((uintptr_t)octa & 15) == 0;
-    const dim3 gmm((unsigned)std::min<size_t>((na + 3) / 4, 65536));
-    if (vec)
-        hipLaunchKernelGGL(k_mask_mean<true>, gmm, dim3(256), 0, s, v0, oct, octa, na, d, st, E, count ? count : cnt);
-    else
-        hipLaunchKernelGGL(k_mask_mean<false>, gmm, dim3(256), 0, s, v0, oct, octa, na, d, st, E, count ? count : cnt);
+    hipLaunchKernelGGL(k_mask_mean, dim3((unsigned)((na + 15) / 16)), dim3(256), 0, s, v0, oct, octa, (unsigned)na, d,
+                       st, E, count ? count : cnt);
     hipLaunchKernelGGL(k_bscan_median, dim3((unsigned)nb), dim3(512), 0, s, E, w, h, V, med);
     hipLaunchKernelGGL(k_enface_finish, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, E, med, from, w, h, V,
                        out);

@@ -1,6 +1,7 @@
 """The walks of the en face filters against the FP64 oracle, voxel counts exactly,
 at the lengths where a walk ends or begins: positions around its chunks of 15 and
-its segments, depths around its tiles of 62 and 64 samples, one and two lines."""
+its segments, depths around its tiles of 62 and 64 samples, one and two lines,
+and so few samples that the order statistics have prefixes of their own."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,8 @@ TOL = 1e-6  # float32 results of float64 means and medians of exactly selected s
 
 
 @pytest.mark.parametrize("shape", [(2, 7, 61), (3, 8, 62), (9, 15, 63), (8, 16, 64), (16, 30, 124), (17, 31, 125),
-                                   (45, 46, 2), (61, 60, 1), (3100, 105, 2), (1600, 215, 1), (106, 3100, 3)])
+                                   (45, 46, 2), (61, 60, 1), (3100, 105, 2), (1600, 215, 1), (106, 3100, 3),
+                                   (1, 1, 21), (1, 2, 40)])
 def test_filters_at_the_ends_of_their_walks(shape):
     import paper_2010_06931_amd as octmc
     h, w, d = shape
