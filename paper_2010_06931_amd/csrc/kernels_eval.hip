@@ -847,21 +847,54 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
 // ---------------------------------------------------------------------------
 // deterministic block reduction helpers
 
+// Sums of N (4 or 8) values over a wave by halving: at each step a lane keeps
+// half of its values and gives the other half to its partner, so N - 1 + log2(64
+// / N) exchanges do.  Lane l is left with the sum of value l / (64 / N).
 template <int N>
-__device__ __forceinline__ void block_reduce_store(double (&v)[N], double* blk_row)
+__device__ __forceinline__ double wave_sums(const double (&in)[N], int lane)
 {
-    __shared__ double sh[N][kRedBlock];
+    double v[N];
 #pragma unroll
-    for (int q = 0; q < N; ++q) sh[q][threadIdx.x] = v[q];
-    __syncthreads();
-    for (int s = kRedBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
+    for (int q = 0; q < N; ++q) v[q] = in[q];
+    int m = 32;
 #pragma unroll
-            for (int q = 0; q < N; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + s];
+    for (int half = N / 2; half > 0; half >>= 1, m >>= 1) {
+#pragma unroll
+        for (int q = 0; q < half; ++q) {
+            const bool up = lane & m;
+            const double give = up ? v[q] : v[q + half], keep = up ? v[q + half] : v[q];
+            v[q] = keep + __shfl_xor(give, m);
         }
-        __syncthreads();
     }
-    if ((int)threadIdx.x < N) blk_row[threadIdx.x] = sh[threadIdx.x][0];
+    for (; m > 0; m >>= 1) v[0] += __shfl_xor(v[0], m);
+    return v[0];
+}
+
+// The waves' sums, one row per wave; after the next barrier wave_rows adds them
+// in order.
+template <int N>
+__device__ __forceinline__ void store_wave_sums(const double (&v)[N], double (&sh)[kRedBlock / 64][N])
+{
+    const int lane = threadIdx.x & 63;
+    const double s = wave_sums<N>(v, lane);
+    if (lane % (64 / N) == 0) sh[threadIdx.x >> 6][lane / (64 / N)] = s;
+}
+template <int N>
+__device__ __forceinline__ double wave_rows(const double (&sh)[kRedBlock / 64][N], int q)
+{
+    double s = sh[0][q];
+#pragma unroll
+    for (int r = 1; r < kRedBlock / 64; ++r) s += sh[r][q];
+    return s;
+}
+
+template <int N>
+__device__ __forceinline__ void block_reduce_store(const double (&v)[N], double* blk_row)
+{
+    __shared__ double sh[kRedBlock / 64][N];
+    store_wave_sums<N>(v, sh);
+    __syncthreads();
+    if ((int)threadIdx.x < N) blk_row[threadIdx.x] = wave_rows<N>(sh, threadIdx.x);
 }
 
 // Fixed-order sum of the rows of block partials (strided per thread, then a
@@ -870,7 +903,7 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[N], double* blk_r
 template <int N>
 __device__ __forceinline__ void sum_rows(const double* blk, int nblk, double (&out)[N])
 {
-    __shared__ double sh[N][kRedBlock];
+    __shared__ double sh[kRedBlock / 64][N];
     double acc[N];
 #pragma unroll
     for (int q = 0; q < N; ++q) acc[q] = 0.0;
@@ -878,18 +911,10 @@ __device__ __forceinline__ void sum_rows(const double* blk, int nblk, double (&o
 #pragma unroll
         for (int q = 0; q < N; ++q) acc[q] += blk[(size_t)r * N + q];
     }
-#pragma unroll
-    for (int q = 0; q < N; ++q) sh[q][threadIdx.x] = acc[q];
+    store_wave_sums<N>(acc, sh);
     __syncthreads();
-    for (int s = kRedBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
 #pragma unroll
-            for (int q = 0; q < N; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int q = 0; q < N; ++q) out[q] = sh[q][0];
+    for (int q = 0; q < N; ++q) out[q] = wave_rows<N>(sh, q);
 }
 
 // ---------------------------------------------------------------------------
@@ -913,10 +938,10 @@ __global__ __launch_bounds__(kRedBlock) void k_sum(const SumJobs jobs)
     block_reduce_store<4>(v, J.blk + (size_t)b * 4);
 }
 
-// pseudo-Huber in float64 (regulariser and en face terms)
-__device__ __forceinline__ void huber_d(double x, double eps, double& L, double& dL)
+// pseudo-Huber in float64 (regulariser and en face terms); ieps = 1 / eps
+__device__ __forceinline__ void huber_d(double x, double eps, double ieps, double& L, double& dL)
 {
-    const double u = x / eps;
+    const double u = x * ieps;
     const double s = sqrt(1.0 + u * u);
     L = eps * u * u / (s + 1.0);
     dL = u / s;
@@ -1027,7 +1052,7 @@ __global__ __launch_bounds__(kRedBlock) void k_combine(const CombineJobs jobs)
         sample2(J.ax, w, h, i, j, dX[0], dX[1], jx);
         sample2(J.ay, w, h, i, j, dY[0], dY[1], jy);
         double LA, GA;
-        huber_d((double)jx[0] - (double)jy[0], J.eps_h, LA, GA);
+        huber_d((double)jx[0] - (double)jy[0], J.eps_h, J.ieps_h, LA, GA);
         // validity (Eq. 5) varies along each scan's slow axis: y for an X-fast
         // scan (index j, component dy), x for a Y-fast scan
         const int oX = J.orient & 1, oY = (J.orient >> 1) & 1;
@@ -1073,11 +1098,11 @@ __global__ __launch_bounds__(kRedBlock) void k_combine(const CombineJobs jobs)
                 for (int c = 0; c < 3; ++c) {
                     double Lr, dLr;
                     if (pa >= 0) {
-                        huber_d((double)da[c] - (double)DV[(size_t)pa * 3 + c], J.eps_r, Lr, dLr);
+                        huber_d((double)da[c] - (double)DV[(size_t)pa * 3 + c], J.eps_r, J.ieps_r, Lr, dLr);
                         g[V * 3 + c] += J.alpha * dd * omp * dLr;
                     }
                     if (nb >= 0) {
-                        huber_d((double)DV[(size_t)nb * 3 + c] - (double)da[c], J.eps_r, Lr, dLr);
+                        huber_d((double)DV[(size_t)nb * 3 + c] - (double)da[c], J.eps_r, J.ieps_r, Lr, dLr);
                         g[V * 3 + c] -= J.alpha * dd * omn * dLr;
                         reg += dd * omn * Lr;
                     }
@@ -1122,38 +1147,224 @@ __global__ __launch_bounds__(kRedBlock) void k_combine(const CombineJobs jobs)
     block_reduce_store<8>(v, J.blk + (size_t)b * 8);
 }
 
-// Final sums of one evaluation per job (one block each), after k_combine:
-// the objective terms (mode 1) or the level's eta (mode 0, Eq. 10).
+// Final sums of one evaluation from the rows of its blocks: the objective terms
+// (mode 1) or the level's eta (mode 0, Eq. 10).
+__device__ __forceinline__ void finalize(const CombineJob& J, const double (&sumd)[4])
+{
+    double s[8];
+    sum_rows<8>(J.blk, J.nblk, s);
+    if (threadIdx.x != 0) return;
+    if (J.mode == 0) {
+        // eta = 1 where a term vanishes (identical inputs)
+        *J.eta = (s[5] > 1e-300 && s[6] > 1e-300) ? sqrt(s[6] / s[5]) : 1.0;
+        return;
+    }
+    const double eta = *J.eta;
+    double m = 0.0;
+    for (int c = 0; c < 3; ++c) m += sumd[c] * sumd[c];
+    m *= J.gamma * (double)J.d / (2.0 * (double)J.na);
+    double* t = J.terms;
+    t[OCTMC_TERM_DATA] = s[0];
+    t[OCTMC_TERM_STR] = s[1];
+    t[OCTMC_TERM_ANG] = s[2];
+    t[OCTMC_TERM_REG] = s[3];
+    t[OCTMC_TERM_MEAN] = m;
+    t[OCTMC_TERM_STR05] = s[5];
+    t[OCTMC_TERM_ANG05] = s[6];
+    t[OCTMC_TERM_ETA] = eta;
+    t[OCTMC_TERM_GP] = s[7];
+    t[OCTMC_TERM_F] = s[0] + J.alpha * s[3] + m;
+}
+
+// One block per job, after k_combine.
 __global__ __launch_bounds__(kRedBlock) void k_finalize(const CombineJobs jobs)
 {
     if (jobs.skip && *jobs.skip) return;
     const CombineJob& J = jobs.j[blockIdx.x];
-    double s[8];
-    sum_rows<8>(J.blk, J.nblk, s);
-    if (J.mode == 0) {
-        // eta = 1 where a term vanishes (identical inputs)
-        if (threadIdx.x == 0) *J.eta = (s[5] > 1e-300 && s[6] > 1e-300) ? sqrt(s[6] / s[5]) : 1.0;
-        return;
+    double sumd[4] = {0, 0, 0, 0};
+    if (J.mode == 1) sum_rows<4>(J.sum_blk, J.nsum, sumd);
+    finalize(J, sumd);
+}
+
+// sample2 by four lanes, lane b of them taking source row b (the same operations
+// in the same order); `first` is the first of the four.
+__device__ __forceinline__ void sample2_rows(const float* img, int w, int h, int i, int j, float dx, float dy, int b,
+                                        int first, float out[3])
+{
+    int nx, ny;
+    float tx, ty;
+    split(i, dx, nx, tx);
+    split(j, dy, ny, ty);
+    float wx[4], dwx[4], wy[4], dwy[4];
+    cr_taps(tx, wx, dwx);
+    cr_taps(ty, wy, dwy);
+    const float* row = img + (size_t)clampi(ny - 1 + b, 0, h - 1) * w;
+    float rv = 0.f, rd = 0.f;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const float s = row[clampi(nx - 1 + a, 0, w - 1)];
+        rv = fmaf(wx[a], s, rv);
+        rd = fmaf(dwx[a], s, rd);
     }
-    double sumd[4];
-    sum_rows<4>(J.sum_blk, J.nsum, sumd);
-    if (threadIdx.x == 0) {
+    float v = 0.f, gx = 0.f, gy = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float qv = __shfl(rv, first + q), qd = __shfl(rd, first + q);
+        v = fmaf(wy[q], qv, v);
+        gx = fmaf(wy[q], qd, gx);
+        gy = fmaf(dwy[q], qv, gy);
+    }
+    out[0] = v;
+    out[1] = gx;
+    out[2] = gy;
+}
+
+// Sum of the displacements of both slots by every block for itself (few
+// A-scans): sixteen-byte loads of four A-scans' twelve floats, four of them in
+// flight.
+__device__ __forceinline__ void own_sums(const CombineJob& J, double (&v)[4])
+{
+    typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
+    const int quads = J.na / 4;
+#pragma unroll
+    for (int V = 0; V < 2; ++V) {
+        const float* __restrict__ D = J.disp[V];
+#pragma unroll 4
+        for (int q = threadIdx.x; q < quads; q += kRedBlock) {
+            const quad_t* p = reinterpret_cast<const quad_t*>(D + (size_t)q * 12);
+            const quad_t x = p[0], y = p[1], z = p[2];
+            v[0] += ((double)x[0] + (double)x[3]) + ((double)y[2] + (double)z[1]);
+            v[1] += ((double)x[1] + (double)y[0]) + ((double)y[3] + (double)z[2]);
+            v[2] += ((double)x[2] + (double)y[1]) + ((double)z[0] + (double)z[3]);
+        }
+        const int a = 4 * quads + threadIdx.x;
+        if (a < J.na) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c] += (double)D[(size_t)a * 3 + c];
+        }
+    }
+}
+
+// k_combine for few A-scans, which are latency: eight lanes take an A-scan, and
+// the launches before and after it go into it.  Lanes 0 - 3 sample the first
+// scan's en face image and lanes 4 - 7 the second's, a source row each; every lane
+// forms the terms that all components share; lanes 0 - 5 form one component of the
+// gradient each, with its two links of the regulariser.  Every block sums the
+// displacements for itself and the last one done forms the final sums.  64 x 64
+// x 128 float32: displacement sum, combination and final sums 18.5 us in three
+// launches, 10.6 in one (the block's count with its release and acquire 1.6 of
+// them, which is why many A-scans keep three launches: with the count 12 us
+// more at 1000 blocks).
+__global__ __launch_bounds__(kRedBlock) void k_combine_few(const CombineJobs jobs)
+{
+    __shared__ double shd[kRedBlock / 64][4];
+    __shared__ int last;
+    if (jobs.skip && *jobs.skip) return;
+    int jid = 0;
+    for (int q = 1; q < jobs.n; ++q)
+        if ((int)blockIdx.x >= jobs.j[q].blk_begin) jid = q;
+    const CombineJob& J = jobs.j[jid];
+    const int b = blockIdx.x - J.blk_begin;
+    const int lane = threadIdx.x & 63, r = lane & 7, V = r >> 2;
+    const int w = J.w, h = J.h, na = J.na;
+    const double dd = (double)J.d;
+    const int oX = J.orient & 1, oY = (J.orient >> 1) & 1, oV = V == 0 ? oX : oY;
+    // this lane's component of the gradient: slot S, component c (lanes 6 and 7 none)
+    const int S = r >= 3, c = r - 3 * S, oS = S == 0 ? oX : oY;
+    const int mine = b * kFewAscans + (int)(threadIdx.x >> 3);
+    const bool live = mine < na;
+    const int a = live ? mine : na - 1;  // all lanes of a wave exchange: idle ones repeat the last A-scan
+    const int i = a % w, j = a / w;
+    // sum of all displacements (mean term)
+    double sumd[4] = {0, 0, 0, 0};
+    if (J.mode == 1) {  // block-uniform
+        double own[4] = {0, 0, 0, 0};
+        own_sums(J, own);
+        store_wave_sums<4>(own, shd);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sumd[q] = wave_rows<4>(shd, q);
+    }
+    const float4 p0 = reinterpret_cast<const float4*>(J.part)[(size_t)a * 2];
+    const float4 p1 = reinterpret_cast<const float4*>(J.part)[(size_t)a * 2 + 1];
+    const double lam = p0.x;
+    const float* dV = J.disp[V] + (size_t)a * 3;
+    float mv[3], ov[3];  // en face sample of this lane's scan and of the other
+    sample2_rows(V == 0 ? J.ax : J.ay, w, h, i, j, dV[0], dV[1], r & 3, lane & ~3, mv);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) ov[q] = __shfl_xor(mv[q], 4);
+    double LA, GA;
+    huber_d(V == 0 ? (double)mv[0] - (double)ov[0] : (double)ov[0] - (double)mv[0], J.eps_h, J.ieps_h, LA, GA);
+    // validity (Eq. 5), as in k_combine
+    float rv[2];
+    sample1(V == 0 ? J.vx : J.vy, oV == 0 ? h : w, oV == 0 ? j : i, oV == 0 ? dV[1] : dV[0], rv);
+    const float ro[2] = {__shfl_xor(rv[0], 4), __shfl_xor(rv[1], 4)};
+    const float rx0 = V == 0 ? rv[0] : ro[0], ry0 = V == 0 ? ro[0] : rv[0];
+    const float rx1 = V == 0 ? rv[1] : ro[1], ry1 = V == 0 ? ro[1] : rv[1];
+    const double tvx = rx0 <= 0.f ? 0.0 : (rx0 >= 1.f ? 1.0 : (double)rx0);
+    const double dtvx = (rx0 > 0.f && rx0 < 1.f) ? (double)rx1 : 0.0;
+    const double tvy = ry0 <= 0.f ? 0.0 : (ry0 >= 1.f ? 1.0 : (double)ry0);
+    const double dtvy = (ry0 > 0.f && ry0 < 1.f) ? (double)ry1 : 0.0;
+    // partial sums: data, str, ang, reg, (unused), str05, ang05, g.p
+    double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (live && r == 0) {
+        v[5] = (1.0 - 0.5 * tvx * tvy) * lam;
+        v[6] = 0.5 * tvx * tvy * dd * LA;
+    }
+    if (J.mode == 1) {
         const double eta = *J.eta;
-        double m = 0.0;
-        for (int c = 0; c < 3; ++c) m += sumd[c] * sumd[c];
-        m *= J.gamma * (double)J.d / (2.0 * (double)J.na);
-        double* t = J.terms;
-        t[OCTMC_TERM_DATA] = s[0];
-        t[OCTMC_TERM_STR] = s[1];
-        t[OCTMC_TERM_ANG] = s[2];
-        t[OCTMC_TERM_REG] = s[3];
-        t[OCTMC_TERM_MEAN] = m;
-        t[OCTMC_TERM_STR05] = s[5];
-        t[OCTMC_TERM_ANG05] = s[6];
-        t[OCTMC_TERM_ETA] = eta;
-        t[OCTMC_TERM_GP] = s[7];
-        t[OCTMC_TERM_F] = s[0] + J.alpha * s[3] + m;
+        const double delta = J.delta0 * tvx * tvy;  // Eq. 8
+        const double ws = eta * (1.0 - delta);       // structural weight (Eqs. 6, 9)
+        const double wa = dd / eta * delta;          // angiographic weight (Eqs. 7, 9)
+        if (live && r == 0) {
+            v[1] = (1.0 - delta) * lam;
+            v[2] = delta * dd * LA;
+            v[0] = eta * v[1] + v[2] / eta;
+        }
+        const double dpd = -eta * lam + dd / eta * LA;  // d(data)/d(delta)
+        // the component's partial, and the en face derivative of its scan (lane 3's
+        // is the other four's)
+        const double pc = S == 0 ? (c == 0 ? p0.y : (c == 1 ? p0.z : p0.w)) : (c == 0 ? p1.x : (c == 1 ? p1.y : p1.z));
+        const float jc = S == V ? (c == 0 ? mv[1] : mv[2]) : (c == 0 ? ov[1] : ov[2]);
+        double g = c == 2 ? ws * pc : ws * pc + wa * GA * jc;
+        if (S == 1) g = -g;
+        if (S == 0 && c == (oX == 0 ? 1 : 0)) g += dpd * J.delta0 * tvy * dtvx;
+        if (S == 1 && c == (oY == 1 ? 0 : 1)) g += dpd * J.delta0 * tvx * dtvy;
+        if (live && r < 6) {
+            // scan-order regulariser (gather form: this A-scan's two links)
+            const float* DS = J.disp[S];
+            const double da = DS[(size_t)a * 3 + c];
+            double omp, omn, Lr, dLr;
+            const int pa = prev_ascan(oS, i, j, w, h, J.wfb, omp);
+            const int nb = next_ascan(oS, i, j, w, h, J.wfb, omn);
+            if (pa >= 0) {
+                huber_d(da - (double)DS[(size_t)pa * 3 + c], J.eps_r, J.ieps_r, Lr, dLr);
+                g += J.alpha * dd * omp * dLr;
+            }
+            if (nb >= 0) {
+                huber_d((double)DS[(size_t)nb * 3 + c] - da, J.eps_r, J.ieps_r, Lr, dLr);
+                g -= J.alpha * dd * omn * dLr;
+                v[3] = dd * omn * Lr;
+            }
+            // mean-displacement term: dM/dd_c = gamma d sum_c / N_A
+            g += J.gamma * dd * (c == 0 ? sumd[0] : (c == 1 ? sumd[1] : sumd[2])) / (double)na;
+            const size_t at = ((size_t)S * na + a) * 3 + c;
+            if (J.grad) J.grad[at] = (float)g;
+            if (J.grad64) J.grad64[at] = g;
+            if (J.p) v[7] = g * J.p[at];  // directional derivative g . p (line search)
+        }
     }
+    block_reduce_store<8>(v, J.blk + (size_t)b * 8);
+    __syncthreads();
+    // the block that comes last (its count releases its row and acquires the
+    // others') forms the sums, and leaves the count at zero for the next launch
+    if (threadIdx.x == 0) {
+        const unsigned n = __hip_atomic_fetch_add(J.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        last = n == (unsigned)J.nblk - 1;
+        if (last) __hip_atomic_store(J.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (last) finalize(J, sumd);
 }
 
 // ---------------------------------------------------------------------------
@@ -1709,10 +1920,26 @@ hipError_t launch_struct(const StructJobs& jobs, int total_blocks, octmc_dtype d
     return axial ? launch_struct_t<true>(jobs, total_blocks, dt, s) : launch_struct_t<false>(jobs, total_blocks, dt, s);
 }
 
-hipError_t launch_combine(const CombineJobs& jobs, int total_blocks, hipStream_t s)
+// The choice is made by the job's own sizes, as for the structural kernels.
+hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_combine, dim3(total_blocks), dim3(kRedBlock), 0, s, jobs);
-    hipLaunchKernelGGL(k_finalize, dim3(jobs.n), dim3(kRedBlock), 0, s, jobs);
+    CombineJobs few{}, many{};
+    few.skip = many.skip = jobs.skip;
+    int nb[2] = {0, 0};
+    for (int q = 0; q < jobs.n; ++q) {
+        CombineJob J = jobs.j[q];
+        const bool f = few_ascans(J.na);
+        J.blk_begin = nb[f];
+        J.nblk = combine_rows(J.na);
+        nb[f] += J.nblk;
+        CombineJobs& to = f ? few : many;
+        to.j[to.n++] = J;
+    }
+    if (few.n) hipLaunchKernelGGL(k_combine_few, dim3(nb[1]), dim3(kRedBlock), 0, s, few);
+    if (many.n) {
+        hipLaunchKernelGGL(k_combine, dim3(nb[0]), dim3(kRedBlock), 0, s, many);
+        hipLaunchKernelGGL(k_finalize, dim3(many.n), dim3(kRedBlock), 0, s, many);
+    }
     return hipGetLastError();
 }
 

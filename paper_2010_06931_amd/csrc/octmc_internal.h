@@ -170,15 +170,16 @@ struct CombineJob {
     const float* ay;
     const float* vx;     // validity [h]
     const float* vy;     // validity [w]
-    const double* sum_blk;  // [nsum][4] displacement-sum partials of step 0
+    const double* sum_blk;  // [nsum][4] displacement-sum partials of step 0 (not for few A-scans)
     double* eta;         // level constant (read in mode 1, written in mode 0)
     const double* p;     // [2][na][3] search direction (float64) or nullptr
     double* blk;         // [nblk][8] block partials
+    unsigned* ticket;    // few A-scans: blocks done, 0 between launches
     double* terms;       // [OCTMC_NTERMS] (mode 1)
     int w, h, d, na, blk_begin, nblk, nsum;
     int mode;            // 0: only set eta (Eq. 10); 1: full evaluation
     int orient;          // scan orientation of the two slots (bit 0: first, bit 1: second; 0 X-fast, 1 Y-fast)
-    double delta0, eps_h, eps_r, alpha, gamma, wfb;
+    double delta0, eps_h, eps_r, ieps_h, ieps_r, alpha, gamma, wfb;
 };
 struct CombineJobs {
     CombineJob j[kMaxJobs];
@@ -193,9 +194,16 @@ hipError_t launch_sum(const SumJobs& jobs, int total_blocks, hipStream_t s);
 // the centre column alone and leave the x and y partials at 0
 hipError_t launch_struct(const StructJobs& jobs, int total_blocks, octmc_dtype dt, hipStream_t s,
                          bool axial = false);
-// per-A-scan combination (total_blocks) followed by the fixed-order final
-// sums, one block per job
-hipError_t launch_combine(const CombineJobs& jobs, int total_blocks, hipStream_t s);
+// per-A-scan combination and the fixed-order final sums.  Few A-scans take one
+// launch, with the displacement sum in it; the others launch_sum before it.
+// Evaluations of float32, 128 samples, as few / as many: 64 x 64 21.3 / 26.2 us,
+// 90 x 90 33.0 / 33.2, 100 x 100 37.4 / 36.4, 128 x 128 51.0 / 43.6.
+constexpr int kFewMaxAscans = 8192;
+constexpr int kFewAscans = kRedBlock / 8;  // A-scans of a block of theirs
+inline bool few_ascans(int na) { return na <= kFewMaxAscans; }
+// rows of block partials
+inline int combine_rows(int na) { return few_ascans(na) ? (na + kFewAscans - 1) / kFewAscans : (na + kRedBlock - 1) / kRedBlock; }
+hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s);
 // the structural partials of every volume pair of n volumes at one level,
 // each volume resampled once (n = 3 or 4; float32 storage, or 16-bit storage
 // at an even storage pitch dp: see struct_multi_supported); part[q] is pair

@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <deque>
 #include <memory>
 #include <mutex>
@@ -80,6 +81,14 @@ int scratch_address(int device, void** out)
 namespace {
 
 constexpr int kSumBlocks = 256;
+// The count of finished combination blocks lies in the unused fourth column of
+// the last row of the displacement-sum partials: zero when allocated, and k_sum
+// writes 0.0 there.
+constexpr size_t kTicketAt = kSumBlocks * 4 - 1;
+// The rows of few A-scans are more than of many; they lie where the dot products'
+// rows do (an evaluation and a pass of dot products follow each other).
+static_assert(512 * (kMaxDots + 1) >= kFewMaxAscans / kFewAscans * 8, "they fit there");
+static_assert((size_t)kFewMaxAscans / kFewAscans * 64 <= kNoAllocComb, "and in the static scratch");
 
 int nblk_combine(int na) { return (na + kRedBlock - 1) / kRedBlock; }
 
@@ -93,12 +102,12 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
     SumJobs sj{};
     StructJobs tj{};
     CombineJobs cj{};
-    sj.n = tj.n = cj.n = n;
+    tj.n = cj.n = n;
     // one skip flag for the grouped launch (a solver enqueued ahead of its decisions)
     sj.skip = tj.skip = cj.skip = ea[0].skip;
     for (int q = 1; q < n; ++q)
         if (ea[q].skip != ea[0].skip) return fail(OCTMC_E_INVALID, "grouped evaluations must share their skip flag");
-    int sb = 0, tb = 0, cb = 0;
+    int sb = 0, tb = 0;
     EvalView views[kMaxJobs];
     for (int q = 0; q < n; ++q) {
         if (ea[q].view) {
@@ -111,7 +120,7 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
             v.params = &P->params;
             v.part = P->part;
             v.sum_blk = P->sum_blk;
-            v.comb_blk = P->comb_blk;
+            v.comb_blk = few_ascans(v.L.na) ? P->dot_blk : P->comb_blk;
             v.eta = P->eta + ea[q].level;
             v.orient = P->orient;
         }
@@ -124,16 +133,15 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
         any_eta |= ea[q].eta_mode == 0;
         const octmc_params& pr = *V.params;
         if (V.dtype != dt) return fail(OCTMC_E_DTYPE, "batched pairs must share the storage type");
-        const int nsum = std::min(kSumBlocks, (2 * L.na + kRedBlock - 1) / kRedBlock);
+        const int nsum = few_ascans(L.na) ? 0 : std::min(kSumBlocks, (2 * L.na + kRedBlock - 1) / kRedBlock);
         const float* dy = ea[q].disp_y ? ea[q].disp_y : ea[q].disp + (size_t)L.na * 3;
         if (with_struct && dy != ea[q].disp + (size_t)L.na * 3)
             return fail(OCTMC_E_INVALID, "the structural kernels read both slots' fields as one [2][na][3] array");
-        sj.j[q] = SumJob{{ea[q].disp, dy}, V.sum_blk, L.na, sb, nsum};
+        if (nsum) sj.j[sj.n++] = SumJob{{ea[q].disp, dy}, V.sum_blk, L.na, sb, nsum};
         sb += nsum;
         tj.j[q] = StructJob{L.sx, L.sy, ea[q].disp, V.part, L.w, L.h, L.d, L.na, tb, L.vol_bytes,
                             (float)pr.eps_huber, L.dp};
         tb += struct_blocks(L.w, L.h);
-        const int nc = nblk_combine(L.na);
         const int blen = L.w;  // square scans: every B-scan has w A-scans
         const double f = std::floor(pr.flyback_frac * blen + 0.5);
         CombineJob c{};
@@ -151,26 +159,27 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
         c.eta = V.eta;
         c.p = ea[q].p;
         c.blk = V.comb_blk;
+        c.ticket = reinterpret_cast<unsigned*>(V.sum_blk + kTicketAt);
         c.terms = ea[q].terms;
         c.w = L.w;
         c.h = L.h;
         c.d = L.d;
         c.na = L.na;
-        c.blk_begin = cb;
-        c.nblk = nc;
         c.mode = 1;
         c.orient = V.orient;
         c.delta0 = pr.delta0;
         c.eps_h = pr.eps_huber;
         c.eps_r = pr.eps_reg;
+        constexpr double most = std::numeric_limits<double>::max();
+        c.ieps_h = std::min(1.0 / pr.eps_huber, most);
+        c.ieps_r = std::min(1.0 / pr.eps_reg, most);
         c.alpha = pr.alpha;
         c.gamma = pr.mean_weight;
         c.wfb = 1.0 / std::sqrt(1.0 + f);
         cj.j[q] = c;
-        cb += nc;
     }
     if (ev) HIP_TRY(hipEventRecord(ev[0], s));
-    HIP_TRY(launch_sum(sj, sb, s));
+    if (sj.n) HIP_TRY(launch_sum(sj, sb, s));
     if (ev) HIP_TRY(hipEventRecord(ev[1], s));
     bool axial = true;
     for (int q = 0; q < n; ++q) axial &= ea[q].axial;
@@ -179,7 +188,6 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
     if (any_eta) {  // eta of the jobs that ask for it, before their evaluation
         CombineJobs c0{};
         c0.skip = cj.skip;
-        int b0 = 0;
         for (int q = 0; q < n; ++q) {
             if (ea[q].eta_mode != 0) continue;
             CombineJob c = cj.j[q];
@@ -187,13 +195,11 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
             c.grad = nullptr;
             c.grad64 = nullptr;
             c.p = nullptr;
-            c.blk_begin = b0;
-            b0 += c.nblk;
             c0.j[c0.n++] = c;
         }
-        HIP_TRY(launch_combine(c0, b0, s));
+        HIP_TRY(launch_combine(c0, s));
     }
-    HIP_TRY(launch_combine(cj, cb, s));
+    HIP_TRY(launch_combine(cj, s));
     if (ev) HIP_TRY(hipEventRecord(ev[3], s));
     return OCTMC_OK;
 }
@@ -226,6 +232,7 @@ int octmc::pair_alloc_scratch(octmc_pair* P, size_t na, hipStream_t s)
     HIP_TRY(P->alloc(&P->eta, OCTMC_MAX_LEVELS * 8));
     HIP_TRY(P->alloc(&P->terms, OCTMC_NTERMS * 8));
     HIP_TRY(P->alloc(&P->dot_blk, (size_t)512 * (kMaxDots + 1) * 8));
+    HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(P->sum_blk + kTicketAt), 0u, 2, s));
     HIP_TRY(P->alloc(&P->dot_out, (kMaxDots + 1) * 8));
     HIP_TRY(P->alloc(&P->lb, sizeof(LbState)));
     static const std::vector<double> ones(OCTMC_MAX_LEVELS, 1.0);
