@@ -22,6 +22,7 @@
 #include <cmath>
 
 #include "octmc_internal.h"
+#include "row_quads.h"
 
 namespace octmc {
 namespace {
@@ -378,48 +379,14 @@ __global__ __launch_bounds__(256) void k_enface_init(const float* __restrict__ v
     }
 }
 
-// Sixteen lanes take an A-scan and a lane four consecutive samples of it at a
-// time, with one 16-byte load (4-byte alignment costs nothing), so that every
-// depth and alignment is read at the same rate; the loads of kRowLoads steps are
-// issued together.  500 x 500 x 465, one load at a time and a wave to an A-scan
-// before: a radix pass 158 -> 110 us (465 MB), the masked mean 362 -> 234 us (1.4
-// GB; 16-byte loads for whole multiples of 4 only before).  With the loads left to
-// an unrolled loop a radix pass took 193 us: the loop's remainder, one load at a
-// time, is where all of an A-scan falls.
-typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
-
-struct Quad {
-    quad_t v;
-    int first;  // the samples `first`.. 3 belong to this lane
-};
-// samples k .. k + 3 of a column of d; beyond its end, the last four from their
-// place on
-__device__ __forceinline__ Quad load_quad(const float* __restrict__ col, int k, int d)
-{
-    Quad q;
-    if (d >= 4) {  // uniform
-        const int at = k < d - 4 ? k : d - 4;
-        q.v = *reinterpret_cast<const quad_t*>(col + at);
-        q.first = k < d ? k - at : 4;
-    } else {
-        // the first d places hold nothing; their samples end at place 3
-#pragma unroll
-        for (int e = 0; e < 4; ++e) q.v[e] = col[e - (4 - d) < 0 ? 0 : e - (4 - d)];
-        q.first = k < d ? 4 - d + k : 4;
-    }
-    return q;
-}
-constexpr int kRowLanes = 16;            // lanes of an A-scan
-constexpr int kRowStep = 4 * kRowLanes;  // samples they take at a time
-constexpr int kRowLoads = 8;             // of these steps are in flight together
-
 // Radix passes 1 and 2 over the filtered volume: pass 1 counts bits 20..10
 // of the samples whose bits 31..21 equal one of the distinct target
 // prefixes, pass 2 bits 9..0 of those whose bits 31..10 do; one histogram of
 // kHistBins counters per distinct prefix (kTargets of them at most).  Pass 0 is
 // counted by the slow-axis rank filter.  Prefixes and digits are taken from the
 // float's own bits, which the key inverts below zero: a prefix that is below
-// zero is compared inverted, and so is its digit.
+// zero is compared inverted, and so is its digit.  500 x 500 x 465, 465 MB: 110 us
+// (158 with a wave to an A-scan and 4-byte loads).
 template <int kTargets>
 __device__ __forceinline__ void count_rows(const float* __restrict__ vol, int w, int h, int d, int V,
                                            const float* __restrict__ valid, const SelState* __restrict__ st, int pass,
@@ -649,23 +616,10 @@ __global__ __launch_bounds__(256) void k_noise_final(const double* __restrict__ 
     else st->thr_s = st->mu + 2.0 * sqrt(s / cnt);
 }
 
-// Sum over the sixteen lanes of an A-scan; every lane gets it.
-__device__ __forceinline__ double row_sum(double v)
-{
-#pragma unroll
-    for (int m = kRowLanes / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
-    return v;
-}
-__device__ __forceinline__ int row_sum(int v)
-{
-#pragma unroll
-    for (int m = kRowLanes / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
-    return v;
-}
-
 // Both masks and the masked depth mean.  The FP64 thresholds are compared as the
 // float32 values that part the samples alike: r < t if r < the least float not
-// below t, s > t if s > the largest not above it.
+// below t, s > t if s > the largest not above it.  500 x 500 x 465, 1.4 GB: 234 us
+// (362 with a wave to an A-scan and 16-byte loads for whole multiples of 4 only).
 __global__ __launch_bounds__(256) void k_mask_mean(const float* __restrict__ filt, const float* __restrict__ oct,
                                                    const float* __restrict__ octa, unsigned na, int d,
                                                    const SelState* __restrict__ st, double* __restrict__ E,

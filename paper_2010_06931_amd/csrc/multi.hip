@@ -317,62 +317,39 @@ int ingest_volume(octmc_multi* M, int V, const octmc_shape* shape, const float* 
         HIP_TRY(hipStreamSynchronize(s));
         if (bad) return fail(OCTMC_E_NAN, "non-finite values in a structural volume");
     }
-    // validity on the host (for the substitution table) and on the device
-    std::vector<float> hv(nb, 1.0f);
+    const bool host = shape->mem == OCTMC_MEM_HOST, detect = octa && !valid && (pr.flags & OCTMC_DETECT_INVALID);
     float* vd = nullptr;
     HIP_TRY(M->alloc(&vd, (size_t)nb * 4));
-    if (valid) {
-        HIP_TRY(hipMemcpyAsync(hv.data(), valid, (size_t)nb * 4,
-                               shape->mem == OCTMC_MEM_HOST ? hipMemcpyHostToHost : hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-    }
+    if (valid) HIP_TRY(hipMemcpyAsync(vd, valid, (size_t)nb * 4, kind, s));
+    else if (!detect) HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(vd), 0x3F800000u, nb, s));
     float* enf = nullptr;
     HIP_TRY(M->alloc(&enf, na * 4));
     if (octa) {
         HIP_TRY(M->alloc(&P.octa, nv * 4));
-        HIP_TRY(hipMemcpyAsync(P.octa, octa, nv * 4, kind, s));
-        if (!valid && (pr.flags & OCTMC_DETECT_INVALID)) {
+        if (host) {
+            HIP_TRY(hipMemcpyAsync(P.octa, octa, nv * 4, kind, s));
+            octa = P.octa;
+        }
+        if (detect) {
             double* means = (double*)tmp.get((size_t)nb * 8);
             if (!means) return fail(OCTMC_E_OOM, "out of device memory (validity)");
-            HIP_TRY(launch_validity(P.octa, w, h, d, o, means, vd, s));
-            HIP_TRY(hipMemcpyAsync(hv.data(), vd, (size_t)nb * 4, hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
+            HIP_TRY(launch_validity(octa, w, h, d, o, means, vd, s));
         }
-    }
-    HIP_TRY(hipMemcpyAsync(vd, hv.data(), (size_t)nb * 4, hipMemcpyHostToDevice, s));
-    if (octa) {
-        if (!enface && (pr.flags & OCTMC_ENFACE_PROJECT)) {
+        const bool project = !enface && (pr.flags & OCTMC_ENFACE_PROJECT);
+        if (project) {
             void* scratch = tmp.get(enface_scratch_bytes(w, h, d));
             if (!scratch) return fail(OCTMC_E_OOM, "out of device memory (projection)");
-            HIP_TRY(launch_enface_project(f32, P.octa, w, h, d, o, vd, nullptr, enf, nullptr, nullptr, scratch, s));
+            HIP_TRY(launch_enface_project(f32, octa, w, h, d, o, vd, nullptr, enf, nullptr, nullptr, scratch, s));
         }
         // nearest valid B-scan for the merge (the lower one on a tie)
-        bool any_valid = false, any_invalid = false;
-        for (int b = 0; b < nb; ++b) {
-            any_valid |= hv[b] > 0.5f;
-            any_invalid |= !(hv[b] > 0.5f);
+        int* from = nullptr;
+        if (valid || detect) {
+            from = (int*)tmp.get((size_t)nb * 4);
+            if (!from) return fail(OCTMC_E_OOM, "out of device memory");
+            HIP_TRY(launch_nearest_valid(vd, nb, from, s));
         }
-        if (any_valid && any_invalid) {
-            std::vector<int> from(nb);
-            for (int b = 0; b < nb; ++b) {
-                if (hv[b] > 0.5f) {
-                    from[b] = b;
-                    continue;
-                }
-                int best = -1;
-                for (int dist = 1; dist < nb && best < 0; ++dist) {
-                    if (b - dist >= 0 && hv[b - dist] > 0.5f) best = b - dist;
-                    else if (b + dist < nb && hv[b + dist] > 0.5f) best = b + dist;
-                }
-                from[b] = best;
-            }
-            int* dfrom = (int*)tmp.get((size_t)nb * 4);
-            if (!dfrom) return fail(OCTMC_E_OOM, "out of device memory");
-            HIP_TRY(hipMemcpyAsync(dfrom, from.data(), (size_t)nb * 4, hipMemcpyHostToDevice, s));
-            HIP_TRY(launch_copy_bscans(P.octa, w, h, d, dfrom, o, s));
-            HIP_TRY(hipStreamSynchronize(s));  // `from` is host memory
-        }
-        if (!enface && !(pr.flags & OCTMC_ENFACE_PROJECT)) HIP_TRY(launch_enface_mean(P.octa, (int)na, d, enf, s));
+        const bool mean = !enface && !project;
+        if (!host || from || mean) HIP_TRY(launch_take_octa(octa, P.octa, w, h, d, from, o, mean ? enf : nullptr, s));
     }
     if (enface) HIP_TRY(hipMemcpyAsync(enf, enface, na * 4, kind, s));
     // pyramid
@@ -380,27 +357,39 @@ int ingest_volume(octmc_multi* M, int V, const octmc_shape* shape, const float* 
     float* cen = enf;
     float* cv = vd;
     for (int l = 0; l < M->nlev; ++l) {
-        const int lw = M->w[l], lh = M->h[l], ld = M->d[l];
+        LevelJob job;
+        job.nvol = 1;
+        job.w = M->w[l];
+        job.h = M->h[l];
+        job.d = M->d[l];
         // stored with an even pitch in 16-bit storage (odd depths padded), as a pair's levels
-        const int lp = storage_pitch(ld, M->dtype);
-        HIP_TRY(M->alloc(&P.s[l], (size_t)lw * lh * lp * esz(M->dtype)));
-        HIP_TRY(launch_to_storage_pitched(cur, P.s[l], lw * lh, ld, lp, M->dtype, s));
+        job.dp = storage_pitch(job.d, M->dtype);
+        job.in[0] = cur;
+        job.image[0] = cen;
+        job.valid[0] = cv;
+        job.nvalid[0] = o == 0 ? job.h : job.w;
+        const bool more = l + 1 < M->nlev, as_is = M->dtype == OCTMC_F32;
+        if (as_is && l > 0) {  // the level's float32 volume is its storage
+            P.s[l] = const_cast<float*>(cur);
+        } else {
+            HIP_TRY(M->alloc(&P.s[l], (size_t)job.w * job.h * job.dp * esz(M->dtype)));
+            job.store[0] = P.s[l];
+        }
         P.a[l] = cen;
         P.v[l] = cv;
-        if (l + 1 < M->nlev) {
+        if (more) {
             const int w2 = M->w[l + 1], h2 = M->h[l + 1], d2 = M->d[l + 1];
-            float* nxt = (float*)tmp.get((size_t)w2 * h2 * d2 * 4);
-            if (!nxt) return fail(OCTMC_E_OOM, "out of device memory (pyramid)");
-            HIP_TRY(launch_pyr3(cur, lw, lh, ld, nxt, s));
-            float *ne = nullptr, *nvv = nullptr;
-            HIP_TRY(M->alloc(&ne, (size_t)w2 * h2 * 4));
-            HIP_TRY(launch_pyr2(cen, lw, lh, ne, s));
-            HIP_TRY(M->alloc(&nvv, (size_t)(o == 0 ? h2 : w2) * 4));
-            HIP_TRY(launch_pyr1(cv, o == 0 ? lh : lw, nvv, s));
-            cur = nxt;
-            cen = ne;
-            cv = nvv;
+            const size_t bytes = (size_t)w2 * h2 * d2 * 4;
+            if (as_is) HIP_TRY(M->alloc(&job.next[0], bytes));
+            else job.next[0] = (float*)tmp.get(bytes);
+            if (!job.next[0]) return fail(OCTMC_E_OOM, "out of device memory (pyramid)");
+            HIP_TRY(M->alloc(&job.next_image[0], (size_t)w2 * h2 * 4));
+            HIP_TRY(M->alloc(&job.next_valid[0], (size_t)(o == 0 ? h2 : w2) * 4));
         }
+        if (job.store[0] || more) HIP_TRY(launch_level(job, M->dtype, s));
+        cur = job.next[0];
+        cen = job.next_image[0];
+        cv = job.next_valid[0];
     }
     return OCTMC_OK;
 }

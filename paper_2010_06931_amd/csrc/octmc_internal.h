@@ -215,17 +215,23 @@ hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp,
                                const int* skip = nullptr);
 
 // preparation (kernels_prep.hip)
-hipError_t launch_to_storage(const float* in, void* out, size_t n, octmc_dtype dt, hipStream_t s);
-// float32 [na][d] -> storage type [na][dp] (dp >= d; samples d .. dp - 1 of
-// every A-scan repeat sample d - 1)
-hipError_t launch_to_storage_pitched(const float* in, void* out, int na, int d, int dp, octmc_dtype dt,
-                                     hipStream_t s);
-hipError_t launch_pyr3(const float* in, int w, int h, int d, float* out, hipStream_t s);
-hipError_t launch_pyr2(const float* in, int w, int h, float* out, hipStream_t s);
-hipError_t launch_pyr1(const float* in, int n, float* out, hipStream_t s);
-hipError_t launch_enface_mean(const float* vol, int na, int d, float* out, hipStream_t s);
+// One level of the pyramids of one or two volumes with their images and validity.
+struct LevelJob {
+    int nvol = 0, w = 0, h = 0, d = 0, dp = 0;  // dp: pitch of the storage, d or d + 1
+    const float* in[2] = {};    // float32 [h][w][d]
+    void* store[2] = {};        // the level in the storage type [h][w][dp], or null
+    float* next[2] = {};        // the next level in float32, or null
+    const float* image[2] = {}; // en face images [h][w]
+    float* next_image[2] = {};  // the next level's (null: there is none), and with it
+    const float* valid[2] = {}; // validity of nvalid B-scans
+    float* next_valid[2] = {};
+    int nvalid[2] = {};
+};
+hipError_t launch_level(const LevelJob& job, octmc_dtype dt, hipStream_t s);
+hipError_t launch_take_octa(const float* in, float* out, int w, int h, int d, const int* from, int V, float* mean,
+                            hipStream_t s);
+hipError_t launch_nearest_valid(const float* valid, int nb, int* from, hipStream_t s);
 hipError_t launch_count_nonfinite(const float* v, size_t n, unsigned* counter, hipStream_t s);
-hipError_t launch_copy_bscans(float* vol, int w, int h, int d, const int* src, int V, hipStream_t s);
 hipError_t launch_upsample(const double* coarse, int wc, int hc, double* fine, int wf, int hf, hipStream_t s,
                            int nvol = 2);
 // Stage 1, rough axial prealignment (kernels_prealign.hip, prealign.hip).

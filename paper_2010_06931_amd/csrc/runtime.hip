@@ -537,12 +537,6 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
         HIP_TRY(hipMemcpyAsync(copy, f32[V], nv * 4, kind, s));
         f32[V] = copy;
     }
-    std::vector<float> hvx(h, 1.0f), hvy(w, 1.0f);
-    if (valid_x) {
-        HIP_TRY(hipMemcpyAsync(hvx.data(), valid_x, h * 4, host ? hipMemcpyHostToHost : hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(hvy.data(), valid_y, w * 4, host ? hipMemcpyHostToHost : hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-    }
     unsigned* ctr = nullptr;
     HIP_TRY(P->alloc(&ctr, 64));
     HIP_TRY(launch_fill_u32(ctr, 0u, 16, s));
@@ -555,6 +549,15 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
         HIP_TRY(hipStreamSynchronize(s));
         if (bad) return fail(OCTMC_E_NAN, "non-finite values in the structural volumes");
     }
+    // validity: as given, from the OCTA volumes below, or all valid
+    float* cval[2] = {nullptr, nullptr};
+    const int nval[2] = {h, w};
+    const float* valid[2] = {valid_x, valid_y};
+    for (int V = 0; V < 2; ++V) {
+        HIP_TRY(P->alloc(&cval[V], nval[V] * 4));
+        if (valid_x) HIP_TRY(hipMemcpyAsync(cval[V], valid[V], nval[V] * 4, kind, s));
+        else if (!detect) HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(cval[V]), 0x3F800000u, nval[V], s));
+    }
     // OCTA volumes: keep for the merge, replace invalid B-scans by their
     // nearest valid neighbour (Sec. 2.3, 2.5), then project
     float* enf[2] = {nullptr, nullptr};
@@ -564,53 +567,30 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
         const float* src[2] = {octa_x, octa_y};
         for (int V = 0; V < 2; ++V) {
             HIP_TRY(P->alloc(&P->octa[V], nv * 4));
-            HIP_TRY(hipMemcpyAsync(P->octa[V], src[V], nv * 4, kind, s));
-            if (detect) {  // B-scan validity from the OCTA volume (Sec. 2.2)
-                std::vector<float>& hv = V == 0 ? hvx : hvy;
-                double* means = (double*)talloc(hv.size() * 8);
-                float* dv = (float*)talloc(hv.size() * 4);
-                if (!means || !dv) return fail(OCTMC_E_OOM, "out of device memory (validity)");
-                HIP_TRY(launch_validity(P->octa[V], w, h, d, V, means, dv, s));
-                HIP_TRY(hipMemcpyAsync(hv.data(), dv, hv.size() * 4, hipMemcpyDeviceToHost, s));
-                HIP_TRY(hipStreamSynchronize(s));
+            if (host) {
+                HIP_TRY(hipMemcpyAsync(P->octa[V], src[V], nv * 4, kind, s));
+                src[V] = P->octa[V];
             }
-            const std::vector<float>& val = V == 0 ? hvx : hvy;
-            const int nb = V == 0 ? h : w;
+            if (detect) {  // B-scan validity from the OCTA volume (Sec. 2.2)
+                double* means = (double*)talloc(nval[V] * 8);
+                if (!means) return fail(OCTMC_E_OOM, "out of device memory (validity)");
+                HIP_TRY(launch_validity(src[V], w, h, d, V, means, cval[V], s));
+            }
             if (project) {  // Sec. 2.3, from the OCTA volume before substitution
                 if (!pscratch) pscratch = talloc(enface_scratch_bytes(w, h, d));
-                float* dv = (float*)talloc((size_t)nb * 4);
-                if (!pscratch || !dv) return fail(OCTMC_E_OOM, "out of device memory (projection)");
-                HIP_TRY(hipMemcpyAsync(dv, val.data(), (size_t)nb * 4, hipMemcpyHostToDevice, s));
-                HIP_TRY(launch_enface_project(f32[V], P->octa[V], w, h, d, V, dv, nullptr, enf[V], nullptr, nullptr,
+                if (!pscratch) return fail(OCTMC_E_OOM, "out of device memory (projection)");
+                HIP_TRY(launch_enface_project(f32[V], src[V], w, h, d, V, cval[V], nullptr, enf[V], nullptr, nullptr,
                                               pscratch, s));
-                HIP_TRY(hipStreamSynchronize(s));  // `val` is host memory
             }
-            std::vector<int> from(nb);
-            bool any_valid = false, any_invalid = false;
-            for (int b = 0; b < nb; ++b) {
-                any_valid |= val[b] > 0.5f;
-                any_invalid |= !(val[b] > 0.5f);
+            int* from = nullptr;
+            if (valid_x || detect) {
+                from = (int*)talloc(nval[V] * 4);
+                if (!from) return fail(OCTMC_E_OOM, "out of device memory");
+                HIP_TRY(launch_nearest_valid(cval[V], nval[V], from, s));
             }
-            if (any_valid && any_invalid) {
-                for (int b = 0; b < nb; ++b) {
-                    if (val[b] > 0.5f) {
-                        from[b] = b;
-                        continue;
-                    }
-                    int best = -1;
-                    for (int dist = 1; dist < nb && best < 0; ++dist) {
-                        if (b - dist >= 0 && val[b - dist] > 0.5f) best = b - dist;
-                        else if (b + dist < nb && val[b + dist] > 0.5f) best = b + dist;
-                    }
-                    from[b] = best;
-                }
-                int* dfrom = (int*)talloc(nb * 4);
-                if (!dfrom) return fail(OCTMC_E_OOM, "out of device memory");
-                HIP_TRY(hipMemcpyAsync(dfrom, from.data(), nb * 4, hipMemcpyHostToDevice, s));
-                HIP_TRY(launch_copy_bscans(P->octa[V], w, h, d, dfrom, V, s));
-                HIP_TRY(hipStreamSynchronize(s));  // `from` is host memory
-            }
-            if (!have_enface && !project) HIP_TRY(launch_enface_mean(P->octa[V], (int)na, d, enf[V], s));
+            const bool mean = !have_enface && !project;
+            if (!host || from || mean)
+                HIP_TRY(launch_take_octa(src[V], P->octa[V], w, h, d, from, V, mean ? enf[V] : nullptr, s));
         }
     }
     if (have_enface) {
@@ -620,11 +600,6 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
     // pyramid: float32 at every level, stored in the storage type
     const float* cur[2] = {f32[0], f32[1]};
     float* cen[2] = {enf[0], enf[1]};
-    float *cvx = nullptr, *cvy = nullptr;
-    HIP_TRY(P->alloc(&cvx, h * 4));
-    HIP_TRY(P->alloc(&cvy, w * 4));
-    HIP_TRY(hipMemcpyAsync(cvx, hvx.data(), h * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(cvy, hvy.data(), w * 4, hipMemcpyHostToDevice, s));
     int lw = w, lh = h, ld = d;
     for (int l = 0; l < P->nlev; ++l) {
         Level& L = P->lev[l];
@@ -637,41 +612,51 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
         L.dp = storage_pitch(ld, P->dtype);
         const size_t lnv = (size_t)L.na * L.dp;
         L.vol_bytes = (uint32_t)(lnv * esize(P->dtype));
+        LevelJob job;
+        job.nvol = 2;
+        job.w = lw;
+        job.h = lh;
+        job.d = ld;
+        job.dp = L.dp;
+        const bool more = l + 1 < P->nlev, as_is = P->dtype == OCTMC_F32;
+        const int w2 = (lw + 1) / 2, h2 = (lh + 1) / 2, d2 = (ld + 1) / 2;
         void* st[2];
+        float *ne[2], *nval2[2];
         for (int V = 0; V < 2; ++V) {
-            HIP_TRY(P->alloc(&st[V], lnv * esize(P->dtype)));
-            HIP_TRY(launch_to_storage_pitched(cur[V], st[V], L.na, ld, L.dp, P->dtype, s));
+            job.in[V] = cur[V];
+            job.image[V] = cen[V];
+            job.valid[V] = cval[V];
+            job.nvalid[V] = V == 0 ? lh : lw;
+            if (as_is && l > 0) {  // the level's float32 volume is its storage
+                st[V] = const_cast<float*>(cur[V]);
+            } else {
+                HIP_TRY(P->alloc(&st[V], lnv * esize(P->dtype)));
+                job.store[V] = st[V];
+            }
+            if (more) {
+                const size_t bytes = (size_t)w2 * h2 * d2 * 4;
+                if (as_is) HIP_TRY(P->alloc(&job.next[V], bytes));
+                else job.next[V] = (float*)talloc(bytes);
+                if (!job.next[V]) return fail(OCTMC_E_OOM, "out of device memory (pyramid)");
+                HIP_TRY(P->alloc(&ne[V], (size_t)w2 * h2 * 4));
+                HIP_TRY(P->alloc(&nval2[V], (V == 0 ? h2 : w2) * 4));
+                job.next_image[V] = ne[V];
+                job.next_valid[V] = nval2[V];
+            }
         }
+        if (job.store[0] || more) HIP_TRY(launch_level(job, P->dtype, s));
         L.sx = st[0];
         L.sy = st[1];
         L.ax = cen[0];
         L.ay = cen[1];
-        L.vx = cvx;
-        L.vy = cvy;
-        if (l + 1 < P->nlev) {
-            const int w2 = (lw + 1) / 2, h2 = (lh + 1) / 2, d2 = (ld + 1) / 2;
-            float* nxt[2];
+        L.vx = cval[0];
+        L.vy = cval[1];
+        if (more) {
             for (int V = 0; V < 2; ++V) {
-                nxt[V] = (float*)talloc((size_t)w2 * h2 * d2 * 4);
-                if (!nxt[V]) return fail(OCTMC_E_OOM, "out of device memory (pyramid)");
-                HIP_TRY(launch_pyr3(cur[V], lw, lh, ld, nxt[V], s));
+                cur[V] = job.next[V];
+                cen[V] = ne[V];
+                cval[V] = nval2[V];
             }
-            float* ne[2];
-            for (int V = 0; V < 2; ++V) {
-                HIP_TRY(P->alloc(&ne[V], (size_t)w2 * h2 * 4));
-                HIP_TRY(launch_pyr2(cen[V], lw, lh, ne[V], s));
-            }
-            float *nvx, *nvy;
-            HIP_TRY(P->alloc(&nvx, h2 * 4));
-            HIP_TRY(P->alloc(&nvy, w2 * 4));
-            HIP_TRY(launch_pyr1(cvx, lh, nvx, s));
-            HIP_TRY(launch_pyr1(cvy, lw, nvy, s));
-            cur[0] = nxt[0];
-            cur[1] = nxt[1];
-            cen[0] = ne[0];
-            cen[1] = ne[1];
-            cvx = nvx;
-            cvy = nvy;
             lw = w2;
             lh = h2;
             ld = d2;
