@@ -9,6 +9,7 @@
 //   dz(f, b) = z_b + t_b (f - (n_f - 1) / 2),  dx = dy = 0,
 // with f the index along the fast axis and n_f the B-scan length.
 #include "octmc_internal.h"
+#include "row_quads.h"
 
 namespace octmc {
 namespace {
@@ -123,12 +124,18 @@ __global__ __launch_bounds__(256) void k_tilt_finish(const double* __restrict__ 
 
 // out(i, j, k) = I(vol, i, j, k + dz(i, j)): the cubic Hermite interpolator
 // with central-difference tangents (Catmull-Rom) along depth, tap indices
-// clamped to the A-scan.  One block per A-scan (its shift and taps are
-// uniform), threads along depth.
-__global__ __launch_bounds__(256) void k_resample_z(const float* __restrict__ vol, const float* __restrict__ dz, int d,
-                                                   float* __restrict__ out)
+// clamped to the A-scan.  Sixteen lanes take an A-scan (whose shift and taps are
+// theirs alike) and a lane four consecutive outputs at a time, from the seven
+// samples that their taps span: two 16-byte loads, four steps in flight.  Bound by
+// the memory: 500 x 500 x 800, 1.6 GB, 296 us, 5.4 TB/s (one block an A-scan, a sample a thread
+// and four loads each before: 441 us, 3.6 TB/s).
+__global__ __launch_bounds__(256) void k_resample_z(const float* __restrict__ vol, const float* __restrict__ dz, int na,
+                                                   int d, float* __restrict__ out)
 {
-    const size_t a = blockIdx.x;
+    constexpr int kLoads = kRowLoads / 2;  // of two quads each
+    const int part = threadIdx.x & (kRowLanes - 1);
+    const int a = (int)(blockIdx.x * (blockDim.x / kRowLanes) + threadIdx.x / kRowLanes);
+    if (a >= na) return;
     // integer and fractional parts of the shift taken apart so that the
     // fraction is exact (k + dz rounded in float32 would not be); beyond
     // +-(d + 2) every tap is clamped anyway
@@ -139,18 +146,49 @@ __global__ __launch_bounds__(256) void k_resample_z(const float* __restrict__ vo
     const float h00 = 2.0f * t3 - 3.0f * t2 + 1.0f, h10 = t3 - 2.0f * t2 + t;
     const float h01 = -2.0f * t3 + 3.0f * t2, h11 = t3 - t2;
     const float wt[4] = {-0.5f * h10, h00 - 0.5f * h11, h01 + 0.5f * h10, 0.5f * h11};
-    const float* __restrict__ col = vol + a * d;
-    float* __restrict__ o = out + a * d;
-    for (int k = threadIdx.x; k < d; k += blockDim.x) {
-        const int n = k + (int)fz;
-        float v = 0.0f;
+    const float* __restrict__ col = vol + (size_t)a * d;
+    float* __restrict__ o = out + (size_t)a * d;
+    const int shift = (int)fz - 1;  // first tap of output 0
+    for (int k0 = 0; k0 < d; k0 += kLoads * kRowStep) {
+        float v[kLoads][8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            int idx = n - 1 + e;
-            idx = idx < 0 ? 0 : (idx >= d ? d - 1 : idx);
-            v += wt[e] * col[idx];
+        for (int g = 0; g < kLoads; ++g) {
+            const int k = k0 + g * kRowStep + 4 * part, at = k + shift;
+            if (k0 + g * kRowStep >= d) break;
+            if (at >= 0 && at + 8 <= d) {
+                const quad_t x = *reinterpret_cast<const quad_t*>(col + at), y = *reinterpret_cast<const quad_t*>(col + at + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[g][e] = x[e];
+                    v[g][4 + e] = y[e];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int idx = at + e;
+                    v[g][e] = col[idx < 0 ? 0 : (idx >= d ? d - 1 : idx)];
+                }
+            }
         }
-        o[k] = v;
+#pragma unroll
+        for (int g = 0; g < kLoads; ++g) {
+            const int k = k0 + g * kRowStep + 4 * part;
+            if (k0 + g * kRowStep >= d) break;
+            float r[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                r[q] = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[q] += wt[e] * v[g][q + e];
+            }
+            if (k + 4 <= d) {
+                *reinterpret_cast<quad_t*>(o + k) = quad_t{r[0], r[1], r[2], r[3]};
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (k + q < d) o[k + q] = r[q];
+            }
+        }
     }
 }
 
@@ -184,8 +222,9 @@ hipError_t launch_tilt_finish(const double* theta, double* gtheta, int w, int h,
 hipError_t launch_resample_z(const float* vol, const float* dz, size_t na, int d, float* out, hipStream_t s)
 {
     if (na == 0 || d <= 0) return hipSuccess;
-    if (na > 0x7fffffffu) return hipErrorInvalidValue;  // one block per A-scan
-    hipLaunchKernelGGL(k_resample_z, dim3((unsigned)na), dim3(256), 0, s, vol, dz, d, out);
+    if (na > 0x7fffffffu) return hipErrorInvalidValue;
+    constexpr int rows = 256 / kRowLanes;
+    hipLaunchKernelGGL(k_resample_z, dim3((unsigned)((na + rows - 1) / rows)), dim3(256), 0, s, vol, dz, (int)na, d, out);
     return hipGetLastError();
 }
 
