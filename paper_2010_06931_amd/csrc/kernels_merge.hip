@@ -9,8 +9,9 @@
 //                   the OCTA weights are further multiplied by the resampled
 //                   validity (Eq. 5); where both vanish, OCT keeps the scan with
 //                   the lower density and OCTA is 0
-//   k_merge_volume  resample both scans with their fields (Eq. 2 interpolator,
-//                   value only) and write the weighted sum; k_merge_tile the
+//   k_merge_quads   resample both scans with their fields (Eq. 2 interpolator,
+//                   value only) and write the weighted sum (float32 volumes);
+//   k_merge_volume  the same of 16-bit volumes; k_merge_tile the
 //                   same on the matrix cores, for volumes of many A-scans
 #include <hip/hip_runtime.h>
 
@@ -139,11 +140,6 @@ __device__ __forceinline__ float ld<f16_t>(const void* p, size_t q)
 template <typename T>
 __device__ __forceinline__ float ldb(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff);
 template <>
-__device__ __forceinline__ float ldb<float>(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-}
-template <>
 __device__ __forceinline__ float ldb<bf16_t>(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
     return __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0) << 16);
@@ -235,8 +231,7 @@ __global__ __launch_bounds__(256) void k_merge_volume(const void* __restrict__ s
 // (tile_blend.h), L depths per lane.  k_merge_volume loads every column of a
 // tile up to four times, one sample per lane and load, and keeps the texture
 // path busy with that; here a tile's columns are loaded once, 16 bytes per lane.
-// 500 x 500 x 465: 1.50 -> 0.46 ms from BF16 volumes, 1.61 -> 0.84 ms from
-// float32 ones.
+// 500 x 500 x 465: 1.50 -> 0.46 ms from BF16 volumes.
 template <typename T, int L>
 __global__ __launch_bounds__(256, 3) void k_merge_tile(const void* __restrict__ sx, const void* __restrict__ sy,
                                                        const float* __restrict__ disp, const float4* __restrict__ wts,
@@ -319,6 +314,110 @@ __global__ __launch_bounds__(256, 3) void k_merge_tile(const void* __restrict__ 
         }
         groups = mx_next(groups, __ballot(bad != 0.f) != 0);
         if (!groups) return;
+    }
+}
+
+// float32 volumes, four samples a lane: k_merge_volume is bound by its loads, one of
+// 8.6 cycles of the CU's vector memory path per column and 61 outputs; a 16-byte one
+// takes 16.7 and serves 252.  A wave takes an A-scan and a workgroup 2 x 2 of them,
+// step by step together, so that the columns they share are still in the L1 when
+// the others read them; that takes all 16 loads of a scan in flight and no more than
+// four waves a SIMD, which the registers see to (500 x 500 x 465: 0.77 ms so, 0.93
+// with six, 1.15 with five, whose workgroups drift apart).  Lane l holds samples
+// base + 252 n + 4 l .. + 3; those outside the A-scan take the edge's value after the
+// blend (the loads stay inside).  Arithmetic and order are k_merge_volume's.  200 x
+// 200 x 300, both volumes: 367 us by k_merge_volume, 262 in a tile's distinct columns
+// on the matrix cores (where float32 runs at the vector rate), 231 so; 64 x 64 x 128
+// 51, -, 42.
+constexpr int kQuadStep = 252;
+
+__global__ __launch_bounds__(256, 4) void k_merge_quads(const float* __restrict__ sx, const float* __restrict__ sy,
+                                                     const float* __restrict__ disp, const float4* __restrict__ wts,
+                                                     int which, int w, int h, int d, uint32_t vol_bytes,
+                                                     float* __restrict__ out)
+{
+    typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
+    const int wv = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    // tiles in 8 bands of rows (one per XCD), swept column by column
+    const int tpr = (w + 1) >> 1, trows = (h + 1) >> 1, rpb = (trows + 7) >> 3;
+    const int t = xcd_block(blockIdx.x, gridDim.x), band = t / (rpb * tpr), tb = t - band * (rpb * tpr);
+    const int trow = band * rpb + tb % rpb;
+    if (t >= 8 * rpb * tpr || trow >= trows) return;  // whole block
+    const int i = 2 * (tb / rpb) + (wv & 1), j = 2 * trow + (wv >> 1);
+    const bool active = i < w && j < h;  // wave-uniform
+    const int na = w * h, a = uni(active ? j * w + i : 0);
+    const float4 wt = wts[a];
+    const float wgt[2] = {which ? wt.z : wt.x, which ? wt.w : wt.y};
+    const float* vol[2] = {sx, sy};
+    __amdgpu_buffer_rsrc_t rs[2];
+    uint32_t off[2][16];
+    float wl[2][16], wz[2][4];
+    int base[2];
+#pragma unroll
+    for (int V = 0; V < 2; ++V) {
+        rs[V] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vol[V]), (short)0, (int)vol_bytes, kRsrcWord3);
+        const float* dv = disp + ((size_t)V * na + a) * 3;
+        const float fxf = floorf(dv[0]), fyf = floorf(dv[1]), fzf = floorf(dv[2]);
+        const int nx = i + (int)fxf, ny = j + (int)fyf, nz = (int)fzf;
+        float wx[4], wy[4];
+        cr_w(dv[0] - fxf, wx);
+        cr_w(dv[1] - fyf, wy);
+        cr_w(dv[2] - fzf, wz[V]);
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                off[V][b * 4 + c] = (uint32_t)uni((int)((uint32_t)(clampi(ny - 1 + b, 0, h - 1) * w +
+                                                                   clampi(nx - 1 + c, 0, w - 1)) * (uint32_t)d * 4u));
+                wl[V][b * 4 + c] = wx[c] * wy[b];
+            }
+        base[V] = uni(min(max(nz, -kMxLimit), kMxLimit) - 1);
+    }
+    const int nsteps = (d + kQuadStep - 1) / kQuadStep;
+    for (int n = 0; n < nsteps; ++n) {
+        float res[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int V = 0; V < 2; ++V) {
+            const int m = base[V] + kQuadStep * n + 4 * lane, at = clampi(m, 0, d - 4);
+            quad_t x[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                x[q] = __builtin_bit_cast(quad_t, __builtin_amdgcn_raw_buffer_load_b128(rs[V], 4u * (uint32_t)at, off[V][q], 0));
+            float c[7] = {};
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) c[e] = fmaf(wl[V][q], x[q][e], c[e]);
+            if (base[V] + kQuadStep * n < 0 || base[V] + kQuadStep * n + 256 > d) {  // uniform
+                const float b0 = c[0], b1 = c[1], b2 = c[2], b3 = c[3];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int q = clampi(m + e, 0, d - 1) - at;
+                    c[e] = q <= 0 ? b0 : (q == 1 ? b1 : (q == 2 ? b2 : b3));
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 3; ++e) c[4 + e] = next_lane(c[e]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float iv = 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) iv = fmaf(wz[V][q], c[e + q], iv);
+                res[e] = fmaf(wgt[V], iv, res[e]);
+            }
+        }
+        const int k = kQuadStep * n + 4 * lane;
+        if (active && 4 * lane < kQuadStep && k < d) {
+            float* const o = out + (size_t)a * d + k;
+            if (k + 4 <= d) {
+                *reinterpret_cast<quad_t*>(o) = quad_t{res[0], res[1], res[2], res[3]};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (k + e < d) o[e] = res[e];
+            }
+        }
+        __builtin_amdgcn_s_barrier();
     }
 }
 
@@ -474,13 +573,24 @@ static hipError_t launch_merge_t(const void* vx, const void* vy, const float* di
     return hipGetLastError();
 }
 
+static hipError_t launch_merge_f32(const float* vx, const float* vy, const float* disp, const float4* wts, int which,
+                                   int w, int h, int d, int dp, float* out, hipStream_t s)
+{
+    const size_t bytes = (size_t)w * h * d * 4;
+    if (bytes >= (1ull << 31) || d < 4 || dp != d) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_merge_quads, dim3(struct_blocks(w, h)), dim3(256), 0, s, vx, vy, disp, wts, which, w, h, d,
+                       (uint32_t)bytes, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_merge_volume(const void* vx, const void* vy, octmc_dtype dt, const float* disp, const float4* wts,
                                int which, int w, int h, int d, int dp, float* out, hipStream_t s)
 {
     const bool eight = mx_eight(d, dp);
     switch (dt) {
     case OCTMC_F32:
-        return launch_merge_t<float, 4>(vx, vy, disp, wts, which, w, h, d, dp, out, s);
+        return launch_merge_f32(static_cast<const float*>(vx), static_cast<const float*>(vy), disp, wts, which, w, h, d, dp,
+                                out, s);
     case OCTMC_BF16:
         return eight ? launch_merge_t<bf16_t, 8>(vx, vy, disp, wts, which, w, h, d, dp, out, s)
                      : launch_merge_t<bf16_t, 4>(vx, vy, disp, wts, which, w, h, d, dp, out, s);
