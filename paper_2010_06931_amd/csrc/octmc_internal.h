@@ -133,10 +133,15 @@ struct StructJob {
     uint32_t vol_bytes; // bytes of one volume (buffer range)
     float eps_h;        // pseudo-Huber parameter (Eq. 4)
     int dp;             // storage pitch: samples between neighbouring A-scans' columns (d or d + 1)
+    // the sum of the displacements as part of this launch (step 0): nsum rows of
+    // block partials, none of them for nsum = 0 (and for the axial kernels)
+    double* sum_blk;
+    int nsum, sum_begin;
 };
 struct StructJobs {
     StructJob j[kMaxJobs];
     int n;
+    int sum_blocks;     // leading blocks of the grid, a multiple of 8
     const int* skip = nullptr;  // device flag: when nonzero the whole launch does nothing
 };
 // Blocks of one structural job: one 2 x 2 tile of A-scans per block, in 8
@@ -192,8 +197,7 @@ struct CombineJobs {
 hipError_t launch_sum(const SumJobs& jobs, int total_blocks, hipStream_t s);
 // axial: every displacement has dx = dy = 0 (stage 1); the kernels then read
 // the centre column alone and leave the x and y partials at 0
-hipError_t launch_struct(const StructJobs& jobs, int total_blocks, octmc_dtype dt, hipStream_t s,
-                         bool axial = false);
+hipError_t launch_struct(const StructJobs& jobs, octmc_dtype dt, hipStream_t s, bool axial = false);
 // per-A-scan combination and the fixed-order final sums.  Few A-scans take one
 // launch, with the displacement sum in it; the others launch_sum before it.
 // Evaluations of float32, 128 samples, as few / as many: 64 x 64 21.3 / 26.2 us,

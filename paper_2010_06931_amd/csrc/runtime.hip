@@ -107,7 +107,10 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
     sj.skip = tj.skip = cj.skip = ea[0].skip;
     for (int q = 1; q < n; ++q)
         if (ea[q].skip != ea[0].skip) return fail(OCTMC_E_INVALID, "grouped evaluations must share their skip flag");
-    int sb = 0, tb = 0;
+    int sb = 0;
+    bool axial = true;
+    for (int q = 0; q < n; ++q) axial &= ea[q].axial;
+    const bool fold = with_struct && !axial && !ev;
     EvalView views[kMaxJobs];
     for (int q = 0; q < n; ++q) {
         if (ea[q].view) {
@@ -137,11 +140,12 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
         const float* dy = ea[q].disp_y ? ea[q].disp_y : ea[q].disp + (size_t)L.na * 3;
         if (with_struct && dy != ea[q].disp + (size_t)L.na * 3)
             return fail(OCTMC_E_INVALID, "the structural kernels read both slots' fields as one [2][na][3] array");
-        if (nsum) sj.j[sj.n++] = SumJob{{ea[q].disp, dy}, V.sum_blk, L.na, sb, nsum};
+        // the sums go with the structural launch where that can take them (not between
+        // the events that time the two apart)
+        if (nsum && !fold) sj.j[sj.n++] = SumJob{{ea[q].disp, dy}, V.sum_blk, L.na, sb, nsum};
         sb += nsum;
-        tj.j[q] = StructJob{L.sx, L.sy, ea[q].disp, V.part, L.w, L.h, L.d, L.na, tb, L.vol_bytes,
-                            (float)pr.eps_huber, L.dp};
-        tb += struct_blocks(L.w, L.h);
+        tj.j[q] = StructJob{L.sx, L.sy, ea[q].disp, V.part, L.w, L.h, L.d, L.na, 0, L.vol_bytes,
+                            (float)pr.eps_huber, L.dp, V.sum_blk, fold ? nsum : 0, 0};
         const int blen = L.w;  // square scans: every B-scan has w A-scans
         const double f = std::floor(pr.flyback_frac * blen + 0.5);
         CombineJob c{};
@@ -181,9 +185,7 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
     if (ev) HIP_TRY(hipEventRecord(ev[0], s));
     if (sj.n) HIP_TRY(launch_sum(sj, sb, s));
     if (ev) HIP_TRY(hipEventRecord(ev[1], s));
-    bool axial = true;
-    for (int q = 0; q < n; ++q) axial &= ea[q].axial;
-    if (with_struct) HIP_TRY(launch_struct(tj, (tb + 7) / 8 * 8, dt, s, axial));  // multiple of the 8 XCDs
+    if (with_struct) HIP_TRY(launch_struct(tj, dt, s, axial));
     if (ev) HIP_TRY(hipEventRecord(ev[2], s));
     if (any_eta) {  // eta of the jobs that ask for it, before their evaluation
         CombineJobs c0{};
