@@ -319,11 +319,12 @@ __global__ __launch_bounds__(256, 3) void k_merge_tile(const void* __restrict__ 
 
 // float32 volumes, four samples a lane: k_merge_volume is bound by its loads, one of
 // 8.6 cycles of the CU's vector memory path per column and 61 outputs; a 16-byte one
-// takes 16.7 and serves 252.  A wave takes an A-scan and a workgroup 2 x 2 of them,
+// takes 16.7 and serves 252.  A wave takes an A-scan and a workgroup four in a row,
 // step by step together, so that the columns they share are still in the L1 when
 // the others read them; that takes all 16 loads of a scan in flight and no more than
-// four waves a SIMD, which the registers see to (500 x 500 x 465: 0.77 ms so, 0.93
-// with six, 1.15 with five, whose workgroups drift apart).  Lane l holds samples
+// four waves a SIMD, which the registers see to (500 x 500 x 465, 2 x 2 A-scans a
+// workgroup: 0.77 ms so, 0.93 with six, 1.15 with five, whose workgroups drift apart;
+// four in a row 0.74, 4 x 2 0.75, 4 x 4 0.84).  Lane l holds samples
 // base + 252 n + 4 l .. + 3; those outside the A-scan take the edge's value after the
 // blend (the loads stay inside).  Arithmetic and order are k_merge_volume's.  200 x
 // 200 x 300, both volumes: 367 us by k_merge_volume, 262 in a tile's distinct columns
@@ -338,13 +339,12 @@ __global__ __launch_bounds__(256, 4) void k_merge_quads(const float* __restrict_
 {
     typedef float quad_t __attribute__((ext_vector_type(4), aligned(4)));
     const int wv = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-    // tiles in 8 bands of rows (one per XCD), swept column by column
-    const int tpr = (w + 1) >> 1, trows = (h + 1) >> 1, rpb = (trows + 7) >> 3;
-    const int t = xcd_block(blockIdx.x, gridDim.x), band = t / (rpb * tpr), tb = t - band * (rpb * tpr);
-    const int trow = band * rpb + tb % rpb;
-    if (t >= 8 * rpb * tpr || trow >= trows) return;  // whole block
-    const int i = 2 * (tb / rpb) + (wv & 1), j = 2 * trow + (wv >> 1);
-    const bool active = i < w && j < h;  // wave-uniform
+    // 8 bands of rows (one per XCD), swept column by column
+    const int rpb = (h + 7) >> 3, per = rpb * ((w + 3) >> 2);
+    const int t = xcd_block(blockIdx.x, gridDim.x), band = t / per, tb = t - band * per;
+    const int i = 4 * (tb / rpb) + wv, j = band * rpb + tb % rpb;
+    if (j >= h) return;           // whole block
+    const bool active = i < w;  // wave-uniform
     const int na = w * h, a = uni(active ? j * w + i : 0);
     const float4 wt = wts[a];
     const float wgt[2] = {which ? wt.z : wt.x, which ? wt.w : wt.y};
@@ -578,7 +578,7 @@ static hipError_t launch_merge_f32(const float* vx, const float* vy, const float
 {
     const size_t bytes = (size_t)w * h * d * 4;
     if (bytes >= (1ull << 31) || d < 4 || dp != d) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_merge_quads, dim3(struct_blocks(w, h)), dim3(256), 0, s, vx, vy, disp, wts, which, w, h, d,
+    hipLaunchKernelGGL(k_merge_quads, dim3(8 * ((h + 7) / 8) * ((w + 3) / 4)), dim3(256), 0, s, vx, vy, disp, wts, which, w, h, d,
                        (uint32_t)bytes, out);
     return hipGetLastError();
 }
