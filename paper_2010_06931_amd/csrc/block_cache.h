@@ -1,14 +1,14 @@
 // Device blocks kept from one object or call for the next.
 //
-// A pair of 300 x 300 x 640 float32 scans takes 27 blocks, 1.1 GB together
+// A pair of 300 x 300 x 640 float32 scans takes some twenty blocks, about 1 GB together
 // (two more volumes where the inputs are on the host), and gives them back
 // when it is destroyed.  hipFree waits for the device and then costs 0.27 ms a
 // large block, and memory given back to the driver is cleared before it is
 // given out again: a program that creates one pair after another runs at the
 // clearing rate once the device's memory has been through it.  Kept blocks cost
 // neither: that pair, its evaluation at the coarser levels and its end take
-// 1.24 ms instead of 5.0 ms at first and 42 ms in the long run (the structural
-// inputs that are on the device are also read there and not copied any more).
+// 0.65 ms instead of 5.0 ms at first and 42 ms in the long run (1.24 ms before the
+// ingest was one kernel a level).
 //
 // One cache per device, shared by the contexts on it and by the objects that
 // hold blocks of it, and emptied with the last of them.  Only idle blocks come

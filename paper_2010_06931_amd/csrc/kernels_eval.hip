@@ -1,7 +1,8 @@
 // Hot-path kernels: one evaluation of the registration objective and its
 // gradient (Eqs. 1-10 of Ploner et al., without the stage-1 tilt term).
 //
-//   k_sum     sum of the displacements of both scans (mean term M)
+//   k_sum     sum of the displacements of both scans (mean term M); part of
+//             the launches of k_struct, k_struct2 and k_struct_mx otherwise
 //   k_struct  per output A-scan: resample both structural volumes with
 //             their displacement (Eq. 2), residual, pseudo-Huber loss (Eq. 4)
 //             and the depth sums of the loss and of its gradient with respect
@@ -9,7 +10,7 @@
 //             storage, and 16-bit volumes of odd depth in the caller's layout)
 //   k_struct2 the same with two 16-bit samples per lane (small levels: an odd
 //             depth is stored with one padding sample)
-//   k_struct_mx the same for 16-bit volumes of many A-scans, the lateral
+//   k_struct_mx the same for volumes of many A-scans, the lateral
 //             resampling on the matrix cores
 //   k_struct_multi, k_struct_multi1, k_multi_mx  the structural partials of
 //             every volume pair of n = 3 or 4 volumes, each volume resampled
@@ -17,7 +18,8 @@
 //   k_combine per output A-scan: en face residual (Eq. 7), resampled
 //             validity (Eq. 5), weight delta (Eq. 8), combination with eta
 //             (Eq. 9), scan-order regulariser, mean term, gradient; float64
-//             block partials
+//             block partials (k_combine_few: few A-scans, with the sums of the
+//             displacements and the final sums in the same launch)
 //   k_finalize the float64 global sums in a fixed order (one block per job;
 //             a kernel boundary, not a device-scope fence per block, makes
 //             the partials visible)
@@ -335,7 +337,7 @@ __device__ __forceinline__ void sum_block(const float* __restrict__ dx, const fl
 
 // The first blocks of a structural launch sum the displacements of its jobs (a
 // multiple of the 8 XCDs, so that the others stay where they were): a launch less,
-// 4.8 of 77 us for 251 x 251 x 233 BF16.
+// 4.8 of 81 us for 251 x 251 x 233 BF16.
 __device__ __forceinline__ bool struct_sums(const StructJobs& jobs)
 {
     const int b = blockIdx.x;
@@ -827,14 +829,19 @@ __device__ __forceinline__ void mx_depth(MxSums& A, const float (&x)[L + 3], con
 // step of a tile are 16 of 1 KB here.  500 x 500 x 800 in BF16: 1.058 -> 0.563
 // ms (68 TFLOP/s of the method's operations), 500 x 500 x 465 in FP16: 0.645 ->
 // 0.367, 300 x 300 x 233 in BF16 0.160 -> 0.092 ms.
+// float32 (four depths a lane): bound by its matrix products, 56 to 64 of 32 cycles
+// a step, and some 290 vector instructions, which do not overlap; four waves per
+// SIMD.  500 x 500 x 800 1.60 -> 1.19 ms (32 TFLOP/s), 300 x 300 x 640 0.464 -> 0.418
+// (with the fours of slots without a column multiplied too 0.434).
 template <typename T, int L>
 __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
 {
     if (jobs.skip && *jobs.skip) return;
     if (struct_sums(jobs)) return;
-    __shared__ MxLds<2, 2, L> lds[4];
+    constexpr int kEs = (int)esize<T>::v;
+    __shared__ MxLds<kEs, 2, L> lds[4];
     const int wv = uni((int)(threadIdx.x >> 6));
-    MxLds<2, 2, L>& M = lds[wv];
+    MxLds<kEs, 2, L>& M = lds[wv];
     const int lb = xcd_block((int)blockIdx.x - jobs.sum_blocks, (int)gridDim.x - jobs.sum_blocks);
     int jid = -1;
     for (int q = 0; q < jobs.n; ++q)
@@ -848,7 +855,7 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.sx), (short)0, (int)J.vol_bytes, kRsrcWord3);
     const __amdgpu_buffer_rsrc_t ry =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(J.sy), (short)0, (int)J.vol_bytes, kRsrcWord3);
-    typedef MxGeo<2, L> Geo;
+    typedef MxGeo<kEs, L> Geo;
     const float eps = J.eps_h;
     const float inv_eps = 1.0f / J.eps_h;
     // The groups of the tile evaluated together: all four; two where the four
@@ -888,7 +895,7 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
                 mx_load(qy, SY, M, 1, ry, s, dp, lane);
                 float v[3][L];
                 f32x4 D[L] = {};
-                mx_blend<T>(D, qx, M, 0, lane);
+                mx_blend<T>(D, qx, M, 0, lane, SX.ns);
                 if (SX.ns > 32) mx_rest<T>(D, SX, M, 0, rx, s, dp, lane);
                 mx_rows<false>(v, D, SX, M, s, dp, lane);
 #pragma unroll
@@ -898,7 +905,7 @@ __global__ __launch_bounds__(256, 3) void k_struct_mx(const StructJobs jobs)
                     xy[i] = v[2][i];
                 }
                 f32x4 E[L] = {};
-                mx_blend<T>(E, qy, M, 1, lane);
+                mx_blend<T>(E, qy, M, 1, lane, SY.ns);
                 if (SY.ns > 32) mx_rest<T>(E, SY, M, 1, ry, s, dp, lane);
                 mx_rows<true>(v, E, SY, M, s, dp, lane);
 #pragma unroll
@@ -1276,8 +1283,8 @@ __device__ __forceinline__ void own_sums(const CombineJob& J, double (&v)[4])
 // displacements for itself and the last one done forms the final sums.  64 x 64
 // x 128 float32: displacement sum, combination and final sums 18.5 us in three
 // launches, 10.6 in one (the block's count with its release and acquire 1.6 of
-// them, which is why many A-scans keep three launches: with the count 12 us
-// more at 1000 blocks).
+// them, and 12 with 1000 blocks, which is why many A-scans keep a launch for the
+// final sums).
 __global__ __launch_bounds__(kRedBlock) void k_combine_few(const CombineJobs jobs)
 {
     __shared__ double shd[kRedBlock / 64][4];
@@ -1900,6 +1907,20 @@ static int struct_form(const StructJob& J, bool axial)
     return mx_eight(J.d, J.dp) ? kByMx8 : kByMx4;
 }
 
+// float32 jobs likewise.  Its matrix products run at the vector units' expense, so
+// k_struct_mx needs more tiles to pay, and depths whose steps are no more than those
+// of k_struct's 61 outputs (one step costs 0.82 .. 0.92 of k_struct's from 200 x 200
+// A-scans on, as much at 180 x 180 and more below): 200 x 200 x 512 172 -> 158 us,
+// 224 x 224 x 512 205 -> 173, 300 x 300 x 640 464 -> 418, 500 x 500 x 800 1600 ->
+// 1189; 200 x 200 x 300 (6 steps to 5) 101 against 114, 251 x 251 x 233 (5 to 4) 124
+// against 128, 172 x 172 x 555 141 against 150.
+constexpr int kMxMinAscansF32 = 40000;
+static bool struct_f32_mx(const StructJob& J)
+{
+    constexpr int out = MxGeo<4, 4>::kOut, out1 = kOutPerStep;
+    return J.na >= kMxMinAscansF32 && J.dp >= 4 && 7 * ((J.d + out - 1) / out) <= 8 * ((J.d + out1 - 1) / out1);
+}
+
 // The jobs of one kernel's launch, and its blocks: first those of the displacement
 // sums that the jobs ask for, then the jobs' own.
 struct StructLaunch {
@@ -1948,11 +1969,19 @@ static hipError_t launch_struct_t(const StructJobs& jobs, octmc_dtype dt, hipStr
 {
     switch (dt) {
     case OCTMC_F32: {
-        StructLaunch all;
-        for (int q = 0; q < jobs.n; ++q) all.add(jobs.j[q], struct_blocks(jobs.j[q].w, jobs.j[q].h));
-        all.jobs.skip = jobs.skip;
-        const dim3 grid = all.grid();
-        hipLaunchKernelGGL((k_struct<float, AXIAL>), grid, dim3(256), 0, s, all.jobs);
+        StructLaunch part[2];
+        for (int q = 0; q < jobs.n; ++q) {
+            const StructJob& J = jobs.j[q];
+            const int k = !AXIAL && struct_f32_mx(J);
+            part[k].add(J, k ? struct_mx_blocks(J.w, J.h) : struct_blocks(J.w, J.h));
+        }
+        for (StructLaunch& P : part) P.jobs.skip = jobs.skip;
+        if constexpr (!AXIAL) {
+            const dim3 grid = part[1].grid();
+            if (part[1].jobs.n) hipLaunchKernelGGL((k_struct_mx<float, 4>), grid, dim3(256), 0, s, part[1].jobs);
+        }
+        const dim3 grid = part[0].grid();
+        if (part[0].jobs.n) hipLaunchKernelGGL((k_struct<float, AXIAL>), grid, dim3(256), 0, s, part[0].jobs);
         return hipGetLastError();
     }
     case OCTMC_BF16:

@@ -78,17 +78,21 @@ __device__ __forceinline__ float row_shr_add(float v)
 // set of displacements is served: 32 slots take one matrix product per depth
 // tile, up to 48 a second one, and a tile with more (disjoint stencils) is
 // served two A-scans at a time.
-// The products are v_mfma_f32_16x16x32 on the samples of 16-bit storage.  The
-// float32 weights enter as three 16-bit parts, each the rest rounded to nearest,
-// whose sum is the weight exactly (BF16: three times 8 bits; FP16: 11 + 11 + 2
-// bits of the weight times 2^12, undone in the depth taps), so the products are
-// those of a float32 blend and no sample is converted.  The trailing parts are
-// summed first, so that few additions round at the blend's full size (error of a
-// merged 200 x 200 x 300 volume against 64 bits: 6.1e-8, leading parts first
-// 7.6e-8, vector FMAs 7.5e-8).  Splitting by truncation instead would bias S_str by
-// -2.6e-8: an addend smaller than the products it is added to is truncated.
-// (Matrix products of float32 run on the vector units, timed: no overlap with
-// vector instructions.  float32 volumes have kernels without them.)
+//   16-bit storage: v_mfma_f32_16x16x32 on the stored samples.  The float32
+//     weights enter as three 16-bit parts, each the rest rounded to nearest,
+//     whose sum is the weight exactly (BF16: three times 8 bits; FP16: 11 + 11 +
+//     2 bits of the weight times 2^12, undone in the depth taps), so the
+//     products are those of a float32 blend and no sample is converted.  The
+//     trailing parts are summed first, so that few additions round at the
+//     blend's full size (error of a merged 200 x 200 x 300 volume against 64
+//     bits: 6.1e-8, leading parts first 7.6e-8, vector FMAs 7.5e-8).  Splitting
+//     by truncation instead would bias S_str by -2.6e-8: an addend smaller than
+//     the products it is added to is truncated.
+//   float32 storage: v_mfma_f32_16x16x4_f32, four slots at a time and none for
+//     fours without a column.  These run on the vector units (timed: no overlap
+//     with vector instructions), at twice their rate.  The last slots first: in
+//     their order the error of a merged 300 x 300 x 300 volume is 7.6e-8,
+//     reversed 7.3e-8, of vector FMAs 7.5e-8.
 constexpr int kMxSlots = 48;
 constexpr int kMxRest = 2;  // volumes of a tile that may have more than 32 slots
 constexpr int kMxLimit = 1 << 28;  // positions beyond this lie outside every volume
@@ -155,6 +159,18 @@ __device__ __forceinline__ void mx_pack(const S (&v)[NQ], int p, B& b0, B& b1)
 }
 
 template <>
+struct MxOps<float> {
+    static constexpr float kUnscale = 1.f;
+    typedef float part;
+    static constexpr int kParts = 1;
+    static __device__ __forceinline__ void split_weight(float w, part (&p)[1]) { p[0] = w; }
+    static __device__ __forceinline__ f32x4 mfma(int a, int b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b), c, 0, 0, 0);
+    }
+};
+
+template <>
 struct MxOps<bf16_t> {
     static constexpr float kUnscale = 1.f;
     typedef unsigned short part;
@@ -210,12 +226,24 @@ struct MxOps<f16_t> {
     }
 };
 
+// The weights' arrays: of slot 4 q + kg, row m is element q (float32: q % 4 of
+// array q / 4) of lane 16 kg + m.
+template <int ES>
+struct MxArr {  // 16-bit: one array per part
+    static constexpr int kMain = 3, kRest = 3;
+    typedef i32x2 rest_t;
+};
+template <>
+struct MxArr<4> {
+    static constexpr int kMain = 2, kRest = 1;
+    typedef i32x4 rest_t;
+};
+
 // Per-wave LDS, for N volumes.
 template <int ES, int N, int L>
 struct MxLds {
-    // the weights' parts: of slot 4 q + kg, row m is element q of lane 16 kg + m
-    i32x4 a[N][3][64];           // of a volume's slots 0 .. 31
-    i32x2 rest[kMxRest][3][64];  // of slots 32 .. 47, for the volumes that have them
+    i32x4 a[N][MxArr<ES>::kMain][64];  // weights of a volume's slots 0 .. 31
+    typename MxArr<ES>::rest_t rest[kMxRest][MxArr<ES>::kRest][64];  // of slots 32 .. 47, for the volumes that have them
     float edge[L][64];
     int2 key[N][64];     // per slot: byte offset of the column, first source depth of the window
     i32x4 off[N][4][2];  // [kg][q]: slot 4 q + kg, the column's byte offset at the tile's first window start, zlo
@@ -281,6 +309,7 @@ __device__ __forceinline__ bool mx_setup(MxScan& S, MxLds<(int)esize<T>::v, N, L
 {
     typedef MxGeo<(int)esize<T>::v, L> Geo;
     typedef MxOps<T> Ops;
+    typedef MxArr<Geo::es> Arr;
     const int g = lane >> 4, n = lane & 15;
     int nx, ny, nz;
     float tx, ty, tz;
@@ -345,10 +374,10 @@ __device__ __forceinline__ bool mx_setup(MxScan& S, MxLds<(int)esize<T>::v, N, L
     // weights: 0 but for the rows of an A-scan in the slots of its columns.
     // Unused slots: an offset beyond the volume, whose loads return 0.
 #pragma unroll
-    for (int k = 0; k < Ops::kParts; ++k) M.a[V][k][lane] = i32x4{};
+    for (int k = 0; k < Arr::kMain; ++k) M.a[V][k][lane] = i32x4{};
     if (S.ns > 32) {
 #pragma unroll
-        for (int k = 0; k < Ops::kParts; ++k) M.rest[S.rest][k][lane] = i32x2{};
+        for (int k = 0; k < Arr::kRest; ++k) M.rest[S.rest][k][lane] = typename Arr::rest_t{};
     }
     M.key[V][lane] = make_int2((int)0x80000000u, (int)0x80000000u);
     int* const off = reinterpret_cast<int*>(&M.off[V][0][0]);
@@ -376,8 +405,8 @@ __device__ __forceinline__ bool mx_setup(MxScan& S, MxLds<(int)esize<T>::v, N, L
         const float wt[3] = {vx * vy, gx * vy, vx * gy};
         const int q = (slot & 31) >> 2, row = 16 * (slot & 3) + 4 * g;
         typedef typename Ops::part part;
-        constexpr int kEl = 8, kEl1 = 4;  // parts of a lane of both arrays
-        part* a0 = reinterpret_cast<part*>(&M.a[V][0][0]) + row * kEl + q;
+        constexpr int kEl = 16 / (int)sizeof(part), kEl1 = (int)(sizeof(typename Arr::rest_t) / sizeof(part));
+        part* a0 = reinterpret_cast<part*>(&M.a[V][0][0]) + (q / kEl * 64 + row) * kEl + q % kEl;
         part* a1 = reinterpret_cast<part*>(&M.rest[S.rest][0][0]) + row * kEl1 + q % kEl1;
         part p[NOUT][Ops::kParts];
 #pragma unroll
@@ -432,30 +461,40 @@ __device__ __forceinline__ void mx_load(typename MxDwords<L * ES / 4>::type (&s)
     for (int q = 0; q < 8; ++q) s[q] = MxDwords<Geo::kDw>::load(r, off[q], 0);
 }
 
-// D += the blends of NQ slots per lane group, whose samples are s: a, their weights' arrays
+// D += the blends of NQ slots per lane group, whose samples are s: a, their weights' arrays; ns of the slots hold columns
 template <typename T, int NQ, int L, typename S, typename A>
-__device__ __forceinline__ void mx_mul(f32x4 (&D)[L], const S (&s)[NQ], const A* a, int lane)
+__device__ __forceinline__ void mx_mul(f32x4 (&D)[L], const S (&s)[NQ], const A* a, int lane, int ns)
 {
     typedef MxOps<T> Ops;
-    const A a0 = a[lane], a1 = a[64 + lane], a2 = a[128 + lane];
+    if constexpr (esize<T>::v == 4) {
 #pragma unroll
-    for (int p = 0; p < L / 2; ++p) {
-        A b0, b1;
-        mx_pack(s, p, b0, b1);
-        D[2 * p] = Ops::mfma(a2, b0, D[2 * p]);
-        D[2 * p + 1] = Ops::mfma(a2, b1, D[2 * p + 1]);
-        D[2 * p] = Ops::mfma(a1, b0, D[2 * p]);
-        D[2 * p + 1] = Ops::mfma(a1, b1, D[2 * p + 1]);
-        D[2 * p] = Ops::mfma(a0, b0, D[2 * p]);
-        D[2 * p + 1] = Ops::mfma(a0, b1, D[2 * p + 1]);
+        for (int q = NQ - 1; q >= 0; --q) {  // the outer columns of most A-scans, then the inner ones
+            if (4 * q >= ns) continue;
+            const int w = a[(q >> 2) * 64 + lane][q & 3];
+#pragma unroll
+            for (int i = 0; i < L; ++i) D[i] = Ops::mfma(w, s[q][i], D[i]);
+        }
+    } else {
+        const A a0 = a[lane], a1 = a[64 + lane], a2 = a[128 + lane];
+#pragma unroll
+        for (int p = 0; p < L / 2; ++p) {
+            A b0, b1;
+            mx_pack(s, p, b0, b1);
+            D[2 * p] = Ops::mfma(a2, b0, D[2 * p]);
+            D[2 * p + 1] = Ops::mfma(a2, b1, D[2 * p + 1]);
+            D[2 * p] = Ops::mfma(a1, b0, D[2 * p]);
+            D[2 * p + 1] = Ops::mfma(a1, b1, D[2 * p + 1]);
+            D[2 * p] = Ops::mfma(a0, b0, D[2 * p]);
+            D[2 * p + 1] = Ops::mfma(a0, b1, D[2 * p + 1]);
+        }
     }
 }
 
 // D += the blends of slots 0 .. 31 of volume V, whose samples are s
 template <typename T, int ES, int N, int L, typename S>
-__device__ __forceinline__ void mx_blend(f32x4 (&D)[L], const S (&s)[8], const MxLds<ES, N, L>& M, int V, int lane)
+__device__ __forceinline__ void mx_blend(f32x4 (&D)[L], const S (&s)[8], const MxLds<ES, N, L>& M, int V, int lane, int ns = 32)
 {
-    mx_mul<T, 8>(D, s, &M.a[V][0][0], lane);
+    mx_mul<T, 8>(D, s, &M.a[V][0][0], lane, ns);
 }
 
 // D += the blends of slots 32 .. 47 (only where a tile has them)
@@ -471,7 +510,7 @@ __device__ __forceinline__ void mx_rest(f32x4 (&D)[L], const MxScan& S, const Mx
         const int2 k = M.key[V][32 + 4 * q + kg];
         s[q] = MxDwords<Geo::kDw>::load(r, (uint32_t)k.x + (uint32_t)ES * (uint32_t)min(max(k.y + z0 + L * n, 0), dp - L), 0);
     }
-    mx_mul<T, 4>(D, s, &M.rest[S.rest][0][0], lane);
+    mx_mul<T, 4>(D, s, &M.rest[S.rest][0][0], lane, S.ns - 32);
 }
 
 // L samples read at clamp(m, 0, dp - L), moved to m .. m + L - 1 with the edge

@@ -69,6 +69,8 @@ def _eval(octmc, n, d, dtype, S, A, V, D):
     (91, 122, "bf16", "noise"), (92, 123, "f16", "noise"), (93, 244, "bf16", "apart"), (94, 245, "f16", "depth"),
     (91, 58, "bf16", "apart"), (93, 59, "f16", "noise"), (91, 117, "bf16", "depth"), (92, 233, "bf16", "shift"),
     (91, 4, "bf16", "noise"), (91, 7, "f16", "depth"), (91, 8, "bf16", "apart"), (95, 465, "bf16", "noise"),
+    (200, 4, "f32", "noise"), (201, 58, "f32", "apart"), (203, 62, "f32", "depth"), (200, 116, "f32", "shift"),
+    (201, 174, "f32", "noise"),
 ])
 def test_parity(octmc, n, d, dtype, case):
     log(f"matrix-core structural kernel n={n} d={d} {dtype} {case}")
