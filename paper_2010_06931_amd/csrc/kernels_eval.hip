@@ -7,14 +7,14 @@
 //             their displacement (Eq. 2), residual, pseudo-Huber loss (Eq. 4)
 //             and the depth sums of the loss and of its gradient with respect
 //             to the A-scan's displacement; one depth sample per lane (float32
-//             storage, and 16-bit volumes of odd depth in the caller's layout)
+//             storage, and 16-bit volumes of odd depth in the caller's layout; fewer A-scans)
 //   k_struct2 the same with two 16-bit samples per lane (small levels: an odd
 //             depth is stored with one padding sample)
 //   k_struct_mx the same for volumes of many A-scans, the lateral
 //             resampling on the matrix cores
 //   k_struct_multi, k_struct_multi1, k_multi_mx  the structural partials of
 //             every volume pair of n = 3 or 4 volumes, each volume resampled
-//             once (16-bit, float32, many A-scans of 16-bit)
+//             once (16-bit, float32, many A-scans; the last not for three of float32)
 //   k_combine per output A-scan: en face residual (Eq. 7), resampled
 //             validity (Eq. 5), weight delta (Eq. 8), combination with eta
 //             (Eq. 9), scan-order regulariser, mean term, gradient; float64
@@ -1622,7 +1622,7 @@ __global__ __launch_bounds__(256) void k_struct_multi(const StructMultiJob<N> J)
     }
 }
 
-// k_multi_mx: k_struct_multi on the matrix cores (16-bit storage), with the
+// k_multi_mx: k_struct_multi and k_struct_multi1 on the matrix cores, with the
 // tiles, set-up and layout of k_struct_mx.  Every volume's blends are moved to
 // the positions of the first volume's; a lane then holds the value and the x, y,
 // z derivatives of all N volumes at four depths (four rather than eight, since
@@ -1632,17 +1632,19 @@ __global__ __launch_bounds__(256) void k_struct_multi(const StructMultiJob<N> J)
 // Two waves per SIMD (256 registers); the depth taps and the column offsets are
 // read from the LDS at each step, which leaves registers to load one volume
 // ahead.  Four volumes of 300 x 300 x 640 in BF16: 1230 -> 850 us per
-// evaluation (1013 without loading ahead, 880 with the offsets in registers).
+// evaluation (1013 without loading ahead, 880 with the offsets in registers); in
+// float32, whose matrix products take the vector units' time, 1521 -> 1318.
 template <typename T, int N>
 __global__ __launch_bounds__(256, 2) void k_multi_mx(const StructMultiJob<N> J)
 {
     if (J.skip && *J.skip) return;
     constexpr int NP = N * (N - 1) / 2, L = 4;
-    typedef MxGeo<2, L> Geo;
-    __shared__ MxLds<2, N, L> lds[4];
+    constexpr int kEs = (int)esize<T>::v;
+    typedef MxGeo<kEs, L> Geo;
+    __shared__ MxLds<kEs, N, L> lds[4];
     __shared__ f32x4 taps[4][N][4][2];  // per wave, volume and A-scan: the depth taps and their derivatives
     const int wv = uni((int)(threadIdx.x >> 6));
-    MxLds<2, N, L>& M = lds[wv];
+    MxLds<kEs, N, L>& M = lds[wv];
     const int w = J.w, h = J.h, d = J.d, dp = J.dp;
     int i0, j0;
     if (!mx_tile(w, h, xcd_block(blockIdx.x, gridDim.x), wv, i0, j0)) return;
@@ -1699,7 +1701,7 @@ __global__ __launch_bounds__(256, 2) void k_multi_mx(const StructMultiJob<N> J)
                 else if (s + 1 < nsteps) mx_load(next, S[0], M, 0, rs[0], s + 1, dp, lane);
                 __builtin_amdgcn_sched_barrier(0);
                 f32x4 D[L] = {};
-                mx_blend<T>(D, q, M, V, lane);
+                mx_blend<T>(D, q, M, V, lane, S[V].ns);
                 if (S[V].ns > 32) mx_rest<T>(D, S[V], M, V, rs[V], s, dp, lane);
                 float v[3][L];
                 if (V == 0) mx_rows<false>(v, D, S[V], M, s, dp, lane);
@@ -1915,10 +1917,10 @@ static int struct_form(const StructJob& J, bool axial)
 // 1189; 200 x 200 x 300 (6 steps to 5) 101 against 114, 251 x 251 x 233 (5 to 4) 124
 // against 128, 172 x 172 x 555 141 against 150.
 constexpr int kMxMinAscansF32 = 40000;
-static bool struct_f32_mx(const StructJob& J)
+static bool f32_mx(int na, int d, int dp)
 {
     constexpr int out = MxGeo<4, 4>::kOut, out1 = kOutPerStep;
-    return J.na >= kMxMinAscansF32 && J.dp >= 4 && 7 * ((J.d + out - 1) / out) <= 8 * ((J.d + out1 - 1) / out1);
+    return na >= kMxMinAscansF32 && dp >= 4 && 7 * ((d + out - 1) / out) <= 8 * ((d + out1 - 1) / out1);
 }
 
 // The jobs of one kernel's launch, and its blocks: first those of the displacement
@@ -1972,7 +1974,7 @@ static hipError_t launch_struct_t(const StructJobs& jobs, octmc_dtype dt, hipStr
         StructLaunch part[2];
         for (int q = 0; q < jobs.n; ++q) {
             const StructJob& J = jobs.j[q];
-            const int k = !AXIAL && struct_f32_mx(J);
+            const int k = !AXIAL && f32_mx(J.na, J.d, J.dp);
             part[k].add(J, k ? struct_mx_blocks(J.w, J.h) : struct_blocks(J.w, J.h));
         }
         for (StructLaunch& P : part) P.jobs.skip = jobs.skip;
@@ -2024,7 +2026,10 @@ hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s)
 // k_multi_mx with fewer A-scans than this leaves the device's registers and LDS
 // (two workgroups per CU) without tiles: four volumes of 96 x 96 x 200 in BF16
 // 99 against k_struct_multi's 87 us per evaluation, 128 x 128 x 256 141 against
-// 153.
+// 153.  Four volumes in float32 take it where two do: 200 x 200 x 512 589 -> 519 us,
+// 300 x 300 x 640 1521 -> 1318; 160 x 160 x 200 187 against 207, 181 x 181 x 300 (6
+// steps to 5) 282 against 322.  Three stay with k_struct_multi1, which has the
+// registers for them: 200 x 200 x 512 302 against 342, 300 x 300 x 640 833 against 870.
 constexpr int kMxMultiMinAscans = 16384;
 template <int N>
 static hipError_t launch_struct_multi_n(const void* const* vol, const float* disp, float* const* part, int w, int h,
@@ -2045,6 +2050,11 @@ static hipError_t launch_struct_multi_n(const void* const* vol, const float* dis
     J.eps_h = eps_h;
     const int blocks = (struct_blocks(w, h) + 7) / 8 * 8;  // a multiple of the 8 XCDs
     const int mx = struct_mx_blocks(w, h);
+    if constexpr (N == 4)
+        if (dt == OCTMC_F32 && f32_mx(J.na, d, dp)) {
+            hipLaunchKernelGGL((k_multi_mx<float, N>), dim3(mx), dim3(256), 0, s, J);
+            return hipGetLastError();
+        }
     if (dt == OCTMC_F32)
         hipLaunchKernelGGL((k_struct_multi1<N>), dim3(blocks), dim3(256), 0, s, J);
     else if (J.na >= kMxMultiMinAscans && dt == OCTMC_BF16)

@@ -114,7 +114,7 @@ def test_not_finite_stays_local(octmc, value):
 
 @pytest.mark.parametrize("n,d,dtype,count,case", [
     (91, 58, "bf16", 3, "noise"), (92, 59, "f16", 4, "depth"), (93, 117, "bf16", 4, "apart"), (91, 4, "f16", 3, "depth"),
-    (94, 130, "bf16", 4, "noise"),
+    (94, 130, "bf16", 4, "noise"), (200, 58, "f32", 4, "noise"), (201, 62, "f32", 4, "apart"), (203, 4, "f32", 4, "depth"),
 ])
 def test_parity_multi(octmc, n, d, dtype, count, case):
     log(f"matrix-core structural kernel of {count} volumes n={n} d={d} {dtype} {case}")
