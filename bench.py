@@ -384,7 +384,7 @@ def _rms_px(a, b):
 def clinical_bench(octmc, torch, log, steps=200, warmup=20, cpu=True):
     """The clinical workload (300 x 300 A-scans x 640 samples, float32
     storage): evaluations per second of the full objective and gradient at
-    the finest level, the structural kernel (k_struct<float>) against its
+    the finest level, the structural kernel (k_struct_mx<float, 4>) against its
     roofs, and full solves at the workload's 4 levels and at the automatic
     depth: time, gauge-free error against ground truth, and distance to the
     FP64 oracle's solve of the same inputs (stored)."""
@@ -418,7 +418,7 @@ def clinical_bench(octmc, torch, log, steps=200, warmup=20, cpu=True):
            "evals_per_s": round(1000.0 / ms, 2), "ms_per_eval": round(ms, 5),
            "hbm_GBps_algorithmic_eval": round(alg / (ms * 1e-3) / 1e9, 1),
            "kernel_ms": {"sum": round(st[0], 5), "struct": round(st[1], 5), "combine": round(st[2], 5)},
-           "roofline_struct": {"kernel": "k_struct<float>", "algorithmic_bytes": alg,
+           "roofline_struct": {"kernel": "k_struct_mx<float, 4>", "algorithmic_bytes": alg,
                                "hbm": {"achieved": round(hbm, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                        "frac": round(hbm / HBM_PEAK_GBS, 4)},
                                "alu": {"achieved": round(tfl, 2), "peak": round(VALU_PEAK_TFLOPS, 1),
