@@ -161,32 +161,21 @@ __device__ __forceinline__ float next_lane(float v)
 // blended values of lanes l .. l + 3.
 constexpr int kMergeStep = 61;
 
-// one wavefront per output A-scan, lanes along depth; which = 0 uses the OCT
-// weights (wts.x, wts.y), which = 1 the OCTA weights (wts.z, wts.w).  The 16
-// lateral columns of each scan are read with 32-bit buffer offsets (their
+// One output A-scan (a at i, j) by one wave, lanes along depth, from volumes of dp
+// samples a column (the first d are the A-scan); wt: the weights of the two scans.
+// The 16 lateral columns of each scan are read with 32-bit buffer offsets (their
 // offsets and weights wave-uniform), each source sample once per step.
 template <typename T>
-__global__ __launch_bounds__(256) void k_merge_volume(const void* __restrict__ sx, const void* __restrict__ sy,
-                                                      const float* __restrict__ disp, const float4* __restrict__ wts,
-                                                      int which, int w, int h, int d, int dp, uint32_t vol_bytes,
-                                                      float* __restrict__ out)
+__device__ __forceinline__ void merge_ascan(const __amdgpu_buffer_rsrc_t (&rs)[2], const float* __restrict__ disp, int a,
+                                            int i, int j, const float (&wgt)[2], int w, int h, int d, int dp, int lane,
+                                            float* __restrict__ out)
 {
-    // sx, sy: [h][w] columns of dp samples (the first d are the A-scan); out: [h][w][d]
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int na = w * h;
-    const int a = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wv);
-    if (a >= na) return;
-    const int i = a % w, j = a / w;
-    const float4 wt = wts[a];
-    const float wgt[2] = {which ? wt.z : wt.x, which ? wt.w : wt.y};
-    const void* vol[2] = {sx, sy};
-    __amdgpu_buffer_rsrc_t rs[2];
     uint32_t off[2][16];
     float wl[2][16], wz[2][4];
     int base[2];
 #pragma unroll
     for (int V = 0; V < 2; ++V) {
-        rs[V] = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(vol[V]), (short)0, (int)vol_bytes, 0x00020000);
         const float* dv = disp + ((size_t)V * na + a) * 3;
         const float fxf = floorf(dv[0]), fyf = floorf(dv[1]), fzf = floorf(dv[2]);
         const int nx = i + (int)fxf, ny = j + (int)fyf, nz = (int)fzf;
@@ -227,11 +216,32 @@ __global__ __launch_bounds__(256) void k_merge_volume(const void* __restrict__ s
     }
 }
 
+// one wavefront per output A-scan; which = 0 uses the OCT weights (wts.x, wts.y),
+// which = 1 the OCTA weights (wts.z, wts.w)
+template <typename T>
+__global__ __launch_bounds__(256) void k_merge_volume(const void* __restrict__ sx, const void* __restrict__ sy,
+                                                      const float* __restrict__ disp, const float4* __restrict__ wts,
+                                                      int which, int w, int h, int d, int dp, uint32_t vol_bytes,
+                                                      float* __restrict__ out)
+{
+    const int a = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (a >= w * h) return;
+    const float4 wt = wts[a];
+    const float wgt[2] = {which ? wt.z : wt.x, which ? wt.w : wt.y};
+    const __amdgpu_buffer_rsrc_t rs[2] = {
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(sx), (short)0, (int)vol_bytes, kRsrcWord3),
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(sy), (short)0, (int)vol_bytes, kRsrcWord3)};
+    merge_ascan<T>(rs, disp, a, a % w, a / w, wgt, w, h, d, dp, threadIdx.x & 63, out);
+}
+
 // k_merge_volume on the matrix cores: one wave per 2 x 2 tile of A-scans
 // (tile_blend.h), L depths per lane.  k_merge_volume loads every column of a
 // tile up to four times, one sample per lane and load, and keeps the texture
 // path busy with that; here a tile's columns are loaded once, 16 bytes per lane.
 // 500 x 500 x 465: 1.50 -> 0.46 ms from BF16 volumes.
+// Outputs that are not finite are formed again by merge_ascan, each A-scan for
+// itself: a sample that is not finite reaches the whole tile through the weights
+// 0, and the three parts of a weight make a NaN of an infinity.
 template <typename T, int L>
 __global__ __launch_bounds__(256, 3) void k_merge_tile(const void* __restrict__ sx, const void* __restrict__ sy,
                                                        const float* __restrict__ disp, const float4* __restrict__ wts,
@@ -250,7 +260,7 @@ __global__ __launch_bounds__(256, 3) void k_merge_tile(const void* __restrict__ 
     const __amdgpu_buffer_rsrc_t ry =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(sy), (short)0, (int)vol_bytes, kRsrcWord3);
     const size_t na = (size_t)w * h;
-    int groups = 15;  // of the tile's A-scans, as in the structural kernel
+    int groups = 15;  // the tile's A-scans of a round: all, or two where they need too many slots
     for (;;) {
         int lane = threadIdx.x & 63;
         asm volatile("" : "+v"(lane));
@@ -312,7 +322,18 @@ __global__ __launch_bounds__(256, 3) void k_merge_tile(const void* __restrict__ 
                 }
             }
         }
-        groups = mx_next(groups, __ballot(bad != 0.f) != 0);
+        if (__ballot(bad != 0.f)) {
+            __threadfence();  // the stores above come first
+            const __amdgpu_buffer_rsrc_t rs[2] = {rx, ry};
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + (q & 1), j = j0 + (q >> 1), a = uni(j * w + i);
+                if (!(groups >> q & 1) || i >= w || j >= h) continue;  // wave-uniform
+                const float4 wq = wts[a];
+                const float wgt[2] = {which ? wq.z : wq.x, which ? wq.w : wq.y};
+                merge_ascan<T>(rs, disp, a, i, j, wgt, w, h, d, dp, lane, out);
+            }
+        }
+        groups = mx_next(groups, false);
         if (!groups) return;
     }
 }
