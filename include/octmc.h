@@ -422,7 +422,8 @@ OCTMC_API int octmc_eval_batched(octmc_pair* const* pairs, int32_t npairs, int32
  * OCTMC_NOALLOC_MAX_ASCANS), OCTMC_E_DTYPE.
  * Every call on one GPU shares that GPU's array, which keeps the last call's
  * contents: calls that overlap on one GPU (other streams, other threads,
- * other contexts) race and must be ordered by the caller. */
+ * other contexts) race and must be ordered by the caller.  A race spoils the
+ * results of the calls that overlap, and of no later one. */
 #define OCTMC_NOALLOC_MAX_ASCANS (512 * 512)
 #define OCTMC_NOALLOC_SCRATCH_BYTES (OCTMC_NOALLOC_MAX_ASCANS * 32 + 8192 + (OCTMC_NOALLOC_MAX_ASCANS + 255) / 256 * 64)
 OCTMC_API int octmc_eval_noalloc(octmc_ctx* ctx, const octmc_params* params, const octmc_shape* shape, const void* sx,

@@ -350,6 +350,16 @@ __device__ __forceinline__ bool struct_sums(const StructJobs& jobs)
     return true;
 }
 
+// The count of finished blocks of a combination of few A-scans is cleared by the
+// structural launch before it, so that no evaluation depends on how an earlier one
+// ended (evaluations that overlapped on one object may leave any count).  The lane
+// that stores A-scan 0 does it, at the end: at the start every wave would wait for
+// one more load of its arguments (64 x 64 x 128 21.1 -> 21.6 us).
+__device__ __forceinline__ void clear_ticket(unsigned* ticket, int a)
+{
+    if (a == 0 && ticket) *ticket = 0u;
+}
+
 template <typename T, bool AXIAL>
 __global__ __launch_bounds__(256) void k_struct(const StructJobs jobs)
 {
@@ -511,6 +521,7 @@ __global__ __launch_bounds__(256) void k_struct(const StructJobs jobs)
         float4* o = reinterpret_cast<float4*>(J.part + (size_t)a * 8);
         o[0] = make_float4(lam, gxx, gyx, gzx);
         o[1] = make_float4(gxy, gyy, gzy, 0.f);
+        clear_ticket(J.ticket, a);
     }
 }
 
@@ -733,6 +744,7 @@ __global__ __launch_bounds__(256) void k_struct2(const StructJobs jobs)
         float4* o = reinterpret_cast<float4*>(J.part + (size_t)a * 8);
         o[0] = make_float4(lam, gxx, gyx, gzx);
         o[1] = make_float4(gxy, gyy, gzy, 0.f);
+        clear_ticket(J.ticket, a);
     }
 }
 
@@ -1529,6 +1541,7 @@ struct StructMultiJob {
     const void* vol[N];            // storage-type volumes of this level, [h][w][dp]
     const float* disp;             // [N][h][w][3]
     float* part[N * (N - 1) / 2];  // per pair (P, Q), P < Q in lexicographic order: [na][8]
+    unsigned* ticket[N * (N - 1) / 2];  // of the pairs' combinations (few A-scans), or null
     int w, h, d, na;
     int dp;                        // storage pitch (d, or d + 1 for an odd depth in 16-bit storage)
     uint32_t vol_bytes;
@@ -1618,6 +1631,7 @@ __global__ __launch_bounds__(256) void k_struct_multi(const StructMultiJob<N> J)
             float4* o = reinterpret_cast<float4*>(J.part[q] + (size_t)a * 8);
             o[0] = make_float4(v[0], v[1], v[2], v[3]);
             o[1] = make_float4(v[4], v[5], v[6], 0.f);
+            clear_ticket(J.ticket[q], a);
         }
     }
 }
@@ -1879,6 +1893,7 @@ __global__ __launch_bounds__(256, 3) void k_struct_multi1(const StructMultiJob<N
             float4* o = reinterpret_cast<float4*>(J.part[q] + (size_t)a * 8);
             o[0] = make_float4(v[0], v[1], v[2], v[3]);
             o[1] = make_float4(v[4], v[5], v[6], 0.f);
+            clear_ticket(J.ticket[q], a);
         }
     }
 }
@@ -1901,7 +1916,7 @@ hipError_t launch_sum(const SumJobs& jobs, int total_blocks, hipStream_t s)
 //   k_struct2 loads sample pairs, 32-bit aligned at an even storage pitch
 //   (every level of a pair); an odd pitch (volumes in the caller's layout)
 //   takes one sample per lane.
-constexpr int kMxMinAscans = 8192;
+constexpr int kMxMinAscans = kFewMaxAscans + 1;  // it has no count of a combination's blocks to clear
 enum { kByMx8, kByMx4, kByPairs, kBySamples };
 static int struct_form(const StructJob& J, bool axial)
 {
@@ -2031,15 +2046,19 @@ hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s)
 // steps to 5) 282 against 322.  Three stay with k_struct_multi1, which has the
 // registers for them: 200 x 200 x 512 302 against 342, 300 x 300 x 640 833 against 870.
 constexpr int kMxMultiMinAscans = 16384;
+static_assert(kMxMultiMinAscans > kFewMaxAscans && kMxMinAscansF32 > kFewMaxAscans, "nor have these");
 template <int N>
-static hipError_t launch_struct_multi_n(const void* const* vol, const float* disp, float* const* part, int w, int h,
-                                        int d, int dp, uint32_t vol_bytes, float eps_h, octmc_dtype dt,
-                                        hipStream_t s, const int* skip)
+static hipError_t launch_struct_multi_n(const void* const* vol, const float* disp, float* const* part,
+                                        unsigned* const* ticket, int w, int h, int d, int dp, uint32_t vol_bytes,
+                                        float eps_h, octmc_dtype dt, hipStream_t s, const int* skip)
 {
     StructMultiJob<N> J{};
     J.skip = skip;
     for (int V = 0; V < N; ++V) J.vol[V] = vol[V];
-    for (int q = 0; q < N * (N - 1) / 2; ++q) J.part[q] = part[q];
+    for (int q = 0; q < N * (N - 1) / 2; ++q) {
+        J.part[q] = part[q];
+        J.ticket[q] = few_ascans(w * h) ? ticket[q] : nullptr;
+    }
     J.disp = disp;
     J.w = w;
     J.h = h;
@@ -2075,13 +2094,13 @@ bool struct_multi_supported(int n, int dp, octmc_dtype dt)
     return (n == 3 || n == 4) && (dt == OCTMC_F32 || ((dt == OCTMC_BF16 || dt == OCTMC_F16) && dp % 2 == 0));
 }
 
-hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part, int w, int h,
-                               int d, int dp, uint32_t vol_bytes, float eps_h, octmc_dtype dt, hipStream_t s,
-                               const int* skip)
+hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part,
+                               unsigned* const* ticket, int w, int h, int d, int dp, uint32_t vol_bytes, float eps_h,
+                               octmc_dtype dt, hipStream_t s, const int* skip)
 {
     if (!struct_multi_supported(n, dp, dt) || (dt == OCTMC_F32 && dp != d)) return hipErrorInvalidValue;
-    if (n == 3) return launch_struct_multi_n<3>(vol, disp, part, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
-    return launch_struct_multi_n<4>(vol, disp, part, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
+    if (n == 3) return launch_struct_multi_n<3>(vol, disp, part, ticket, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
+    return launch_struct_multi_n<4>(vol, disp, part, ticket, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
 }
 
 }  // namespace octmc

@@ -244,9 +244,13 @@ struct MultiEvaluator final : Evaluator {
             const void* vols[kMaxVol];
             float* parts[kMaxVol * (kMaxVol - 1) / 2];
             for (int V = 0; V < M->n; ++V) vols[V] = M->vol[V].s[level];
-            for (int q = 0; q < np; ++q) parts[q] = M->views[q]->part;
+            unsigned* tickets[kMaxVol * (kMaxVol - 1) / 2];
+            for (int q = 0; q < np; ++q) {
+                parts[q] = M->views[q]->part;
+                tickets[q] = M->views[q]->ticket;
+            }
             const Level& L = M->views[0]->lev[level];
-            HIP_TRY(launch_struct_multi(vols, M->n, ea.disp, parts, L.w, L.h, L.d, L.dp, L.vol_bytes,
+            HIP_TRY(launch_struct_multi(vols, M->n, ea.disp, parts, tickets, L.w, L.h, L.d, L.dp, L.vol_bytes,
                                         (float)M->params.eps_huber, M->dtype, s, ea.skip));
         }
         for (int q0 = 0; q0 < np; q0 += kMaxJobs)

@@ -137,6 +137,7 @@ struct StructJob {
     // block partials, none of them for nsum = 0 (and for the axial kernels)
     double* sum_blk;
     int nsum, sum_begin;
+    unsigned* ticket;   // of the job's combination (few A-scans), cleared by this launch, or null
 };
 struct StructJobs {
     StructJob j[kMaxJobs];
@@ -179,7 +180,7 @@ struct CombineJob {
     double* eta;         // level constant (read in mode 1, written in mode 0)
     const double* p;     // [2][na][3] search direction (float64) or nullptr
     double* blk;         // [nblk][8] block partials
-    unsigned* ticket;    // few A-scans: blocks done, 0 between launches
+    unsigned* ticket;    // few A-scans: blocks done; 0 before and after a launch
     double* terms;       // [OCTMC_NTERMS] (mode 1)
     int w, h, d, na, blk_begin, nblk, nsum;
     int mode;            // 0: only set eta (Eq. 10); 1: full evaluation
@@ -212,11 +213,11 @@ hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s);
 // each volume resampled once (n = 3 or 4; float32 storage, or 16-bit storage
 // at an even storage pitch dp: see struct_multi_supported); part[q] is pair
 // q's [na][8] partial buffer, the pairs (P, Q), P < Q, in lexicographic
-// order; skip (device flag, may be null): when nonzero the launch does nothing
+// order; ticket[q] is cleared for pair q's combination; skip (device flag, may be null): when nonzero the launch does nothing
 bool struct_multi_supported(int n, int dp, octmc_dtype dt);
-hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part, int w, int h,
-                               int d, int dp, uint32_t vol_bytes, float eps_h, octmc_dtype dt, hipStream_t s,
-                               const int* skip = nullptr);
+hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part,
+                               unsigned* const* ticket, int w, int h, int d, int dp, uint32_t vol_bytes, float eps_h,
+                               octmc_dtype dt, hipStream_t s, const int* skip = nullptr);
 
 // preparation (kernels_prep.hip)
 // One level of the pyramids of one or two volumes with their images and validity.

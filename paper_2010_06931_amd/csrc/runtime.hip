@@ -81,9 +81,9 @@ int scratch_address(int device, void** out)
 namespace {
 
 constexpr int kSumBlocks = 256;
-// The count of finished combination blocks lies in the unused fourth column of
-// the last row of the displacement-sum partials: zero when allocated, and k_sum
-// writes 0.0 there.
+// The count of finished combination blocks lies in the last row of the
+// displacement-sum partials, which few A-scans do not use; the structural launch
+// of each evaluation clears it.
 constexpr size_t kTicketAt = kSumBlocks * 4 - 1;
 // The rows of few A-scans are more than of many; they lie where the dot products'
 // rows do (an evaluation and a pass of dot products follow each other).
@@ -124,6 +124,7 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
             v.part = P->part;
             v.sum_blk = P->sum_blk;
             v.comb_blk = few_ascans(v.L.na) ? P->dot_blk : P->comb_blk;
+            v.ticket = P->ticket;
             v.eta = P->eta + ea[q].level;
             v.orient = P->orient;
         }
@@ -145,7 +146,8 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
         if (nsum && !fold) sj.j[sj.n++] = SumJob{{ea[q].disp, dy}, V.sum_blk, L.na, sb, nsum};
         sb += nsum;
         tj.j[q] = StructJob{L.sx, L.sy, ea[q].disp, V.part, L.w, L.h, L.d, L.na, 0, L.vol_bytes,
-                            (float)pr.eps_huber, L.dp, V.sum_blk, fold ? nsum : 0, 0};
+                            (float)pr.eps_huber, L.dp, V.sum_blk, fold ? nsum : 0, 0,
+                            few_ascans(L.na) ? V.ticket : nullptr};
         const int blen = L.w;  // square scans: every B-scan has w A-scans
         const double f = std::floor(pr.flyback_frac * blen + 0.5);
         CombineJob c{};
@@ -163,7 +165,7 @@ int octmc::eval_group(const EvalArgs* ea, int n, hipStream_t s, hipEvent_t* ev, 
         c.eta = V.eta;
         c.p = ea[q].p;
         c.blk = V.comb_blk;
-        c.ticket = reinterpret_cast<unsigned*>(V.sum_blk + kTicketAt);
+        c.ticket = V.ticket;
         c.terms = ea[q].terms;
         c.w = L.w;
         c.h = L.h;
@@ -230,11 +232,11 @@ int octmc::pair_alloc_scratch(octmc_pair* P, size_t na, hipStream_t s)
 {
     HIP_TRY(P->alloc(&P->part, na * 8 * 4));
     HIP_TRY(P->alloc(&P->sum_blk, kSumBlocks * 4 * 8));
+    P->ticket = reinterpret_cast<unsigned*>(P->sum_blk + kTicketAt);
     HIP_TRY(P->alloc(&P->comb_blk, (size_t)nblk_combine((int)na) * 8 * 8));
     HIP_TRY(P->alloc(&P->eta, OCTMC_MAX_LEVELS * 8));
     HIP_TRY(P->alloc(&P->terms, OCTMC_NTERMS * 8));
     HIP_TRY(P->alloc(&P->dot_blk, (size_t)512 * (kMaxDots + 1) * 8));
-    HIP_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(P->sum_blk + kTicketAt), 0u, 2, s));
     HIP_TRY(P->alloc(&P->dot_out, (kMaxDots + 1) * 8));
     HIP_TRY(P->alloc(&P->lb, sizeof(LbState)));
     static const std::vector<double> ones(OCTMC_MAX_LEVELS, 1.0);
@@ -836,6 +838,7 @@ int octmc_eval_noalloc(octmc_ctx* ctx, const octmc_params* params, const octmc_s
     v.part = reinterpret_cast<float*>(base);
     v.sum_blk = reinterpret_cast<double*>(base + kNoAllocPart);
     v.comb_blk = reinterpret_cast<double*>(base + kNoAllocPart + kNoAllocSum);
+    v.ticket = reinterpret_cast<unsigned*>(v.sum_blk + kTicketAt);
     v.eta = eta;
     v.orient = 2;
     EvalArgs ea{nullptr, disp, terms, grad, nullptr, nullptr, 0, eta_mode};

@@ -43,7 +43,8 @@ struct Level {
 // volumes, en face images and validity, the objective's parameters, and the
 // scratch its kernels write (per-A-scan partials [na][8] float32, the
 // displacement-sum block rows [<= 256][4] and the combination block rows
-// [nblk][8] float64) with the level's eta (one float64).
+// [nblk][8] float64, and the count of the combination's finished blocks) with
+// the level's eta (one float64).
 struct EvalView {
     Level L;
     octmc_dtype dtype = OCTMC_F32;
@@ -51,6 +52,7 @@ struct EvalView {
     float* part = nullptr;
     double* sum_blk = nullptr;
     double* comb_blk = nullptr;
+    unsigned* ticket = nullptr;
     double* eta = nullptr;
     int orient = 2;
 };
@@ -71,6 +73,7 @@ struct octmc_pair {
     double* comb_blk = nullptr; // [nblk0][8]
     double* eta = nullptr;      // [levels]
     double* terms = nullptr;    // [OCTMC_NTERMS] solver scratch
+    unsigned* ticket = nullptr; // blocks of a combination done (a word of sum_blk)
     double* dot_blk = nullptr;  // [512][kMaxDots + 1]
     double* dot_out = nullptr;  // [kMaxDots + 1]
     octmc::LbState* lb = nullptr;  // the device solver's state (LevelRun::run_device)
