@@ -1924,18 +1924,25 @@ static int struct_form(const StructJob& J, bool axial)
     return mx_eight(J.d, J.dp) ? kByMx8 : kByMx4;
 }
 
+// Depth steps of the float32 matrix-core kernels, at most (a tile whose A-scans
+// start apart needs up to kShift more positions, which costs depths just below a
+// multiple of 58 another step), and of the one-A-scan kernels.
+static int steps_mx(int d) { return (d + MxGeo<4, 4>::kShift + MxGeo<4, 4>::kOut - 1) / MxGeo<4, 4>::kOut; }
+static int steps_one(int d) { return (d + kOutPerStep - 1) / kOutPerStep; }
+
 // float32 jobs likewise.  Its matrix products run at the vector units' expense, so
-// k_struct_mx needs more tiles to pay, and depths whose steps are no more than those
-// of k_struct's 61 outputs (one step costs 0.82 .. 0.92 of k_struct's from 200 x 200
-// A-scans on, as much at 180 x 180 and more below): 200 x 200 x 512 172 -> 158 us,
-// 224 x 224 x 512 205 -> 173, 300 x 300 x 640 464 -> 418, 500 x 500 x 800 1600 ->
-// 1189; 200 x 200 x 300 (6 steps to 5) 101 against 114, 251 x 251 x 233 (5 to 4) 124
-// against 128, 172 x 172 x 555 141 against 150.
+// k_struct_mx needs more tiles to pay, and depths whose steps are little more than
+// those of k_struct (one step costs 0.82 .. 0.92 of k_struct's from 200 x 200 A-scans
+// on).  Evaluations by k_struct / k_struct_mx: 200 x 200 x 512 184 / 161 us, 300 x
+// 300 x 640 484 / 431, 400 x 400 x 225 323 / 290; another step than k_struct's: 300 x
+// 300 x 116 128 / 141, x 174 155 / 172, x 232 190 / 202, x 290 227 / 233; one in
+// seven: x 406 312 / 301, 200 x 200 x 406 149 / 152 (156 before the displacement sums
+// went with the launch).  Fewer A-scans: 190 x 190 x 512 165 / 136, 160 x 160 x 512
+// 121 / 110, so the line could lie lower for depths of whole steps.
 constexpr int kMxMinAscansF32 = 40000;
 static bool f32_mx(int na, int d, int dp)
 {
-    constexpr int out = MxGeo<4, 4>::kOut, out1 = kOutPerStep;
-    return na >= kMxMinAscansF32 && dp >= 4 && 7 * ((d + out - 1) / out) <= 8 * ((d + out1 - 1) / out1);
+    return na >= kMxMinAscansF32 && dp >= 4 && 7 * steps_mx(d) <= 8 * steps_one(d);
 }
 
 // The jobs of one kernel's launch, and its blocks: first those of the displacement
@@ -2041,12 +2048,22 @@ hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s)
 // k_multi_mx with fewer A-scans than this leaves the device's registers and LDS
 // (two workgroups per CU) without tiles: four volumes of 96 x 96 x 200 in BF16
 // 99 against k_struct_multi's 87 us per evaluation, 128 x 128 x 256 141 against
-// 153.  Four volumes in float32 take it where two do: 200 x 200 x 512 589 -> 519 us,
-// 300 x 300 x 640 1521 -> 1318; 160 x 160 x 200 187 against 207, 181 x 181 x 300 (6
-// steps to 5) 282 against 322.  Three stay with k_struct_multi1, which has the
-// registers for them: 200 x 200 x 512 302 against 342, 300 x 300 x 640 833 against 870.
+// 153.  Three float32 volumes stay with k_struct_multi1, which has the registers for
+// them: 200 x 200 x 512 302 against 342, 300 x 300 x 640 833 against 870.
 constexpr int kMxMultiMinAscans = 16384;
 static_assert(kMxMultiMinAscans > kFewMaxAscans && kMxMinAscansF32 > kFewMaxAscans, "nor have these");
+// Four float32 volumes gain from some 250 x 250 A-scans on, where a step costs 0.83
+// of k_struct_multi1's, and with fewer where they exceed the 256 MB Infinity Cache,
+// which k_struct_multi1 reads them from more often, and no step is added.
+// k_struct_multi1 / k_multi_mx: 250 x 250 x 110 285 / 267 us, x 170 350 / 338, x 290
+// (6 steps to 5) 566 / 519, x 116 (3 to 2) 283 / 329; 300 x 300 x 174 (4 to 3) 549 /
+// 565; 200 x 200 x 225 282 / 305, x 340 377 / 393, x 400 (256 MB) 483 / 427, x 512
+// 591 / 511; 230 x 230 x 225 367 / 376, x 340 564 / 502, x 406 (8 to 7) 645 / 655.
+static bool f32_multi_mx(int na, int d)
+{
+    if (na >= 62500) return 5 * steps_mx(d) <= 6 * steps_one(d);
+    return (int64_t)na * d >= 16000000 && steps_mx(d) <= steps_one(d);
+}
 template <int N>
 static hipError_t launch_struct_multi_n(const void* const* vol, const float* disp, float* const* part,
                                         unsigned* const* ticket, int w, int h, int d, int dp, uint32_t vol_bytes,
@@ -2070,7 +2087,7 @@ static hipError_t launch_struct_multi_n(const void* const* vol, const float* dis
     const int blocks = (struct_blocks(w, h) + 7) / 8 * 8;  // a multiple of the 8 XCDs
     const int mx = struct_mx_blocks(w, h);
     if constexpr (N == 4)
-        if (dt == OCTMC_F32 && f32_mx(J.na, d, dp)) {
+        if (dt == OCTMC_F32 && f32_multi_mx(J.na, d)) {
             hipLaunchKernelGGL((k_multi_mx<float, N>), dim3(mx), dim3(256), 0, s, J);
             return hipGetLastError();
         }
