@@ -1914,8 +1914,12 @@ hipError_t launch_sum(const SumJobs& jobs, int total_blocks, hipStream_t s)
 //   (64 x 64 x 128: 14 against 18 us, 64 x 64 x 400: 18 against 25, 90 x 90 x
 //   400: 31 against 29, 128 x 128 x 256: 43 against 32).
 //   k_struct2 loads sample pairs, 32-bit aligned at an even storage pitch
-//   (every level of a pair); an odd pitch (volumes in the caller's layout)
-//   takes one sample per lane.
+//   (every level of a pair); an odd pitch (volumes in the caller's layout) of
+//   fewer A-scans takes one sample per lane.
+//   With an odd pitch half the columns start between two 32-bit words, and
+//   k_struct_mx's loads of them take longer (tile_blend.h); it is still the faster
+//   one, k_struct's being one sample each: 500 x 500 x 465 BF16 916 -> 454 us (406
+//   padded), 200 x 200 x 301 FP16 112 -> 75, 91 x 91 x 59 26.0 -> 24.3.
 constexpr int kMxMinAscans = kFewMaxAscans + 1;  // it has no count of a combination's blocks to clear
 enum { kByMx8, kByMx4, kByPairs, kBySamples };
 static int struct_form(const StructJob& J, bool axial)

@@ -108,8 +108,9 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // Depth windows: a lane holds L consecutive source depths (one load per
 // column), a row of 16 lanes a window of 16 L.  An A-scan's window starts
 // sh = 0 .. kShift samples before its first depth tap, at a multiple of 4 bytes
-// (loads off a 4-byte boundary take up to four times as long); A-scans with a
-// common start share their columns' loads.  Position p of the first volume's
+// (loads off a 4-byte boundary take up to four times as long; those of every other
+// column of a 16-bit volume with an odd pitch are); A-scans with a common start share
+// their columns' loads.  Position p of the first volume's
 // window holds the first tap of output kOut step + p - sh; the other volumes'
 // blends are moved to the same positions.
 template <int ES, int L>
