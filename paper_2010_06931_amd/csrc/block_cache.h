@@ -137,17 +137,6 @@ public:
         if (p) (void)hipHostFree(p);
     }
 
-    // Has the runtime finish with the commands it still holds, which a free does (it
-    // waits for the device).  Objects that are created without one leave that to their
-    // first launch: the first evaluation of a new 64 x 64 x 128 pair after a pause took
-    // 63 us, after this 46 (its creation 58 and 63).
-    static void drain()
-    {
-        void* p = nullptr;
-        if (hipMalloc(&p, 64) == hipSuccess) (void)hipFree(p);
-        else (void)hipGetLastError();
-    }
-
     // gives every idle block back to the driver
     void trim()
     {

@@ -520,7 +520,6 @@ int octmc_multi_create(octmc_ctx* ctx, const octmc_params* params_in, const octm
     HIP_TRY(M->alloc(&M->gp_blk, (size_t)kMBlocks * 8));
     HIP_TRY(M->alloc(&M->fsum, 3 * 8));
     HIP_TRY(tmp.settle(s));
-    BlockCache::drain();
     *out = M.release();
     return OCTMC_OK;
 }

@@ -668,7 +668,6 @@ int octmc::pair_create_impl(octmc_ctx* ctx, const octmc_params* params, const oc
     }
     OCTMC_TRY(pair_alloc_scratch(P, na, s));
     HIP_TRY(tmp.settle(s));
-    if (!slab) BlockCache::drain();
     *out = guard.release();
     return OCTMC_OK;
 }
