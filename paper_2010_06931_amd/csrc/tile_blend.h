@@ -79,10 +79,11 @@ __device__ __forceinline__ float row_shr_add(float v)
 // tile, up to 48 a second one, and a tile with more (disjoint stencils) is
 // served two A-scans at a time.
 //   16-bit storage: v_mfma_f32_16x16x32 on the stored samples.  The float32
-//     weights enter as three 16-bit parts, each the rest rounded to nearest,
-//     whose sum is the weight exactly (BF16: three times 8 bits; FP16: 11 + 11 +
-//     2 bits of the weight times 2^12, undone in the depth taps), so the
-//     products are those of a float32 blend and no sample is converted.  The
+//     weights enter as three 16-bit parts, each the rest rounded to nearest.  Their
+//     sum is the weight: exactly for BF16 (three times 8 bits) and for FP16 down to
+//     2^-16 (11 + 11 + 2 bits of the weight times 2^15, undone in the depth taps);
+//     binary16 ends at 2^-24, so a smaller weight is off by up to 2^-40.  The products
+//     are then those of a float32 blend, and no sample is converted.  The
 //     trailing parts are summed first, so that few additions round at the
 //     blend's full size (error of a merged 200 x 200 x 300 volume against 64
 //     bits: 6.1e-8, leading parts first 7.6e-8, vector FMAs 7.5e-8).  Splitting
@@ -200,14 +201,14 @@ struct MxOps<bf16_t> {
 template <>
 struct MxOps<f16_t> {
     // binary16 has no room below 2^-24 for the trailing bits of a weight: the
-    // weights are scaled by 2^12 (the largest is below 2) and the depth taps
-    // by 2^-12, both exact
-    static constexpr float kUnscale = 1.f / 4096.f;
+    // weights are scaled by 2^15 (the largest, a derivative's, is 25 / 18, and 65504
+    // the largest number) and the depth taps by 2^-15, both exact
+    static constexpr float kScale = 32768.f, kUnscale = 1.f / kScale;
     typedef unsigned short part;
     static constexpr int kParts = 3;
     static __device__ __forceinline__ void split_weight(float w, unsigned short (&p)[3])
     {
-        float r = w * 4096.f;
+        float r = w * kScale;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const _Float16 hp = (_Float16)r;
