@@ -94,9 +94,9 @@ constexpr int kAutoCoarsest = 16;
 octmc_params resolve_levels(const octmc_params& p, const octmc_shape& shape);
 int validate_shape(const octmc_params* params, const octmc_shape* shape);
 
-// Device bytes a pair (and its solve and merge) takes from a Slab.
-size_t pair_footprint(const octmc_params& params, const octmc_shape& shape, bool have_octa, bool have_valid,
-                      bool merged);
+// Device bytes a pair (and its solve and merge) takes from a Slab at most.
+size_t pair_footprint(const octmc_params& params, const octmc_shape& shape, bool have_octa, bool have_enface,
+                      bool have_valid, bool merged);
 
 // The C-ABI operations with an optional slab (all device memory, including
 // temporaries, comes from it), an evaluator and host scratch.

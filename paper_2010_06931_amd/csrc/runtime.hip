@@ -315,28 +315,30 @@ int octmc::validate_shape(const octmc_params* params, const octmc_shape* shape)
 }
 
 // Every device allocation pair_create_impl, register_impl and merge_impl make
-// for one pair, each rounded up to the slab alignment.
-size_t octmc::pair_footprint(const octmc_params& pr, const octmc_shape& sh, bool have_octa, bool have_valid,
-                             bool merged)
+// for one pair whose inputs are on the host, each rounded up to the slab alignment.
+// Structural inputs on the device are read where they are: the room of their copies
+// is reserved too and stays free.
+size_t octmc::pair_footprint(const octmc_params& pr, const octmc_shape& sh, bool have_octa, bool have_enface,
+                             bool have_valid, bool merged)
 {
     const size_t w = sh.w, h = sh.h, d = sh.d, na = w * h, nv = na * d;
     const size_t es = esize(sh.dtype);
     size_t t = 0;
-    t += 2 * slab_bytes(nv * 4);  // float32 staging
+    t += 2 * slab_bytes(nv * 4);  // float32 copies of the inputs
     t += slab_bytes(64);          // counters
     t += 2 * slab_bytes(na * 4);  // en face
     if (have_octa) {
         const bool detect = !have_valid && (pr.flags & OCTMC_DETECT_INVALID);
         t += 2 * slab_bytes(nv * 4);
         if (have_valid || detect) t += slab_bytes(h * 4) + slab_bytes(w * 4);  // substitution tables
-        if (detect) t += slab_bytes(h * 8) + slab_bytes(h * 4) + slab_bytes(w * 8) + slab_bytes(w * 4);
-        if (pr.flags & OCTMC_ENFACE_PROJECT)
-            t += slab_bytes(enface_scratch_bytes(sh.w, sh.h, sh.d)) + slab_bytes(h * 4) + slab_bytes(w * 4);
+        if (detect) t += slab_bytes(h * 8) + slab_bytes(w * 8);                // B-scan means
+        if (!have_enface && (pr.flags & OCTMC_ENFACE_PROJECT)) t += slab_bytes(enface_scratch_bytes(sh.w, sh.h, sh.d));
     }
     t += slab_bytes(h * 4) + slab_bytes(w * 4);  // validity
     size_t lw = w, lh = h, ld = d;
     for (int l = 0; l < pr.levels; ++l) {
-        t += 2 * slab_bytes(lw * lh * (size_t)storage_pitch((int)ld, sh.dtype) * es);  // storage at its pitch
+        if (l == 0 || sh.dtype != OCTMC_F32)  // a coarser level's float32 volume is its storage
+            t += 2 * slab_bytes(lw * lh * (size_t)storage_pitch((int)ld, sh.dtype) * es);  // at its pitch
         if (l + 1 < pr.levels) {
             const size_t w2 = (lw + 1) / 2, h2 = (lh + 1) / 2, d2 = (ld + 1) / 2;
             t += 2 * slab_bytes(w2 * h2 * d2 * 4) + 2 * slab_bytes(w2 * h2 * 4) + slab_bytes(h2 * 4) +

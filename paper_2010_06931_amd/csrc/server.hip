@@ -337,7 +337,7 @@ int check_request(const octmc_request* req)
 size_t request_footprint(const octmc_request* req)
 {
     return pair_footprint(resolve_levels(req->params, req->shape), req->shape, req->octa_x != nullptr,
-                          req->valid_x != nullptr, req->merged_oct != nullptr);
+                          req->enface_x != nullptr, req->valid_x != nullptr, req->merged_oct != nullptr);
 }
 
 void destroy_server(octmc_server* S)
