@@ -167,9 +167,19 @@ OCTMC_API const char* octmc_last_error(void);
 /* Fill *out with the defaults listed in octmc_params. */
 OCTMC_API int octmc_params_default(octmc_params* out);
 
-/* Create a context bound to HIP device `device_ordinal`. */
+/* Create a context bound to HIP device `device_ordinal`.  The contexts on one
+ * device share device memory that destroyed objects and finished calls leave
+ * for the next ones: at most 1/32 of the device's memory (9 GB of 288) and 256
+ * KiB of pinned host memory, given back when the last context on the device is
+ * destroyed (and no object of theirs is left), when an allocation of this
+ * library fails, and by octmc_trim. */
 OCTMC_API int octmc_create(int device_ordinal, octmc_ctx** out);
 OCTMC_API int octmc_destroy(octmc_ctx* ctx);
+
+/* Give the memory kept on ctx's device back to it, for other allocators of this
+ * process or other processes.  Memory of live objects is not touched; any thread
+ * may call it at any time.  Waits for the device. */
+OCTMC_API int octmc_trim(octmc_ctx* ctx);
 
 /* Ingest one orthogonal scan pair (Sec. 2.1 input; pyramid of Sec. 2.1
  * "optimization"; validity of Sec. 2.2; en face images of Sec. 2.3/2.4).

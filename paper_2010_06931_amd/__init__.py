@@ -37,7 +37,7 @@ STATUS = {0: "OK", -1: "E_INVALID", -2: "E_SHAPE", -3: "E_DTYPE", -4: "E_OOM", -
           -7: "E_BUSY"}
 
 # exported symbols of include/octmc.h (checked by the CPU test suite)
-SYMBOLS = ("octmc_version", "octmc_last_error", "octmc_params_default", "octmc_create", "octmc_destroy",
+SYMBOLS = ("octmc_version", "octmc_last_error", "octmc_params_default", "octmc_create", "octmc_destroy", "octmc_trim",
            "octmc_pair_create", "octmc_pair_destroy", "octmc_pair_levels", "octmc_pair_level_shape",
            "octmc_validity_from_octa", "octmc_enface_project", "octmc_enface_workspace_size", "octmc_prealign_eval",
            "octmc_prealign",
@@ -117,6 +117,7 @@ def lib():
         L.octmc_params_default.argtypes = [C.POINTER(Params)]
         L.octmc_create.argtypes = [C.c_int, C.POINTER(vp)]
         L.octmc_destroy.argtypes = [vp]
+        L.octmc_trim.argtypes = [vp]
         L.octmc_pair_create.argtypes = [vp, C.POINTER(Params), C.POINTER(Shape)] + [vp] * 8 + [vp, C.POINTER(vp)]
         L.octmc_pair_destroy.argtypes = [vp]
         L.octmc_pair_level_shape.argtypes = [vp, C.c_int32] + [C.POINTER(C.c_int32)] * 3
@@ -200,6 +201,11 @@ class Context:
         self.device = device
         self._h = C.c_void_p()
         _check(lib().octmc_create(device, C.byref(self._h)))
+
+    def trim(self):
+        """Give the device memory that closed objects left for the next ones (at
+        most 1/32 of the device's) back to the device."""
+        _check(lib().octmc_trim(self._h))
 
     def close(self):
         if self._h:

@@ -15,7 +15,8 @@
 // here: their owner has waited for the stream (or the device) that last used
 // them, so any stream of any thread can take them.  The idle blocks are bounded
 // (1 / 32 of the device's memory, 64 host blocks); the oldest are freed beyond
-// that, and all of them when an allocation fails, which is then tried again.
+// that, and all of them when an allocation fails, which is then tried again, or
+// when the caller asks for it (octmc_trim).
 #pragma once
 #include <hip/hip_runtime.h>
 

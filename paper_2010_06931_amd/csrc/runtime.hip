@@ -411,6 +411,14 @@ int octmc_destroy(octmc_ctx* ctx)
     return OCTMC_OK;
 }
 
+int octmc_trim(octmc_ctx* ctx)
+{
+    if (!ctx) return fail(OCTMC_E_INVALID, "ctx is NULL");
+    HIP_TRY(hipSetDevice(ctx->device));
+    ctx_trim(ctx);
+    return OCTMC_OK;
+}
+
 }  // extern "C"
 
 // Stage 1 before ingest (Fig. 1): a structural-only pair (delta0 = 0, no en
