@@ -351,8 +351,9 @@ __device__ __forceinline__ bool struct_sums(const StructJobs& jobs)
 }
 
 // The count of finished blocks of a combination of few A-scans is cleared by the
-// structural launch before it, so that no evaluation depends on how an earlier one
-// ended (evaluations that overlapped on one object may leave any count).  The lane
+// structural launch before it (for the fused pass of several volumes by the launch of
+// their field sums), so that no evaluation depends on how an earlier one ended
+// (evaluations that overlapped on one object may leave any count).  The lane
 // that stores A-scan 0 does it, at the end: at the start every wave would wait for
 // one more load of its arguments (64 x 64 x 128 21.1 -> 21.6 us).
 __device__ __forceinline__ void clear_ticket(unsigned* ticket, int a)
@@ -1541,7 +1542,6 @@ struct StructMultiJob {
     const void* vol[N];            // storage-type volumes of this level, [h][w][dp]
     const float* disp;             // [N][h][w][3]
     float* part[N * (N - 1) / 2];  // per pair (P, Q), P < Q in lexicographic order: [na][8]
-    unsigned* ticket[N * (N - 1) / 2];  // of the pairs' combinations (few A-scans), or null
     int w, h, d, na;
     int dp;                        // storage pitch (d, or d + 1 for an odd depth in 16-bit storage)
     uint32_t vol_bytes;
@@ -1631,7 +1631,6 @@ __global__ __launch_bounds__(256) void k_struct_multi(const StructMultiJob<N> J)
             float4* o = reinterpret_cast<float4*>(J.part[q] + (size_t)a * 8);
             o[0] = make_float4(v[0], v[1], v[2], v[3]);
             o[1] = make_float4(v[4], v[5], v[6], 0.f);
-            clear_ticket(J.ticket[q], a);
         }
     }
 }
@@ -1893,7 +1892,6 @@ __global__ __launch_bounds__(256, 3) void k_struct_multi1(const StructMultiJob<N
             float4* o = reinterpret_cast<float4*>(J.part[q] + (size_t)a * 8);
             o[0] = make_float4(v[0], v[1], v[2], v[3]);
             o[1] = make_float4(v[4], v[5], v[6], 0.f);
-            clear_ticket(J.ticket[q], a);
         }
     }
 }
@@ -2055,7 +2053,7 @@ hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s)
 // 153.  Three float32 volumes stay with k_struct_multi1, which has the registers for
 // them: 200 x 200 x 512 302 against 342, 300 x 300 x 640 833 against 870.
 constexpr int kMxMultiMinAscans = 16384;
-static_assert(kMxMultiMinAscans > kFewMaxAscans && kMxMinAscansF32 > kFewMaxAscans, "nor have these");
+static_assert(kMxMinAscansF32 > kFewMaxAscans, "nor has its float32 form");
 // Four float32 volumes gain from some 250 x 250 A-scans on, where a step costs 0.83
 // of k_struct_multi1's, and with fewer where they exceed the 256 MB Infinity Cache,
 // which k_struct_multi1 reads them from more often, and no step is added.
@@ -2069,17 +2067,14 @@ static bool f32_multi_mx(int na, int d)
     return (int64_t)na * d >= 16000000 && steps_mx(d) <= steps_one(d);
 }
 template <int N>
-static hipError_t launch_struct_multi_n(const void* const* vol, const float* disp, float* const* part,
-                                        unsigned* const* ticket, int w, int h, int d, int dp, uint32_t vol_bytes,
-                                        float eps_h, octmc_dtype dt, hipStream_t s, const int* skip)
+static hipError_t launch_struct_multi_n(const void* const* vol, const float* disp, float* const* part, int w, int h,
+                                        int d, int dp, uint32_t vol_bytes, float eps_h, octmc_dtype dt,
+                                        hipStream_t s, const int* skip)
 {
     StructMultiJob<N> J{};
     J.skip = skip;
     for (int V = 0; V < N; ++V) J.vol[V] = vol[V];
-    for (int q = 0; q < N * (N - 1) / 2; ++q) {
-        J.part[q] = part[q];
-        J.ticket[q] = few_ascans(w * h) ? ticket[q] : nullptr;
-    }
+    for (int q = 0; q < N * (N - 1) / 2; ++q) J.part[q] = part[q];
     J.disp = disp;
     J.w = w;
     J.h = h;
@@ -2115,13 +2110,13 @@ bool struct_multi_supported(int n, int dp, octmc_dtype dt)
     return (n == 3 || n == 4) && (dt == OCTMC_F32 || ((dt == OCTMC_BF16 || dt == OCTMC_F16) && dp % 2 == 0));
 }
 
-hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part,
-                               unsigned* const* ticket, int w, int h, int d, int dp, uint32_t vol_bytes, float eps_h,
-                               octmc_dtype dt, hipStream_t s, const int* skip)
+hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part, int w, int h,
+                               int d, int dp, uint32_t vol_bytes, float eps_h, octmc_dtype dt, hipStream_t s,
+                               const int* skip)
 {
     if (!struct_multi_supported(n, dp, dt) || (dt == OCTMC_F32 && dp != d)) return hipErrorInvalidValue;
-    if (n == 3) return launch_struct_multi_n<3>(vol, disp, part, ticket, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
-    return launch_struct_multi_n<4>(vol, disp, part, ticket, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
+    if (n == 3) return launch_struct_multi_n<3>(vol, disp, part, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
+    return launch_struct_multi_n<4>(vol, disp, part, w, h, d, dp, vol_bytes, eps_h, dt, s, skip);
 }
 
 }  // namespace octmc

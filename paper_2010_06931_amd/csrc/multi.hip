@@ -75,13 +75,27 @@ __device__ __forceinline__ double wave_sum_rows(const double* __restrict__ blk, 
     return s;
 }
 
-// the three field sums from the block partials of k_field_sum (one wave each)
+// the counts of finished blocks of the pairs' combinations (of few A-scans), for the
+// three or four volumes of the fused pass
+struct TicketSpec {
+    unsigned* p[6];
+    int n;
+};
+
+// the three field sums from the block partials of k_field_sum (one wave each); the
+// fourth wave clears the counts for the combinations that follow
 __global__ __launch_bounds__(kMB) void k_field_sum_final(const double* __restrict__ blk, int nblk,
-                                                         double* __restrict__ S, const int* __restrict__ skip)
+                                                         double* __restrict__ S, const TicketSpec tickets,
+                                                         const int* __restrict__ skip)
 {
+    static_assert(kMB == 256, "four waves");
     if (skip && *skip) return;
     const int wv = threadIdx.x >> 6;
-    if (wv >= 3) return;  // uniform per wave
+    if (wv == 3) {  // uniform per wave
+        const int q = threadIdx.x & 63;
+        if (q < tickets.n) *tickets.p[q] = 0u;
+        return;
+    }
     const double s = wave_sum_rows(blk, 3, wv, nblk);
     if ((threadIdx.x & 63) == 0) S[wv] = s;
 }
@@ -244,21 +258,19 @@ struct MultiEvaluator final : Evaluator {
             const void* vols[kMaxVol];
             float* parts[kMaxVol * (kMaxVol - 1) / 2];
             for (int V = 0; V < M->n; ++V) vols[V] = M->vol[V].s[level];
-            unsigned* tickets[kMaxVol * (kMaxVol - 1) / 2];
-            for (int q = 0; q < np; ++q) {
-                parts[q] = M->views[q]->part;
-                tickets[q] = M->views[q]->ticket;
-            }
+            for (int q = 0; q < np; ++q) parts[q] = M->views[q]->part;
             const Level& L = M->views[0]->lev[level];
-            HIP_TRY(launch_struct_multi(vols, M->n, ea.disp, parts, tickets, L.w, L.h, L.d, L.dp, L.vol_bytes,
+            HIP_TRY(launch_struct_multi(vols, M->n, ea.disp, parts, L.w, L.h, L.d, L.dp, L.vol_bytes,
                                         (float)M->params.eps_huber, M->dtype, s, ea.skip));
         }
-        for (int q0 = 0; q0 < np; q0 += kMaxJobs)
-            OCTMC_TRY(eval_group(args.data() + q0, std::min(kMaxJobs, np - q0), s, nullptr, !fused));
         const size_t nq = (size_t)M->n * na;
         const int nsum = grid_n(nq);
+        TicketSpec tickets{};  // the pairs' own structural launches clear them otherwise
+        for (int q = 0; fused && q < np; ++q) tickets.p[tickets.n++] = M->views[q]->ticket;
         hipLaunchKernelGGL(k_field_sum, dim3(nsum), dim3(kMB), 0, s, ea.disp, nq, M->sum_blk, ea.skip);
-        hipLaunchKernelGGL(k_field_sum_final, dim3(1), dim3(kMB), 0, s, M->sum_blk, nsum, M->fsum, ea.skip);
+        hipLaunchKernelGGL(k_field_sum_final, dim3(1), dim3(kMB), 0, s, M->sum_blk, nsum, M->fsum, tickets, ea.skip);
+        for (int q0 = 0; q0 < np; q0 += kMaxJobs)
+            OCTMC_TRY(eval_group(args.data() + q0, std::min(kMaxJobs, np - q0), s, nullptr, !fused));
         GatherSpec gs{};
         gs.n = M->n;
         int cnt[kMaxVol] = {};

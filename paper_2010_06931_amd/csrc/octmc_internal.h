@@ -213,11 +213,11 @@ hipError_t launch_combine(const CombineJobs& jobs, hipStream_t s);
 // each volume resampled once (n = 3 or 4; float32 storage, or 16-bit storage
 // at an even storage pitch dp: see struct_multi_supported); part[q] is pair
 // q's [na][8] partial buffer, the pairs (P, Q), P < Q, in lexicographic
-// order; ticket[q] is cleared for pair q's combination; skip (device flag, may be null): when nonzero the launch does nothing
+// order; skip (device flag, may be null): when nonzero the launch does nothing
 bool struct_multi_supported(int n, int dp, octmc_dtype dt);
-hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part,
-                               unsigned* const* ticket, int w, int h, int d, int dp, uint32_t vol_bytes, float eps_h,
-                               octmc_dtype dt, hipStream_t s, const int* skip = nullptr);
+hipError_t launch_struct_multi(const void* const* vol, int n, const float* disp, float* const* part, int w, int h,
+                               int d, int dp, uint32_t vol_bytes, float eps_h, octmc_dtype dt, hipStream_t s,
+                               const int* skip = nullptr);
 
 // preparation (kernels_prep.hip)
 // One level of the pyramids of one or two volumes with their images and validity.
