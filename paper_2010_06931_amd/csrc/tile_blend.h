@@ -279,7 +279,7 @@ __device__ __forceinline__ float row_sum_last(float x)
 
 // Depths per lane with 16-bit storage: eight (true), since a 128-bit load brings
 // twice the samples of a 64-bit one in the same time, unless windows of four
-// leave enough fewer positions unused (a window of four costs 1.2 times half of
+// leave enough fewer positions unused (a window of four costs 1.18 times half of
 // one of eight); four where an A-scan has fewer than eight samples.
 inline bool mx_eight(int d, int dp)
 {
